@@ -114,7 +114,7 @@ def draw(rng):
     if kind == "batch":
         n = rng.choice([256, 512])
         return dict(base, kind="batch", nx=n, ny=n, npoles=16, medium="sine", amp=0.02, tol=1e-8,
-                    steps=rng.choice([2, 3, 5]), problems=rng.choice([3, 5, 7]), workers=rng.choice([1, 2, 4]))
+                    steps=rng.choice([2, 3, 4]), problems=rng.choice([3, 5, 7]), workers=rng.choice([1, 2, 4]))
     if kind == "pairs":
         nx, ny = grid(512, 2)
         return dict(base, kind="pairs", nx=nx, ny=ny, ncomp=rng.choice([1, 2]), npoles=16, medium="grf",
