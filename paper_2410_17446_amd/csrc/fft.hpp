@@ -29,6 +29,7 @@
 // left every aligned read with one.
 #pragma once
 #include "cplx.hpp"
+#include "wave.hpp"
 
 template <typename T>
 __host__ __device__ constexpr int lds_run() {
@@ -220,53 +221,34 @@ __device__ __forceinline__ cx<T> odd_at(const cx<T>* buf, int n, int i) {
 }
 
 // Inclusive prefix sum of v over the NT threads t = 0..NT-1 of one transform
-// (groups of NT consecutive threads are independent).  Power-of-two NT: wave
-// shuffles, plus LDS across waves; scr holds NT/64 elements per group.  Other
-// NT (3 * 2^k lengths): Hillis-Steele in LDS; scr holds 2 NT elements per
-// group.  Contains __syncthreads: every thread of the workgroup must call it.
+// (groups of NT consecutive threads are independent).  The threads scan in
+// aligned segments of W lanes by DPP moves (W = NT, 64, or NT/3 for lengths
+// 3 * 2^k); with several segments their sums meet in LDS (scr: SIZE elements per
+// transform) behind one barrier, which every thread of the workgroup must reach.
+// (3 * 2^k lengths took log2(NT) Hillis-Steele steps with a barrier each: the row
+// pass of one 384^2 pole went from 32.9 to 26.6 us with this scan and the DPP sums.)
 template <int NT>
 struct ScanScratch {
   static constexpr bool POW2 = (NT & (NT - 1)) == 0;
-  static constexpr int SIZE = POW2 ? (NT > 64 ? NT / 64 : 1) : 2 * NT;
+  static constexpr int W = POW2 ? (NT < 64 ? NT : 64) : NT / 3;
+  static constexpr int SEG = NT / W;
+  static constexpr int SIZE = SEG;
 };
 
 template <typename T, int NT>
 __device__ __forceinline__ cx<T> group_scan(cx<T> v, cx<T>* scr, int t) {
-  if constexpr (!ScanScratch<NT>::POW2) {
-    cx<T>* a = scr;
-    cx<T>* b = scr + NT;
-    a[t] = v;
-    __syncthreads();
-#pragma unroll
-    for (int d = 1; d < NT; d <<= 1) {
-      const cx<T> x = (t >= d) ? a[t] + a[t - d] : a[t];
-      b[t] = x;
-      __syncthreads();
-      cx<T>* tmp = a;
-      a = b;
-      b = tmp;
-    }
-    const cx<T> r = a[t];
-    __syncthreads();
-    return r;
-  }
-  constexpr int W = NT < 64 ? NT : 64;
-#pragma unroll
-  for (int d = 1; d < W; d <<= 1) {
-    const T re = __shfl_up(v.re, d, W), im = __shfl_up(v.im, d, W);
-    if ((t & (W - 1)) >= d) {
-      v.re += re;
-      v.im += im;
-    }
-  }
-  if constexpr (NT > 64) {
-    const int w = t >> 6;
-    if ((t & 63) == 63) scr[w] = v;
+  constexpr int W = ScanScratch<NT>::W, SEG = ScanScratch<NT>::SEG;
+  v.re = lane_scan<T, W>(v.re);
+  v.im = lane_scan<T, W>(v.im);
+  if constexpr (SEG > 1) {
+    const int w = t / W;
+    if (t % W == W - 1) scr[w] = v;
     __syncthreads();
     cx<T> off = mk<T>(0, 0);
-    for (int i = 0; i < w; ++i) off = off + scr[i];
+#pragma unroll
+    for (int i = 0; i < SEG - 1; ++i)
+      if (i < w) off = off + scr[i];
     v = v + off;
-    __syncthreads();
   }
   return v;
 }
@@ -340,7 +322,9 @@ __device__ __forceinline__ void dst1_core_op(cx<T>* buf, const cx<T>* __restrict
   }
   cx<T> incl = group_scan<T, NT>(run, scr, t);
   const cx<T> base = (T)0.5 * f0 + (incl - run);  // X_1 plus the sums of earlier threads
-  __syncthreads();
+  // every thread has read its F before any X is written (a scan over several
+  // segments has had its barrier since)
+  if constexpr (ScanScratch<NT>::SEG == 1) __syncthreads();
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int k = 4 * t + 1 + i;

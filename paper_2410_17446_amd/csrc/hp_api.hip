@@ -74,7 +74,6 @@ struct hp_plan_s {
   void** uptr_scratch = nullptr;
   int* active_d = nullptr;
   double* est_d = nullptr;
-  int* reduce_done = nullptr;  // per pole: finished reduction workgroups of the round (zeroed workspace)
   double2* part_dots = nullptr;
   double* part_norm = nullptr;
   double* part_misc = nullptr;
@@ -266,7 +265,6 @@ void layout(hp_plan p, Ws& w) {
   p->X = w.take<c128>((size_t)K * fn);
   p->tmp1 = w.take<c128>(fn);
   p->tmp2 = w.take<c128>(fn);
-  p->reduce_done = w.take<int>(HP_MAXPOLES);  // inside the range cleared at creation
   p->st = w.take<PoleState>(K);
   p->st_scratch = w.take<PoleState>(1);
   p->uptr = w.take<void*>((size_t)K * (HP_MAXM + 1));
@@ -289,7 +287,7 @@ void derive(hp_plan p) {
   p->fieldn = p->geo.fsz * d.ncomp;
   const int rpw = 256 / (d.nx / 8) > 0 ? 256 / (d.nx / 8) : 1;
   p->nrowblk = (d.ny - 1 + rpw - 1) / rpw;
-  p->napplyblk = p->mixed ? row_apply_parts<float>(p->geo) : row_apply_parts<double>(p->geo);
+  p->napplyblk = p->mixed ? row_apply_blocks<float>(p->geo) : row_apply_blocks<double>(p->geo);
   p->nupdblk = update_blocks(p->fieldn);
   p->nopblk = op_blocks(p->geo);
   const double s = 1.0 / ((d.k0 * d.n0) * (d.k0 * d.n0));
@@ -380,7 +378,9 @@ cx<T>* fld(void* base, size_t idx, size_t fieldn) {
   return reinterpret_cast<cx<T>*>(base) + idx * fieldn;
 }
 
+// The pointer table serves the absorbing layers' dense stages only.
 int upload_uptr(hp_plan p) {
+  if (!p->pml) return HP_OK;
   hipError_t e = hipMemcpyAsync(p->uptr, p->uptr_h.data(), p->uptr_h.size() * sizeof(void*), hipMemcpyHostToDevice,
                                 p->stream);
   if (e != hipSuccess) return hip_fail(p, e, "upload uptr");
@@ -661,7 +661,7 @@ int run_poles(hp_plan p, const c128* w, const std::vector<int>& subset, bool* no
   cx<T>* Zb = reinterpret_cast<cx<T>*>(p->Z);
   cx<T>* Pb = reinterpret_cast<cx<T>*>(p->P);
   cx<T>* DZb = reinterpret_cast<cx<T>*>(p->DZ);
-  const cx<T>* const* up = reinterpret_cast<const cx<T>* const*>(p->uptr);
+  const Basis<cx<T>> basis{bR, reinterpret_cast<cx<T>*>(p->U), (size_t)(M + 1) * fn, fn};
   struct Flight {
     std::vector<int> poles;
     int slot;
@@ -736,14 +736,16 @@ int run_poles(hp_plan p, const c128* w, const std::vector<int>& subset, bool* no
     const int slot = (int)(next_iter & 1);
     const int na = (int)poles.size();
     int* ad = p->active_d + slot * HP_MAXPOLES;
-    int maxm = 0;
+    RoundList rl;
+    rl.n = na;
     Flight fl{poles, slot, next_iter, 0, std::vector<int>(na), std::vector<char>(na), {-1, -1, -1}, false};
     for (int a = 0; a < na; ++a) {
       const int mk_ = (int)std::min<long>(next_iter - since[poles[a]], M - 1);
-      maxm = std::max(maxm, mk_);
       fl.ms[a] = mk_;
       fl.sh[a] = p->uptr_h[(size_t)poles[a] * (HP_MAXM + 1)] == (void*)bR;
+      rl.e[a] = round_entry(poles[a], mk_, fl.sh[a]);
     }
+    for (int a = na; a < HP_MAXPOLES; ++a) rl.e[a] = 0;
     if (p->pml) {
       // absorbing layers: the dense stages (the first stores the list to ad),
       // then p = A_k z - ~v_m with the inner products, on physical fields
@@ -785,36 +787,34 @@ int run_poles(hp_plan p, const c128* w, const std::vector<int>& subset, bool* no
       }
       {
         Prof pr(p, HP_K_SMALL, 0.0);
-        launch_reduce_dots(p->pml_part, pml_apply_parts(d.nx), p->st, ad, na, maxm, p->reduce_done, p->stream);
+        launch_reduce_dots(p->pml_part, pml_apply_parts(d.nx), p->st, rl, p->stream);
       }
     } else {
       {
-        // the column pass takes the list in its arguments and stores it to ad
-        // for the kernels after it (no host-to-device copy per round)
+        // every kernel of the round takes the list in its arguments (no
+        // host-to-device copy per round)
         Prof pr(p, HP_K_COL, -1.0, &fl.pslot[0]);
-        launch_col<T, C>(up, Zb, zsp, zsi, DZb, dzsp, p->st, poles.data(), na, ad, p->mu_x, p->mu_y, twy, p->geo,
-                         p->sc, p->stream);
+        launch_col<T, C>(basis, Zb, zsp, zsi, DZb, dzsp, p->st, rl, p->mu_x, p->mu_y, twy, p->geo, p->sc, p->stream);
       }
       {
         Prof pr(p, HP_K_ROW_APPLY, -1.0, &fl.pslot[1]);
-        launch_row_apply<T, C>(Zb, zsp, zsi, DZb, dzsp, Pb, psp, up, coef_as<C>(p), p->st, ad, na, p->part_dots,
-                               twx, p->geo, p->sc, p->stream);
+        launch_row_apply<T, C>(Zb, zsp, zsi, DZb, dzsp, Pb, psp, basis, coef_as<C>(p), p->st, rl, p->part_dots, twx,
+                               p->geo, p->sc, p->stream);
       }
       {
         Prof pr(p, HP_K_SMALL, 0.0);
-        launch_reduce_dots(p->part_dots, p->napplyblk, p->st, ad, na, maxm, p->reduce_done, p->stream);
+        launch_reduce_dots(p->part_dots, p->napplyblk, p->st, rl, p->stream);
       }
     }
     {
       Prof pr(p, HP_K_UPDATE, -1.0, &fl.pslot[2]);
-      launch_update<T>(Pb, psp, reinterpret_cast<cx<T>* const*>(p->uptr), p->st, ad, na, p->part_norm, p->nupdblk,
-                       p->geo, p->stream);
+      launch_update<T>(Pb, psp, basis, p->st, rl, p->part_norm, p->nupdblk, p->geo, p->stream);
     }
     {
       Prof pr(p, HP_K_SMALL, 0.0);
       // flags go straight to host memory, tagged with the round
-      launch_arnoldi(p->st, ad, na, p->part_norm, p->nupdblk, M, p->ftag_hd + slot * HP_MAXPOLES, ++p->seq,
-                     p->est_d, p->stream);
+      launch_arnoldi(p->st, rl, p->part_norm, p->nupdblk, M, p->ftag_hd + slot * HP_MAXPOLES, ++p->seq, p->est_d,
+                     p->stream);
     }
     fl.seq = p->seq;
     q.push_back(std::move(fl));
@@ -1007,30 +1007,37 @@ int run_step_sqrt(hp_plan p, const c128* w, c128* out) {
   return noconv ? HP_WARN_NOCONV : HP_OK;
 }
 
-// The column pass reads flag, m, b_k and sigma_m of its pole and u_m from the
-// pointer table: set them for one free-space solve (pole slot 0, m = 0,
-// sigma_0 = 1), by a kernel, so that no host copy is needed.
-__global__ void k_prec_setup(PoleState* st, void** tbl, void* u0, c128 b) {
+// The column pass reads flag, b_k and sigma_m of its pole: set them for one
+// free-space solve (pole slot 0, m = 0, sigma_0 = 1), by a kernel, so that no host
+// copy is needed.
+__global__ void k_prec_setup(PoleState* st, c128 b) {
   if (threadIdx.x != 0) return;
   st->flag = 0;
   st->m = 0;
   st->bk = b;
   st->sigma[0] = 1.0;
-  tbl[0] = u0;
+}
+
+// The one-entry list of such a solve.
+RoundList one_solve() {
+  RoundList l;
+  l.n = 1;
+  for (int a = 0; a < HP_MAXPOLES; ++a) l.e[a] = 0;
+  l.e[0] = round_entry(0, 0, true);
+  return l;
 }
 
 // y = (Zbar_fs - b_k I)^{-1} x (pole < 0: b = 0), asynchronous, with the given
 // intermediate buffers: tmpR, zout (and dz for vector fields) R-domain fields,
-// st one pole state, tbl one basis pointer table, part the row pass's partial norms.
+// st one pole state, part the row pass's partial norms.
 template <typename T, typename C>
 void prec_into(hp_plan p, int pole, const c128* x, c128* y, cx<T>* tmpR, cx<T>* zout, cx<T>* dz, PoleState* st,
-               void** tbl, double* part) {
+               double* part) {
   const c128 b = pole < 0 ? mk(0.0, 0.0) : mk(p->poles[pole].re, p->poles[pole].im);
-  hipLaunchKernelGGL(k_prec_setup, dim3(1), dim3(64), 0, p->stream, st, tbl, (void*)tmpR, b);
+  hipLaunchKernelGGL(k_prec_setup, dim3(1), dim3(64), 0, p->stream, st, b);
   launch_row_fwd<T, C>(x, tmpR, part, reinterpret_cast<const cx<C>*>(p->tw_x), p->geo, p->stream);
-  const int zero = 0;
-  launch_col<T, C>(reinterpret_cast<const cx<T>* const*>(tbl), zout, 0, 0, dz, 0, st, &zero, 1, nullptr, p->mu_x,
-                   p->mu_y, reinterpret_cast<const cx<C>*>(p->tw_y), p->geo, p->sc, p->stream);
+  launch_col<T, C>(Basis<cx<T>>{tmpR, nullptr, 0, 0}, zout, 0, 0, dz, 0, st, one_solve(), p->mu_x, p->mu_y,
+                   reinterpret_cast<const cx<C>*>(p->tw_y), p->geo, p->sc, p->stream);
   launch_row_inv<T, C>(zout, y, reinterpret_cast<const cx<C>*>(p->tw_x), p->geo, tile_width<T>(), p->stream);
 }
 
@@ -1038,7 +1045,7 @@ void prec_into(hp_plan p, int pole, const c128* x, c128* y, cx<T>* tmpR, cx<T>* 
 template <typename T, typename C>
 void prec_ws(hp_plan p, int pole, const c128* x, c128* y) {
   prec_into<T, C>(p, pole, x, y, reinterpret_cast<cx<T>*>(p->tmpR), reinterpret_cast<cx<T>*>(p->P),
-                  reinterpret_cast<cx<T>*>(p->DZ), p->st_scratch, p->uptr_scratch, p->part_misc);
+                  reinterpret_cast<cx<T>*>(p->DZ), p->st_scratch, p->part_misc);
 }
 
 // Learned starting points of every pole for right-hand side w (HP_GUESS_LEARNED):
@@ -1123,31 +1130,22 @@ int get_solution(hp_plan p, int k, c128* x) {
 
 template <typename T, typename C>
 int apply_prec(hp_plan p, int pole, const c128* x, c128* y) {
-  PoleState h;
-  memset(&h, 0, sizeof(h));
-  h.bk = pole < 0 ? mk(0.0, 0.0) : mk(p->poles[pole].re, p->poles[pole].im);
-  h.sigma[0] = 1.0;
-  void* tbl[HP_MAXM + 1] = {nullptr};
-  tbl[0] = p->tmpR;
-  const int zero = 0;
-  if (p->pml) tbl[0] = const_cast<c128*>(x);
-  HPCHK(hipMemcpyAsync(p->st_scratch, &h, sizeof(h), hipMemcpyHostToDevice, p->stream));
-  HPCHK(hipMemcpyAsync(p->uptr_scratch, tbl, sizeof(tbl), hipMemcpyHostToDevice, p->stream));
   if (p->pml) {
+    PoleState h;
+    memset(&h, 0, sizeof(h));
+    h.bk = pole < 0 ? mk(0.0, 0.0) : mk(p->poles[pole].re, p->poles[pole].im);
+    h.sigma[0] = 1.0;
+    void* tbl[HP_MAXM + 1] = {nullptr};
+    tbl[0] = const_cast<c128*>(x);
+    const int zero = 0;
+    HPCHK(hipMemcpyAsync(p->st_scratch, &h, sizeof(h), hipMemcpyHostToDevice, p->stream));
+    HPCHK(hipMemcpyAsync(p->uptr_scratch, tbl, sizeof(tbl), hipMemcpyHostToDevice, p->stream));
     pml_prec(p, p->st_scratch, &zero, 1, nullptr, PmlRef{reinterpret_cast<c128* const*>(p->uptr_scratch), nullptr, 0, 0},
              PmlRef{nullptr, y, 0, 0}, reinterpret_cast<c128*>(p->P), p->pml_s);
-    HPCHK(hipGetLastError());
-    HPCHK(hipStreamSynchronize(p->stream));
-    return HP_OK;
+  } else {
+    prec_ws<T, C>(p, pole, x, y);
   }
-  launch_row_fwd<T, C>(x, reinterpret_cast<cx<T>*>(p->tmpR), p->part_misc, reinterpret_cast<const cx<C>*>(p->tw_x),
-                    p->geo, p->stream);
-  // the first basis slot of pole 0 in Z serves as output; the DZ slot as scratch
-  cx<T>* zout = reinterpret_cast<cx<T>*>(p->P);
-  launch_col<T, C>(reinterpret_cast<const cx<T>* const*>(p->uptr_scratch), zout, 0, 0, reinterpret_cast<cx<T>*>(p->DZ), 0,
-                p->st_scratch, &zero, 1, nullptr, p->mu_x, p->mu_y,
-                reinterpret_cast<const cx<C>*>(p->tw_y), p->geo, p->sc, p->stream);
-  launch_row_inv<T, C>(zout, y, reinterpret_cast<const cx<C>*>(p->tw_x), p->geo, tile_width<T>(), p->stream);
+  HPCHK(hipGetLastError());
   HPCHK(hipStreamSynchronize(p->stream));
   return HP_OK;
 }
@@ -1633,6 +1631,8 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
   p->pml = true;
   p->pml_sigma = sigma_max;
   p->prev_valid = false;
+  if (int rc = upload_uptr(p)) return rc;  // kept on the device from here on
+  HPCHK(hipStreamSynchronize(p->stream));
   return HP_OK;
 }
 
@@ -2032,7 +2032,7 @@ void hp_batch_destroy(hp_batch b) {
 // address is ever handed to kernels.
 
 constexpr size_t kScratchFieldBytes = 48ull << 20;  // R-domain fields: row transform, column pass out, D1y
-constexpr size_t kScratchSmallBytes = 1ull << 20;   // pole state, basis pointer table, partial norms
+constexpr size_t kScratchSmallBytes = 1ull << 20;   // pole state, partial norms
 static __device__ __align__(256) char scratch[kScratchFieldBytes + kScratchSmallBytes];
 
 namespace {
@@ -2074,10 +2074,8 @@ int apply_prec_noalloc(hp_plan p, int pole, const c128* x, c128* y) {
   cx<T>* dz = reinterpret_cast<cx<T>*>(base + 2 * fb);
   char* small = base + kScratchFieldBytes;
   PoleState* st = reinterpret_cast<PoleState*>(small);
-  void** tbl = reinterpret_cast<void**>(small + align256(sizeof(PoleState)));
-  double* part = reinterpret_cast<double*>(small + align256(sizeof(PoleState)) +
-                                           align256((HP_MAXM + 1) * sizeof(void*)));
-  prec_into<T, C>(p, pole, x, y, tmpR, zout, dz, st, tbl, part);
+  double* part = reinterpret_cast<double*>(small + align256(sizeof(PoleState)));
+  prec_into<T, C>(p, pole, x, y, tmpR, zout, dz, st, part);
   HPCHK(hipGetLastError());
   return HP_OK;
 }

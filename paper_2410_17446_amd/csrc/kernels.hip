@@ -242,10 +242,9 @@ struct ColWaves {
 
 template <typename T, typename C, int N, int NC, int LB>
 __global__ __launch_bounds__((ColCfg<T, C, N, LB>::WG), (ColWaves<C, N>::V)) void k_col(
-    const cx<T>* const* __restrict__ uptr, cx<T>* __restrict__ zbase, size_t zsp, size_t zsi,
-    cx<T>* __restrict__ dzbase, size_t dzsp, const PoleState* __restrict__ st, const PoleList list,
-    int* __restrict__ active_out, const double* __restrict__ mu_x, const double* __restrict__ mu_y,
-    const cx<C>* __restrict__ tw, size_t fsz, StencilCoef sc) {
+    const Basis<cx<T>> basis, cx<T>* __restrict__ zbase, size_t zsp, size_t zsi, cx<T>* __restrict__ dzbase,
+    size_t dzsp, const PoleState* __restrict__ st, const RoundList list, const double* __restrict__ mu_x,
+    const double* __restrict__ mu_y, const cx<C>* __restrict__ tw, size_t fsz, StencilCoef sc) {
   using CC = ColCfg<T, C, N, LB>;
   constexpr int NT = CC::NT, TW = CC::TW, GC = CC::GC, WG = CC::WG, S = TW / GC;
   constexpr int PL = CC::PLC;  // padded per-column stride
@@ -259,18 +258,12 @@ __global__ __launch_bounds__((ColCfg<T, C, N, LB>::WG), (ColWaves<C, N>::V)) voi
   const int tid = threadIdx.x;
   const int g = tid / NT, t = tid % NT;
   const C scale = (C)sqrt(2.0 / N);
-  // workgroup (0, 0) stores the pole list for the round's later kernels
-  const bool writer = active_out && blockIdx.x == 0 && blockIdx.y == 0;
-  const int k = list.k[blockIdx.y / NC];
-  if (st[k].flag) {
-    if (writer && tid < list.n) active_out[tid] = list.k[tid];
-    return;
-  }
-  const int m = st[k].m;
+  const int e = list.e[blockIdx.y / NC], k = round_pole(e), m = round_m(e);
   const c128 b = st[k].bk;
+  if (st[k].flag) return;
   const C sc2 = (C)st[k].sigma[m] * scale;
   const size_t tbase = comp * fsz + (size_t)tile * N * TW;  // this tile, component comp (ny == N)
-  const cx<T>* u = uptr[k * (HP_MAXM + 1) + m] + tbase;
+  const cx<T>* __restrict__ u = basis.at(e, m) + tbase;
   cx<T>* z = zbase + k * zsp + m * zsi + tbase;
   cx<T>* dz = (NC == 2) ? dzbase + k * dzsp + tbase : nullptr;
   // The loops below give consecutive threads the columns of a row in turn,
@@ -336,7 +329,6 @@ __global__ __launch_bounds__((ColCfg<T, C, N, LB>::WG), (ColWaves<C, N>::V)) voi
       }
     }
   }
-  if (writer && tid < list.n) active_out[tid] = list.k[tid];
 }
 
 // ------------------------------------------------------------------ row pass (medium part + inner products)
@@ -388,10 +380,17 @@ __device__ __forceinline__ cx<C> row_d1x(const cx<C>* b, int j, const StencilCoe
   return acc;
 }
 
+// Inner products a row workgroup collects in LDS between two barriers.
+constexpr int DOT_B = 16;
+
+// Threads of a row workgroup: 256, but 64 for n <= 128, where a field has too few
+// rows to give every CU a 256-thread workgroup.
+constexpr int apply_threads(int n) { return n <= 128 ? 64 : 256; }
+
 template <int N, int NC>
 struct ApplyCfg {
   static constexpr int NT = N / 8;
-  static constexpr int G0 = (256 / NT) / NC * NC;
+  static constexpr int G0 = (apply_threads(N) / NT) / NC * NC;
   static constexpr int GROUPS = G0 < NC ? NC : G0;  // transforms per workgroup (NC per row)
   static constexpr int ROWS = GROUPS / NC;
   static constexpr int WG = GROUPS * NT;
@@ -400,29 +399,32 @@ struct ApplyCfg {
   static_assert(NT >= 8, "the stencil's interior points assume at least 8 threads per row");
 };
 
-// Waves per SIMD the register allocation must allow: scalar fields four (128
-// VGPRs; 12 bytes spill at n = 128) for 2^k up to 1024, else three (complex128
+// Waves per SIMD the register allocation must allow: two up to 256 (a field has no
+// more of them to offer, and the basis vectors' loads want the registers); above,
+// scalar fields four (128 VGPRs) for 2^k up to 1024, else three (complex128
 // at 2048: two); vector fields four, which lets two 512-thread workgroups share
 // a CU at 2048 (their LDS, one buffer per component, fits twice).
 template <typename C, int N, int NC>
 struct ApplyWaves {
   static constexpr bool POW2 = (N & (N - 1)) == 0;
-  static constexpr int V = NC == 2 ? 4
-                                   : ((N <= 1024 && POW2) ? 4 : (sizeof(C) == 4 || N < 2048 ? 3 : 2));
+  static constexpr int V = N <= 256 ? 2
+                           : NC == 2 ? 4
+                                     : ((N <= 1024 && POW2) ? 4 : (sizeof(C) == 4 || N < 2048 ? 3 : 2));
 };
 
 template <typename T, typename C, int N, int NC>
 __global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) void k_row_apply(
     const cx<T>* __restrict__ zbase, size_t zsp, size_t zsi, const cx<T>* __restrict__ dzbase, size_t dzsp,
-    cx<T>* __restrict__ pbase, size_t psp, const cx<T>* const* __restrict__ uptr, const C* __restrict__ coef,
-    const PoleState* __restrict__ st, const int* __restrict__ active, int nactive, int nrb, double2* __restrict__ part,
-    int nparts, const cx<C>* __restrict__ tw, int ny, size_t fsz, StencilCoef sc) {
+    cx<T>* __restrict__ pbase, size_t psp, const Basis<cx<T>> basis, const C* __restrict__ coef,
+    const PoleState* __restrict__ st, const RoundList list, int nrb, double2* __restrict__ part,
+    const cx<C>* __restrict__ tw, int ny, size_t fsz, StencilCoef sc) {
   using AC = ApplyCfg<N, NC>;
   constexpr int NT = AC::NT, GROUPS = AC::GROUPS, ROWS = AC::ROWS, TW = Tile<T>::W;
   constexpr int PT = N / NT;  // values per thread per row
   constexpr int PL = plen<C>(N);
   __shared__ cx<C> lds[GROUPS * PL];
   __shared__ cx<C> scr[GROUPS * AC::SCR];
+  __shared__ double dsum[AC::WAVES > 1 ? DOT_B : 1][AC::WAVES][4];
   const int g = threadIdx.x / NT, t = threadIdx.x % NT;
   const int comp = g % NC;
   // XCD-aware order (workgroups go round-robin to the eight XCDs): the
@@ -431,13 +433,12 @@ __global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) v
   // coefficients (and, in a first cycle, the shared basis vector) come from
   // that XCD's L2 for all but the first pole
   const int xcd = blockIdx.x % 8, q = blockIdx.x / 8;
-  const int rb = (q / nactive) * 8 + xcd;
+  const int rb = (q / list.n) * 8 + xcd;
   if (rb >= nrb) return;
   const int row = 1 + rb * ROWS + g / NC;
   const bool valid = row < ny;
-  const int k = active[q % nactive];
+  const int e = list.e[q % list.n], k = round_pole(e), m = round_m(e);
   if (st[k].flag) return;
-  const int m = st[k].m;
   cx<C>* buf = lds + g * PL;
   cx<C>* sg = scr + g * AC::SCR;
   const C scale = (C)sqrt(2.0 / N);
@@ -569,22 +570,39 @@ __global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) v
   }
   // <u_i, p> and <u_i, u_m>, i = 0..m: the new direction's projections and
   // the reorthogonalisation of the provisional u_m, from the same reads of the
-  // basis.  Partial sums per wave (no workgroup barrier).
-  cx<T> um[PT];
-  {
-    const cx<T>* u = uptr[k * (HP_MAXM + 1) + m];
+  // basis.  Up to 256 the next vector's loads are in flight while the current one's
+  // products are reduced (above, the other waves of the CU hide them); the waves'
+  // sums meet in LDS once per DOT_B vectors, so a workgroup leaves one partial sum
+  // per product.
+  constexpr bool AHEAD = N <= 256;
+  cx<T> um[PT], un[PT];
+  auto load_u = [&](int i, cx<T>* v) {
+    const cx<T>* __restrict__ u = basis.at(e, i);
 #pragma unroll
-    for (int s = 0; s < PT; ++s) um[s] = valid ? u[toff.at(s)] : czero<T>();
-  }
+    for (int s = 0; s < PT; ++s) v[s] = valid ? u[toff.at(s)] : czero<T>();
+  };
+  load_u(m, um);
+  if (AHEAD && m > 0) load_u(0, un);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int slot = rb * AC::WAVES + wave;
-  for (int i = 0; i <= m; ++i) {
-    const cx<T>* u = uptr[k * (HP_MAXM + 1) + i];
-    double pr = 0.0, pi = 0.0, qr = 0.0, qi = 0.0;
-    if (valid) {
+  double* out = reinterpret_cast<double*>(part) + ((size_t)k * (HP_MAXM + 1) * 2 * nrb + rb) * 2;
+  for (int i0 = 0; i0 <= m; i0 += DOT_B) {
+    const int ie = min(m + 1, i0 + DOT_B);
+    for (int i = i0; i < ie; ++i) {
+      double pr = 0.0, pi = 0.0, qr = 0.0, qi = 0.0;
+      cx<T> uc[PT];
+      if (i == m) {
+#pragma unroll
+        for (int s = 0; s < PT; ++s) uc[s] = um[s];
+      } else if constexpr (AHEAD) {
+#pragma unroll
+        for (int s = 0; s < PT; ++s) uc[s] = un[s];
+        if (i + 1 < m) load_u(i + 1, un);
+      } else {
+        load_u(i, uc);
+      }
 #pragma unroll
       for (int s = 0; s < PT; ++s) {
-        const cx<double> a = cvt<double>(i == m ? um[s] : u[toff.at(s)]);
+        const cx<double> a = cvt<double>(uc[s]);
         const cx<double> bp = cvt<double>(NC == 1 ? pv[s] : pval(s));
         const cx<double> bq = cvt<double>(um[s]);
         pr += a.re * bp.re + a.im * bp.im;
@@ -592,15 +610,23 @@ __global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) v
         qr += a.re * bq.re + a.im * bq.im;
         qi += a.re * bq.im - a.im * bq.re;
       }
+      const double r = wave_sum4(pr, pi, qr, qi);
+      if (lane < 4) {
+        if constexpr (AC::WAVES == 1)
+          out[((size_t)(2 * i + (lane >> 1)) * nrb) * 2 + (lane & 1)] = r;
+        else
+          dsum[i - i0][wave][lane] = r;
+      }
     }
-    pr = wave_sum(pr);
-    pi = wave_sum(pi);
-    qr = wave_sum(qr);
-    qi = wave_sum(qi);
-    if (lane == 0) {
-      const size_t base = (((size_t)k * (HP_MAXM + 1) + i) * 2) * nparts + slot;
-      part[base] = make_double2(pr, pi);
-      part[base + nparts] = make_double2(qr, qi);
+    if constexpr (AC::WAVES > 1) {
+      __syncthreads();
+      for (int x = threadIdx.x; x < 4 * (ie - i0); x += AC::WG) {
+        double r = dsum[x >> 2][0][x & 3];
+#pragma unroll
+        for (int w = 1; w < AC::WAVES; ++w) r += dsum[x >> 2][w][x & 3];
+        out[((size_t)(2 * (i0 + (x >> 2)) + ((x >> 1) & 1)) * nrb) * 2 + (x & 1)] = r;
+      }
+      __syncthreads();
     }
   }
 }
@@ -608,61 +634,69 @@ __global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) v
 // ------------------------------------------------------------------ Gram-Schmidt update
 
 constexpr int UPD_WG = 256;
-constexpr int UPD_E = 4;
 
 // u_{m+1} = cu_{m+1} p + sum_{i<=m} cu_i u_i, and (delayed reorthogonalisation)
-// u_m <- sum_{i<=m} cv_i u_i in place; partial |u_{m+1}|^2.
-template <typename T>
+// u_m <- sum_{i<=m} cv_i u_i in place; partial |u_{m+1}|^2.  E elements per thread,
+// UPD_WG apart, and two basis vectors at a time, so that their loads are in flight
+// together.
+template <typename T, int E>
 __global__ __launch_bounds__(UPD_WG) void k_update(const cx<T>* __restrict__ pbase, size_t psp,
-                                                   cx<T>* const* __restrict__ uptr, const PoleState* __restrict__ st,
-                                                   const int* __restrict__ active, double* __restrict__ part, int nblk,
+                                                   const Basis<cx<T>> basis, const PoleState* __restrict__ st,
+                                                   const RoundList list, double* __restrict__ part, int nblk,
                                                    size_t total) {
   __shared__ c128 cf[HP_MAXM + 2];
   __shared__ c128 cv[HP_MAXM + 1];
-  __shared__ cx<T>* up[HP_MAXM + 2];
   __shared__ double red[UPD_WG / 64];
-  const int k = active[blockIdx.y];
+  const int en = list.e[blockIdx.y], k = round_pole(en), m = round_m(en);
   if (st[k].flag) return;
-  const int m = st[k].m;
-  const int corr = st[k].correct;
-  for (int i = threadIdx.x; i <= m + 1; i += UPD_WG) {
-    cf[i] = st[k].cu[i];
-    up[i] = uptr[k * (HP_MAXM + 1) + i];
-    if (i <= m) cv[i] = st[k].cv[i];
-  }
+  const int corr = m > 0;
+  if ((int)threadIdx.x <= m + 1) cf[threadIdx.x] = st[k].cu[threadIdx.x];
+  if ((int)threadIdx.x <= m) cv[threadIdx.x] = st[k].cv[threadIdx.x];
   __syncthreads();
   const cx<T>* p = pbase + k * psp;
-  cx<T>* out = up[m + 1];
-  cx<T>* um = up[m];
+  cx<T>* out = basis.at(en, m + 1);
+  cx<T>* um = basis.at(en, m);
   double nrm = 0.0;
-  // UPD_E elements per thread, UPD_WG apart, so that each basis vector's
-  // loads are in flight together
-  const size_t chunk = (size_t)UPD_WG * UPD_E;
+  const size_t chunk = (size_t)UPD_WG * E;
   for (size_t base = (size_t)blockIdx.x * chunk + threadIdx.x; base < total; base += (size_t)gridDim.x * chunk) {
-    cx<double> v[UPD_E], c[UPD_E];
+    cx<double> v[E], c[E];
 #pragma unroll
-    for (int e = 0; e < UPD_E; ++e) {
+    for (int e = 0; e < E; ++e) {
       const size_t idx = base + (size_t)e * UPD_WG;
       v[e] = (idx < total) ? cf[m + 1] * cvt<double>(p[idx]) : mk(0.0, 0.0);
       c[e] = mk(0.0, 0.0);
     }
-    for (int i = 0; i <= m; ++i) {
-      const cx<T>* ui = up[i];
-      cx<double> a[UPD_E];
-#pragma unroll
-      for (int e = 0; e < UPD_E; ++e) {
-        const size_t idx = base + (size_t)e * UPD_WG;
-        a[e] = (idx < total) ? cvt<double>(ui[idx]) : mk(0.0, 0.0);
-      }
+    auto add = [&](int i, const cx<T>* a) {
       const c128 fi = cf[i], gi = cv[i];
 #pragma unroll
-      for (int e = 0; e < UPD_E; ++e) {
-        v[e] = v[e] + fi * a[e];
-        c[e] = c[e] + gi * a[e];
+      for (int e = 0; e < E; ++e) {
+        v[e] = v[e] + fi * cvt<double>(a[e]);
+        c[e] = c[e] + gi * cvt<double>(a[e]);
       }
+    };
+    auto load = [&](int i, cx<T>* a) {
+      const cx<T>* ui = basis.at(en, i);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const size_t idx = base + (size_t)e * UPD_WG;
+        a[e] = (idx < total) ? ui[idx] : czero<T>();
+      }
+    };
+    int i = 0;
+    for (; i + 1 <= m; i += 2) {
+      cx<T> a[E], b[E];
+      load(i, a);
+      load(i + 1, b);
+      add(i, a);
+      add(i + 1, b);
+    }
+    if (i <= m) {
+      cx<T> a[E];
+      load(i, a);
+      add(i, a);
     }
 #pragma unroll
-    for (int e = 0; e < UPD_E; ++e) {
+    for (int e = 0; e < E; ++e) {
       const size_t idx = base + (size_t)e * UPD_WG;
       if (idx >= total) continue;
       const cx<T> r = cvt<T>(v[e]);
@@ -677,8 +711,15 @@ __global__ __launch_bounds__(UPD_WG) void k_update(const cx<T>* __restrict__ pba
 
 // ------------------------------------------------------------------ reductions / small FP64 kernels
 
-// Sum the partial inner products, then (one thread) the delayed
-// reorthogonalisation algebra of step m in FP64:
+// v of lane l of the wave (l uniform)
+__device__ __forceinline__ double lane_get(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+__device__ __forceinline__ c128 lane_get(c128 v, int l) { return mk(lane_get(v.re, l), lane_get(v.im, l)); }
+
+// Sum the partial inner products of one pole, then the delayed
+// reorthogonalisation algebra of its step m in FP64:
 //   s_i = <v_i, ~v_m>, t = <~v_m, ~v_m>, rho^2 = t - sum |s_i|^2,
 //   v_m = (~v_m - sum s_i v_i) / rho,
 //   column m-1:  H[i][m-1] += h~ s_i,  H[m][m-1] = h~ rho  (h~ = old H[m][m-1]),
@@ -686,135 +727,110 @@ __global__ __launch_bounds__(UPD_WG) void k_update(const cx<T>* __restrict__ pba
 //   A M^-1 v_m = (~v_m + p - sum_i s_i A M^-1 v_i) / rho   (A M^-1 ~v_m = ~v_m + p),
 //   H[l][m] = <v_l, A M^-1 v_m>, u_{m+1} = A M^-1 v_m - sum_l H[l][m] v_l,
 // expressed as coefficients of the stored vectors for the update kernel.
-// <u_i, p> and <u_i, u_m>: one block per (i, slot) pair sums the row pass's
-// partials in a fixed order.
-// The correction algebra of pole k's step from its reduced inner products
-// (run by the last reduction workgroup of the pole, 256 threads).
-__device__ __forceinline__ void prep_pole(PoleState* __restrict__ st, int k) {
-  __shared__ c128 P[HP_MAXM + 1], Q[HP_MAXM + 1];
-  __shared__ c128 sv[HP_MAXM], cc[HP_MAXM + 1], h[HP_MAXM + 1];
-  const int m = st[k].m;
-  for (int i = threadIdx.x; i <= m; i += 256) {
-    P[i] = st[k].Pd[i];
-    Q[i] = st[k].Qd[i];
-  }
-  __syncthreads();
+//
+// One workgroup per pole (the row pass leaves one partial per workgroup, so a
+// wave sums a product of 1024^2 in eight loads a lane): wave w takes the products
+// i = w, w + 16, ..., then every wave holds s and c, lane i entry i, and the rows
+// l = w, w + 16, ... of the Hessenberg column are wave sums too, so the chain has
+// two barriers and no loop over the basis in one thread.  Latency-bound: 9.5 us
+// at 64^2 and 11.5 us at 1024^2 when 2 (m + 1) workgroups a pole met in an
+// atomic counter and one thread ran the sums.
+constexpr int RED_WG = 1024;
+__global__ __launch_bounds__(RED_WG) void k_reduce_dots(const double2* __restrict__ part, int nparts,
+                                                        PoleState* __restrict__ st, const RoundList list) {
+  constexpr int LD = HP_MAXM + 1, NW = RED_WG / 64;
+  __shared__ c128 PQ[HP_MAXM + 1][2];
+  __shared__ c128 R[HP_MAXM + 1];
+  const int e = list.e[blockIdx.x], k = round_pole(e), m = round_m(e);
   PoleState& S = st[k];
-  constexpr int LD = HP_MAXM + 1;
-  c128* Hr = S.Hraw;
-  __shared__ double sh[4];  // rho, gamma (re, im), h~
-  __shared__ double sig[HP_MAXM + 1];
-  const int tid = threadIdx.x;
-  const double sm = S.sigma[m];
-  for (int i = tid; i <= m; i += 256) sig[i] = S.sigma[i];
-  __syncthreads();
-  for (int i = tid; i < m; i += 256) {
-    sv[i] = (sig[i] * sm) * Q[i];
-    cc[i] = sig[i] * P[i];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // what the algebra needs of the state, in flight during the sums
+  const double sig = lane <= m ? S.sigma[lane] : 0.0;
+  const c128* Hr = S.Hraw;
+  const c128 h0 = (lane < m && wave <= m) ? Hr[wave + lane * LD] : mk(0.0, 0.0);
+  const double hsub = m > 0 ? Hr[m + (m - 1) * LD].re : 0.0;
+  const c128 g0 = S.g[0];
+  if (S.flag) return;
+  for (int i = wave; i <= m; i += NW) {
+    const double2* src = part + (((size_t)k * LD + i) * 2) * nparts;
+    double a[4][4] = {};
+    int b = lane;
+    for (; b + 3 * 64 < nparts; b += 4 * 64) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double2 p = src[b + u * 64], q = src[nparts + b + u * 64];
+        a[u][0] += p.x;
+        a[u][1] += p.y;
+        a[u][2] += q.x;
+        a[u][3] += q.y;
+      }
+    }
+    for (; b < nparts; b += 64) {
+      const double2 p = src[b], q = src[nparts + b];
+      a[0][0] += p.x;
+      a[0][1] += p.y;
+      a[0][2] += q.x;
+      a[0][3] += q.y;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) a[0][v] += a[1][v] + (a[2][v] + a[3][v]);
+    const double r = wave_sum4(a[0][0], a[0][1], a[0][2], a[0][3]);
+    if (lane < 4) reinterpret_cast<double*>(&PQ[i][lane >> 1])[lane & 1] = r;
   }
   __syncthreads();
-  if (tid == 0) {
-    double ssum = 0.0;
-    for (int i = 0; i < m; ++i) ssum += abs2(sv[i]);
-    double rho2 = sm * sm * Q[m].re - ssum;
-    if (!(rho2 > 1e-300)) rho2 = 1e-300;
-    const double rho = sqrt(rho2);
-    c128 cm = sm * P[m];
-    for (int i = 0; i < m; ++i) cm = cm - cmulc(sv[i], cc[i]);
-    cc[m] = (1.0 / rho) * cm;
-    sh[0] = rho;
-    sh[3] = (m > 0) ? Hr[m + (m - 1) * LD].re : 0.0;
-    S.Rc[m + m * LD] = mk(rho, 0.0);
-    if (m == 0) S.g[0] = rho * S.g[0];
+  // lane i: s_i, c_i (i < m); every wave
+  const double sm = lane_get(sig, m);
+  const c128 Pm = PQ[m][0], Qm = PQ[m][1];
+  c128 sv = mk(0.0, 0.0), cc = mk(0.0, 0.0);
+  if (lane < m) {
+    sv = (sig * sm) * PQ[lane][1];
+    cc = sig * PQ[lane][0];
+  }
+  const c128 sc = cmulc(sv, cc);
+  const double t = wave_sum4(abs2(sv), sc.re, sc.im, 0.0);
+  double rho2 = sm * sm * Qm.re - lane_get(t, 0);
+  if (!(rho2 > 1e-300)) rho2 = 1e-300;
+  const double rho = sqrt(rho2), irho = 1.0 / rho;
+  const c128 cm = irho * (sm * Pm - mk(lane_get(t, 1), lane_get(t, 2)));
+  // column m: h_l = (<v_l, ~v_m> + <v_l, p> - A_l) / rho, A_l = sum_{i<m, i>=l-1} s_i H[l][i],
+  // with column m-1 of H as corrected
+  for (int l = wave; l <= m; l += NW) {
+    c128 hv = l == wave ? h0 : (lane < m ? Hr[l + lane * LD] : mk(0.0, 0.0));
+    const c128 sl = l < m ? lane_get(sv, l) : mk(rho, 0.0);
+    if (lane == m - 1) hv = l < m ? hv + hsub * sl : mk(hsub * rho, 0.0);
+    const c128 a = (lane < m && lane >= l - 1) ? sv * hv : mk(0.0, 0.0);
+    const double r = wave_sum4(a.re, a.im, 0.0, 0.0);
+    const c128 A = mk(lane_get(r, 0), lane_get(r, 1));
+    const c128 h = irho * (sl + (l < m ? lane_get(cc, l) : cm) - A);
+    if (lane == 0) {
+      S.Hraw[l + m * LD] = h;
+      R[l] = irho * A + h;
+    }
   }
   __syncthreads();
-  const double rho = sh[0], irho = 1.0 / rho;
-  // Rc column m; correction of Hessenberg column m-1
-  for (int i = tid; i < m; i += 256) {
-    S.Rc[i + m * LD] = sv[i];
-    Hr[i + (m - 1) * LD] = Hr[i + (m - 1) * LD] + sh[3] * sv[i];
-  }
-  __syncthreads();
-  if (tid == 0 && m > 0) Hr[m + (m - 1) * LD] = mk(sh[3] * rho, 0.0);
-  __syncthreads();
-  // column m: h_l = (<v_l, ~v_m> + <v_l, p> - A_l) / rho, A_l = sum_{i<m, i>=l-1} s_i H[l][i]
-  for (int l = tid; l <= m; l += 256) {
-    c128 A = mk(0.0, 0.0);
-    for (int i = (l > 0 ? l - 1 : 0); i < m; ++i) A = A + sv[i] * Hr[l + i * LD];
-    const c128 base = (l < m) ? sv[l] + cc[l] : mk(rho, 0.0) + cc[m];
-    h[l] = irho * (base - A);
-    Hr[l + m * LD] = h[l];
-    P[l] = irho * A + h[l];  // A_l / rho + h_l (P no longer needed)
-  }
-  __syncthreads();
-  const c128 gam = P[m];
+  if (wave != 0) return;
+  const c128 gam = R[m];
   // u_{m+1} = (1/rho) p + (1 - gam)/rho ~v_m + sum_{l<m} (gam s_l / rho - A_l / rho - h_l) v_l
-  for (int l = tid; l < m; l += 256) {
-    S.cu[l] = sig[l] * (irho * (gam * sv[l]) - P[l]);
-    S.cv[l] = (-sig[l] * irho) * sv[l];
+  if (lane < m) {
+    S.cu[lane] = sig * (irho * (gam * sv) - R[lane]);
+    S.cv[lane] = (-sig * irho) * sv;
+    S.Rc[lane + m * LD] = sv;
+    S.Hraw[lane + (m - 1) * LD] = Hr[lane + (m - 1) * LD] + hsub * sv;
   }
-  if (tid == 0) {
+  if (lane == 0) {
+    S.Rc[m + m * LD] = mk(rho, 0.0);
     S.cu[m] = (sm * irho) * (mk(1.0, 0.0) - gam);
     S.cu[m + 1] = mk(irho, 0.0);
     if (m == 0) {
       // v_0 = ~v_0 / rho rescales the (possibly shared) stored vector
+      S.g[0] = rho * g0;
       S.sigma[0] = sm * irho;
-      S.correct = 0;
     } else {
+      S.Hraw[m + (m - 1) * LD] = mk(hsub * rho, 0.0);
       S.cv[m] = mk(sm * irho, 0.0);
       S.sigma[m] = 1.0;
-      S.correct = 1;
     }
   }
-}
-
-__global__ __launch_bounds__(256) void k_reduce_pairs(const double2* __restrict__ part, int nparts,
-                                                      PoleState* __restrict__ st, const int* __restrict__ active,
-                                                      int* __restrict__ done) {
-  __shared__ double red[4];
-  __shared__ int last;
-  const int k = active[blockIdx.y];
-  if (st[k].flag) return;
-  const int m = st[k].m;
-  const int i = blockIdx.x >> 1, slot = blockIdx.x & 1;
-  if (i > m) return;
-  const double2* src = part + (((size_t)k * (HP_MAXM + 1) + i) * 2 + slot) * nparts;
-  double re = 0.0, im = 0.0;
-  {
-    double ar[4] = {0, 0, 0, 0}, ai[4] = {0, 0, 0, 0};
-    int b = threadIdx.x;
-    for (; b + 3 * 256 < nparts; b += 4 * 256) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const double2 v = src[b + u * 256];
-        ar[u] += v.x;
-        ai[u] += v.y;
-      }
-    }
-    for (; b < nparts; b += 256) {
-      ar[0] += src[b].x;
-      ai[0] += src[b].y;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      re += ar[u];
-      im += ai[u];
-    }
-  }
-  re = block_sum<256>(re, red);
-  im = block_sum<256>(im, red);
-  // the last of the pole's 2 (m + 1) workgroups (counted in done[k], which it
-  // clears again) continues with the correction algebra
-  if (threadIdx.x == 0) {
-    (slot ? st[k].Qd : st[k].Pd)[i] = mk(re, im);
-    __threadfence();
-    last = atomicAdd(&done[k], 1) == 2 * (m + 1) - 1;
-  }
-  __syncthreads();
-  if (!last) return;
-  if (threadIdx.x == 0) done[k] = 0;
-  __threadfence();
-  prep_pole(st, k);
 }
 
 __device__ __forceinline__ void givens(c128 a, double b, double& c, c128& sn, c128& r) {
@@ -836,113 +852,116 @@ __device__ __forceinline__ void givens(c128 a, double b, double& c, c128& sn, c1
 // Upper triangle of an n x n matrix packed by columns: (r, c), r <= c.
 __device__ __forceinline__ int pk(int r, int c) { return c * (c + 1) / 2 + r; }
 
-// Back substitution R x = rhs (R packed upper triangular, n <= 64) by the one
-// wave of the block: lane l keeps rhs[l] in a register, x[i] is broadcast by a
-// shuffle; x is written to LDS.  rhs is not modified.
+// Back substitution R x = rhs (R packed upper triangular, n <= 64) by the first
+// wave of the block: lane l keeps rhs[l] in a register and x[i] reaches it by a
+// lane read; x is written to LDS.  rhs is not modified.
 __device__ void upper_solve(const c128* __restrict__ R, const c128* rhs, c128* x, int n) {
   const int l = threadIdx.x;
-  c128 r = (l < n) ? rhs[l] : mk(0.0, 0.0);
-  for (int i = n - 1; i >= 0; --i) {
-    c128 xi = mk(0.0, 0.0);
-    if (l == i) {
-      const c128 d = R[pk(i, i)];
-      xi = (abs2(d) > 0.0) ? cdiv(r, d) : mk(0.0, 0.0);
-      x[i] = xi;
+  if (l < 64) {
+    c128 r = (l < n) ? rhs[l] : mk(0.0, 0.0);
+    // lane l divides by its own diagonal entry; the inverse is ready before the chain
+    const c128 d = (l < n) ? R[pk(l, l)] : mk(1.0, 0.0);
+    c128 col = (l < n) ? R[pk(l, n - 1)] : mk(0.0, 0.0);  // entry l of column i, one step ahead
+    for (int i = n - 1; i >= 0; --i) {
+      const c128 di = lane_get(d, i), ri = lane_get(r, i);
+      const c128 xi = (abs2(di) > 0.0) ? cdiv(ri, di) : mk(0.0, 0.0);
+      const c128 ci = col;
+      if (l < i) col = R[pk(l, i - 1)];
+      if (l == i) x[i] = xi;
+      if (l < i) r = r - ci * xi;
     }
-    xi.re = __shfl(xi.re, i, 64);
-    xi.im = __shfl(xi.im, i, 64);
-    if (l < i) r = r - R[pk(l, i)] * xi;
   }
   __syncthreads();
 }
 
-__global__ __launch_bounds__(64) void k_arnoldi(PoleState* __restrict__ st, const int* __restrict__ active,
-                                                const double* __restrict__ part, int nblk, int restart,
-                                                unsigned long long* __restrict__ ftag, unsigned long long seq,
-                                                double* __restrict__ ests) {
-  __shared__ c128 c1[HP_MAXM + 2], c2[HP_MAXM + 2], sn[HP_MAXM], rhs[HP_MAXM + 1], y[HP_MAXM];
-  __shared__ double cs[HP_MAXM];
+// Hessenberg column m, its rotations, the estimate and the flag of one pole.
+// Wave 0 keeps the columns, cosines and sines in registers (lane i entry i) and
+// walks the rotations with lane reads, columns m-1 and m together; the other
+// waves only help to sum the partial norms and to load the triangles at a
+// cycle's end.
+constexpr int ARN_WG = 256;
+__global__ __launch_bounds__(ARN_WG) void k_arnoldi(PoleState* __restrict__ st, const RoundList list,
+                                                    const double* __restrict__ part, int nblk, int restart,
+                                                    unsigned long long* __restrict__ ftag, unsigned long long seq,
+                                                    double* __restrict__ ests) {
+  __shared__ c128 c1[HP_MAXM + 1], c2[HP_MAXM + 1], rhs[HP_MAXM + 1], y[HP_MAXM];
+  __shared__ double red[ARN_WG / 64];
   __shared__ int flag_s;
-  const int k = active[blockIdx.x];
-  if (st[k].flag) return;
+  const int en = list.e[blockIdx.x], k = round_pole(en), m = round_m(en);
   const int tid = threadIdx.x;
   PoleState& S = st[k];
   constexpr int LD = HP_MAXM + 1;
-  const int m = S.m;
-  // scalars thread 0 needs, loaded up front so their latency overlaps the reduction
-  const c128 gpre_m1 = (tid == 0 && m >= 1) ? S.gpre[m - 1] : mk(0.0, 0.0);
-  const c128 g_m = (tid == 0) ? S.g[m] : mk(0.0, 0.0);
+  // the columns and scalars, in flight during the sum (lane i < 64; entry 64 of a
+  // column is its subdiagonal, set here)
+  c128 x1 = mk(0.0, 0.0), x2 = x1, xs = x1, g_m1 = x1, g_m = x1;
+  double xc = 0.0;
+  if (tid < 64) {
+    if (tid <= m) {
+      x2 = S.Hraw[tid + m * LD];
+      if (m >= 1) x1 = S.Hraw[tid + (m - 1) * LD];
+    }
+    if (tid < m) {
+      xc = S.cs[tid];
+      xs = S.sn[tid];
+    }
+    if (m >= 1) g_m1 = S.gpre[m - 1];
+    g_m = S.g[m];
+  }
   const int fixed = S.fixed, total = S.total;
   const double tol = S.tol;
+  if (S.flag) return;
   double s = 0.0;
   {
-    // eight independent accumulators keep eight loads in flight per thread
-    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    double acc[4] = {0, 0, 0, 0};
     const double* src = part + (size_t)k * nblk;
     int b = tid;
-    for (; b + 7 * 64 < nblk; b += 8 * 64) {
+    for (; b + 3 * ARN_WG < nblk; b += 4 * ARN_WG) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) acc[u] += src[b + u * 64];
+      for (int u = 0; u < 4; ++u) acc[u] += src[b + u * ARN_WG];
     }
-    for (; b < nblk; b += 64) acc[0] += src[b];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += acc[u];
+    for (; b < nblk; b += ARN_WG) acc[0] += src[b];
+    s = wave_sum((acc[0] + acc[1]) + (acc[2] + acc[3]));
   }
-  s = wave_sum(s);
-  for (int i = tid; i <= m; i += 64) {
-    c2[i] = S.Hraw[i + m * LD];
-    if (m >= 1) c1[i] = S.Hraw[i + (m - 1) * LD];
-  }
-  for (int i = tid; i < m; i += 64) {
-    cs[i] = S.cs[i];
-    sn[i] = S.sn[i];
-  }
+  if ((tid & 63) == 0) red[tid >> 6] = s;
   __syncthreads();
-  if (tid == 0) {
-    c128 gm_rot = mk(0.0, 0.0);
-    const double h = sqrt(s);
-    S.Hraw[m + 1 + m * LD] = mk(h, 0.0);
-    c2[m + 1] = mk(h, 0.0);
+  if (tid < 64) {
+    const double h = sqrt((red[0] + red[1]) + (red[2] + red[3]));
+    c128 a1 = lane_get(x1, 0), a2 = lane_get(x2, 0);  // the running entry i of each column
+    for (int i = 0; i + 1 < m; ++i) {
+      const double c = lane_get(xc, i);
+      const c128 sn = lane_get(xs, i), b1 = lane_get(x1, i + 1), b2 = lane_get(x2, i + 1);
+      const c128 r1 = c * a1 + sn * b1, r2 = c * a2 + sn * b2;
+      a1 = -1.0 * cmulc(sn, a1) + c * b1;
+      a2 = -1.0 * cmulc(sn, a2) + c * b2;
+      if (tid == i) {
+        x1 = r1;
+        x2 = r2;
+      }
+    }
+    c128 gm = g_m;  // g[m] as it stands after column m-1
     if (m >= 1) {
       // column m-1 was corrected by the reorthogonalisation: redo its rotation
-      for (int i = 0; i < m - 1; ++i) {
-        const c128 a = c1[i], b = c1[i + 1];
-        c1[i] = cs[i] * a + sn[i] * b;
-        c1[i + 1] = -1.0 * cmulc(sn[i], a) + cs[i] * b;
-      }
       double c;
-      c128 snn, r;
-      givens(c1[m - 1], c1[m].re, c, snn, r);
-      cs[m - 1] = c;
-      sn[m - 1] = snn;
-      c1[m - 1] = r;
-      c1[m] = mk(0.0, 0.0);
-      S.g[m - 1] = c * gpre_m1;
-      gm_rot = -1.0 * cmulc(snn, gpre_m1);
-      S.g[m] = gm_rot;
-    }
-    for (int i = 0; i < m; ++i) {
-      const c128 a = c2[i], b = c2[i + 1];
-      c2[i] = cs[i] * a + sn[i] * b;
-      c2[i + 1] = -1.0 * cmulc(sn[i], a) + cs[i] * b;
+      c128 sn, r;
+      givens(a1, lane_get(x1, m).re, c, sn, r);
+      const c128 b2 = lane_get(x2, m);
+      const c128 r2 = c * a2 + sn * b2;
+      a2 = -1.0 * cmulc(sn, a2) + c * b2;
+      gm = -1.0 * cmulc(sn, g_m1);
+      if (tid == m - 1) {
+        x1 = r;
+        x2 = r2;
+        S.cs[m - 1] = c;
+        S.sn[m - 1] = sn;
+        S.g[m - 1] = c * g_m1;
+      }
+      if (tid == m) x1 = mk(0.0, 0.0);
     }
     double c;
-    c128 snn, r;
-    givens(c2[m], h, c, snn, r);
-    cs[m] = c;
-    sn[m] = snn;
-    c2[m] = r;
-    c2[m + 1] = mk(0.0, 0.0);
-    const c128 gm = (m >= 1) ? gm_rot : g_m;  // g[m] as it stands after column m-1
-    const c128 gnext = -1.0 * cmulc(snn, gm);
+    c128 sn, r;
+    givens(a2, h, c, sn, r);
+    const c128 gnext = -1.0 * cmulc(sn, gm);
     const double est = sqrt(abs2(gnext));
-    S.gpre[m] = gm;
-    S.g[m + 1] = gnext;
-    S.g[m] = c * gm;
-    S.sigma[m + 1] = (h > 0.0) ? 1.0 / h : 0.0;
-    S.est = est;
-    S.m = m + 1;
-    S.total = total + 1;
     int flag = 0;
     if (!isfinite(h) || !isfinite(est)) {
       flag = 4;  // a NaN or Inf reached the Krylov space (n^2 or the right-hand side): stop the pole
@@ -953,21 +972,34 @@ __global__ __launch_bounds__(64) void k_arnoldi(PoleState* __restrict__ st, cons
     } else if (m + 1 >= restart) {
       flag = 2;
     }
-    flag_s = flag;
+    if (tid == m) {
+      x2 = r;
+      S.cs[m] = c;
+      S.sn[m] = sn;
+      S.Hraw[m + 1 + m * LD] = mk(h, 0.0);
+      S.H[m + 1 + m * LD] = mk(0.0, 0.0);
+      S.gpre[m] = gm;
+      S.g[m] = c * gm;
+      S.g[m + 1] = gnext;
+      S.sigma[m + 1] = (h > 0.0) ? 1.0 / h : 0.0;
+      S.est = est;
+      S.m = m + 1;
+      S.total = total + 1;
+      rhs[m] = c * gm;
+      flag_s = flag;
+    }
+    if (tid <= m) {
+      S.H[tid + m * LD] = x2;
+      c2[tid] = x2;
+      if (m >= 1) {
+        S.H[tid + (m - 1) * LD] = x1;
+        c1[tid] = x1;
+      }
+    }
+    if (m >= 1 && tid == m - 1) rhs[m - 1] = S.g[m - 1];
+    if (tid + 1 < m) rhs[tid] = S.g[tid];
   }
   __syncthreads();
-  for (int i = tid; i <= m + 1; i += 64) {
-    S.H[i + m * LD] = c2[i];
-    if (m >= 1 && i <= m) S.H[i + (m - 1) * LD] = c1[i];
-  }
-  if (tid == 0 && m >= 1) {
-    S.cs[m - 1] = cs[m - 1];
-    S.sn[m - 1] = sn[m - 1];
-  }
-  if (tid == 0) {
-    S.cs[m] = cs[m];
-    S.sn[m] = sn[m];
-  }
   int flag = flag_s;
   if (flag && flag != 4) {
     // least squares R y = g, then y~ = Rc^{-1} y (the coefficients of the stored Z~);
@@ -981,23 +1013,22 @@ __global__ __launch_bounds__(64) void k_arnoldi(PoleState* __restrict__ st, cons
       if (c * (c + 1) / 2 > e) --c;
       r = e - c * (c + 1) / 2;
     };
-    for (int e = tid; e < npk; e += 64) {
+    for (int e = tid; e < npk; e += ARN_WG) {
       int r, c;
       unpack(e, r, c);
       tri[e] = (c == m) ? c2[r] : (c == m - 1 ? c1[r] : S.H[r + c * LD]);
     }
-    for (int i = tid; i < n; i += 64) rhs[i] = S.g[i];
     __syncthreads();
     upper_solve(tri, rhs, y, n);
-    for (int e = tid; e < npk; e += 64) {
+    for (int e = tid; e < npk; e += ARN_WG) {
       int r, c;
       unpack(e, r, c);
       tri[e] = S.Rc[r + c * LD];
     }
-    for (int i = tid; i < n; i += 64) rhs[i] = y[i];  // the least-squares solution
+    for (int i = tid; i < n; i += ARN_WG) rhs[i] = y[i];  // the least-squares solution
     __syncthreads();
     upper_solve(tri, rhs, y, n);
-    for (int i = tid; i < n; i += 64) S.y[i] = y[i];
+    for (int i = tid; i < n; i += ARN_WG) S.y[i] = y[i];
     // The estimate measures the split operator I + P M~^-1; it differs from
     // A M~^-1 by about eps kappa(M_k) ||y|| (y the least-squares solution, so
     // ||y|| = ||M x||).  When that is not well below tol, the true residual decides.
@@ -1044,12 +1075,15 @@ __global__ __launch_bounds__(64) void k_cycle_init(PoleState* __restrict__ st, c
   S.est = beta;
   S.g[0] = mk(beta, 0.0);
   S.sigma[0] = (beta > 0.0) ? 1.0 / beta : 0.0;
-  S.correct = 0;
   if (set_has_x) S.has_x = 1;
 }
 
 // ------------------------------------------------------------------ residue-weighted sum and output
 
+// One row per workgroup; its RPW thread groups take the terms (pole, basis
+// index) in turn and meet in LDS in a fixed order, then the first group runs the
+// transform.  (With a row per group 256^2 had 32 workgroups and every thread a
+// chain of all terms: 37 us, latency-bound; large fields run at the copy rate.)
 template <typename T, int N>
 __global__ __launch_bounds__(RowCfg<N>::WG) void k_final(const c128* __restrict__ w, c128* __restrict__ out,
                                                          const cx<T>* __restrict__ zbase, size_t zsp, size_t zsi,
@@ -1062,50 +1096,68 @@ __global__ __launch_bounds__(RowCfg<N>::WG) void k_final(const c128* __restrict_
   __shared__ c128 lds[RPW * plen<double>(N)];
   __shared__ c128 scr[RPW * RC::SCR];
   const int g = threadIdx.x / NT, t = threadIdx.x % NT;
-  const int row = blockIdx.x * RPW + g;  // rows 0..ny-1
+  const int row = blockIdx.x;  // rows 0..ny-1
   const int comp = blockIdx.y;
-  const bool valid = row > 0 && row < ny;
-  c128* buf = lds + g * plen<double>(N);
   const size_t roff = comp * fsz + (size_t)row * N;
-  const RowWalk<TW, NT> toff(comp * fsz, valid ? row : 0, t, ny);
+  if (row == 0) {
+    if (g == 0)
+      for (int j = t; j < N; j += NT) out[roff + j] = mk(0.0, 0.0);
+    return;
+  }
+  c128* buf = lds + g * plen<double>(N);
+  const RowWalk<TW, NT> toff(comp * fsz, row, t, ny);
   c128 acc[PT];
 #pragma unroll
   for (int s = 0; s < PT; ++s) acc[s] = mk(0.0, 0.0);
-  if (valid) {
-    for (int k = 0; k < npoles; ++k) {
-      const c128 ak = st[k].ak;
-      if (st[k].has_x) {
+  // terms are numbered through all poles; group g takes every RPW-th
+  int next = g;
+  for (int k = 0; k < npoles; ++k) {
+    const int m = st[k].m, hx = st[k].has_x, nt = m + hx;
+    const c128 ak = st[k].ak;
+    const cx<T>* zk = zbase + k * zsp;
+    if (hx && next < nt) {  // term 0 of a pole with an accumulator
+      if (next == 0) {
         const c128* xk = xacc + k * xsp;
 #pragma unroll
         for (int s = 0; s < PT; ++s) acc[s] = acc[s] + ak * xk[toff.at(s)];
-      }
-      const int mk_ = st[k].m;
-      const cx<T>* zk = zbase + k * zsp;
-      for (int i = 0; i < mk_; ++i) {
-        const c128 cf = ak * st[k].y[i];
-        const cx<T>* zi = zk + i * zsi;
-#pragma unroll
-        for (int s = 0; s < PT; ++s) acc[s] = acc[s] + cf * cvt<double>(zi[toff.at(s)]);
+        next += RPW;
       }
     }
+#pragma unroll 2
+    for (; next < nt; next += RPW) {
+      const int i = next - hx;
+      const c128 cf = ak * st[k].y[i];
+      const cx<T>* zi = zk + i * zsi;
+#pragma unroll
+      for (int s = 0; s < PT; ++s) acc[s] = acc[s] + cf * cvt<double>(zi[toff.at(s)]);
+    }
+    next -= nt;
   }
   const PStep<double, NT> at(t);  // LDS index of element t + s NT
 #pragma unroll
   for (int s = 0; s < PT; ++s) buf[at(s)] = acc[s];
   __syncthreads();
+  if constexpr (RPW > 1) {
+    // element x of the row: the groups' sums, in the order of the groups
+    for (int x = threadIdx.x; x < N; x += RC::WG) {
+      const int e = pidx<double>(x);
+      c128 v = lds[e];
+#pragma unroll
+      for (int q = 1; q < RPW; ++q) v = v + lds[q * plen<double>(N) + e];
+      lds[e] = v;
+    }
+    __syncthreads();
+  }
+  // every group runs the (same) transform's barriers; only the first one's result is stored
   dst1<double, N>(buf, tw, scr + g * RC::SCR, t);
   const double scale = sqrt(2.0 / N);
-  if (row < ny) {
-#pragma unroll
-    for (int s = 0; s < PT; ++s) {
-      const int j = t + s * NT;
-      c128 v = mk(0.0, 0.0);
-      if (valid && j > 0) {
-        const c128 sv = scale * buf[at(s)];
-        v = edge_loss(row, j, nx, ny, W, eta, loss_coef) * (phase * sv + rinf_phase * w[roff + j]);
-      }
-      out[roff + j] = v;
+  for (int j = threadIdx.x; j < N; j += RC::WG) {
+    c128 v = mk(0.0, 0.0);
+    if (j > 0) {
+      const c128 sv = scale * lds[pidx<double>(j)];
+      v = edge_loss(row, j, nx, ny, W, eta, loss_coef) * (phase * sv + rinf_phase * w[roff + j]);
     }
+    out[roff + j] = v;
   }
 }
 
@@ -1408,21 +1460,18 @@ void launch_row_inv(const cx<T>* in, c128* out, const cx<C>* tw, const Geo& g, i
 }
 
 template <typename T, typename C>
-void launch_col(const cx<T>* const* uptr, cx<T>* zbase, size_t zsp, size_t zsi, cx<T>* dzbase, size_t dzsp,
-                const PoleState* st, const int* poles, int nactive, int* active_out, const double* mu_x,
-                const double* mu_y, const cx<C>* tw, const Geo& g, const StencilCoef& sc, hipStream_t s) {
-  PoleList list;
-  list.n = nactive;
-  for (int a = 0; a < HP_MAXPOLES; ++a) list.k[a] = a < nactive ? poles[a] : 0;
+void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi, cx<T>* dzbase, size_t dzsp,
+                const PoleState* st, const RoundList& list, const double* mu_x, const double* mu_y, const cx<C>* tw,
+                const Geo& g, const StencilCoef& sc, hipStream_t s) {
 #define COLV_(NN, LB)                                                                                          \
   {                                                                                                            \
-    dim3 grid(g.nx / ColCfg<T, C, NN, LB>::GC, g.ncomp * nactive);                                             \
+    dim3 grid(g.nx / ColCfg<T, C, NN, LB>::GC, g.ncomp * list.n);                                              \
     if (g.ncomp == 1)                                                                                          \
-      hipLaunchKernelGGL((k_col<T, C, NN, 1, LB>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, uptr, zbase,    \
-                         zsp, zsi, dzbase, dzsp, st, list, active_out, mu_x, mu_y, tw, g.fsz, sc);             \
+      hipLaunchKernelGGL((k_col<T, C, NN, 1, LB>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, basis, zbase,   \
+                         zsp, zsi, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
     else                                                                                                       \
-      hipLaunchKernelGGL((k_col<T, C, NN, 2, LB>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, uptr, zbase,    \
-                         zsp, zsi, dzbase, dzsp, st, list, active_out, mu_x, mu_y, tw, g.fsz, sc);             \
+      hipLaunchKernelGGL((k_col<T, C, NN, 2, LB>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, basis, zbase,   \
+                         zsp, zsi, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
   }
 #define L_(NN)                                                                                                 \
   {                                                                                                            \
@@ -1440,7 +1489,7 @@ void launch_col(const cx<T>* const* uptr, cx<T>* zbase, size_t zsp, size_t zsi, 
 
 static int apply_groups(const Geo& g) {
   const int nt = g.nx / 8;
-  int groups = (256 / nt) / g.ncomp * g.ncomp;
+  int groups = (apply_threads(g.nx) / nt) / g.ncomp * g.ncomp;
   if (groups < g.ncomp) groups = g.ncomp;
   return groups;
 }
@@ -1451,53 +1500,58 @@ int row_apply_blocks(const Geo& g) {
   return (g.ny - 1 + rows - 1) / rows;
 }
 
-template <typename T>
-int row_apply_parts(const Geo& g) {
-  return row_apply_blocks<T>(g) * ((apply_groups(g) * (g.nx / 8) + 63) / 64);
-}
-
 template <typename T, typename C>
 void launch_row_apply(const cx<T>* zbase, size_t zsp, size_t zsi, const cx<T>* dzbase, size_t dzsp, cx<T>* pbase,
-                      size_t psp, const cx<T>* const* uptr, const C* coef, const PoleState* st,
-                      const int* active, int nactive, double2* part, const cx<C>* tw, const Geo& g,
-                      const StencilCoef& sc, hipStream_t s) {
+                      size_t psp, const Basis<cx<T>>& basis, const C* coef, const PoleState* st,
+                      const RoundList& list, double2* part, const cx<C>* tw, const Geo& g, const StencilCoef& sc,
+                      hipStream_t s) {
   const int nblk = row_apply_blocks<T>(g);
-  const int nparts = row_apply_parts<T>(g);
   // one workgroup per (row block, pole), row blocks padded to a multiple of 8
-  dim3 grid((unsigned)((nblk + 7) / 8 * 8) * (unsigned)nactive);
+  dim3 grid((unsigned)((nblk + 7) / 8 * 8) * (unsigned)list.n);
 #define L_(NN)                                                                                                  \
   if (g.ncomp == 1)                                                                                             \
     hipLaunchKernelGGL((k_row_apply<T, C, NN, 1>), grid, dim3(ApplyCfg<NN, 1>::WG), 0, s, zbase, zsp, zsi, dzbase,  \
-                       dzsp, pbase, psp, uptr, coef, st, active, nactive, nblk, part, nparts, tw, g.ny, g.fsz, sc);  \
+                       dzsp, pbase, psp, basis, coef, st, list, nblk, part, tw, g.ny, g.fsz, sc);               \
   else                                                                                                          \
     hipLaunchKernelGGL((k_row_apply<T, C, NN, 2>), grid, dim3(ApplyCfg<NN, 2>::WG), 0, s, zbase, zsp, zsi, dzbase,  \
-                       dzsp, pbase, psp, uptr, coef, st, active, nactive, nblk, part, nparts, tw, g.ny, g.fsz, sc);
+                       dzsp, pbase, psp, basis, coef, st, list, nblk, part, tw, g.ny, g.fsz, sc);
   HP_DISPATCH_N(g.nx, L_)
 #undef L_
 }
 
-void launch_reduce_dots(const double2* part, int nblk, PoleState* st, const int* active, int nactive, int maxm,
-                        int* done, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_pairs, dim3(2 * (maxm + 1), nactive), dim3(256), 0, s, part, nblk, st, active, done);
+void launch_reduce_dots(const double2* part, int nparts, PoleState* st, const RoundList& list, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_dots, dim3(list.n), dim3(RED_WG), 0, s, part, nparts, st, list);
 }
 
+// Elements per thread of the update: one for fields of up to 2^16 elements, whose
+// workgroups of four elements a thread would leave CUs without work (64 of them at
+// 256^2), else four.  The rule looks at the field alone, so a pole's sums are
+// the same whatever the other poles do.
+static int update_elems(size_t total) { return total <= 65536 ? 1 : 4; }
+
 int update_blocks(size_t total) {
-  size_t b = (total + UPD_WG * UPD_E - 1) / (UPD_WG * UPD_E);
+  const size_t chunk = (size_t)UPD_WG * update_elems(total);
+  size_t b = (total + chunk - 1) / chunk;
   if (b > 2048) b = 2048;
   if (b < 1) b = 1;
   return (int)b;
 }
 
 template <typename T>
-void launch_update(const cx<T>* pbase, size_t psp, cx<T>* const* uptr, const PoleState* st, const int* active,
-                   int nactive, double* part, int nblk, const Geo& g, hipStream_t s) {
-  hipLaunchKernelGGL((k_update<T>), dim3(nblk, nactive), dim3(UPD_WG), 0, s, pbase, psp, uptr, st, active, part,
-                     nblk, (size_t)g.ncomp * g.fsz);
+void launch_update(const cx<T>* pbase, size_t psp, const Basis<cx<T>>& basis, const PoleState* st,
+                   const RoundList& list, double* part, int nblk, const Geo& g, hipStream_t s) {
+  const size_t total = (size_t)g.ncomp * g.fsz;
+  if (update_elems(total) == 1)
+    hipLaunchKernelGGL((k_update<T, 1>), dim3(nblk, list.n), dim3(UPD_WG), 0, s, pbase, psp, basis, st, list, part,
+                       nblk, total);
+  else
+    hipLaunchKernelGGL((k_update<T, 4>), dim3(nblk, list.n), dim3(UPD_WG), 0, s, pbase, psp, basis, st, list, part,
+                       nblk, total);
 }
 
-void launch_arnoldi(PoleState* st, const int* active, int nactive, const double* part, int nblk, int restart,
+void launch_arnoldi(PoleState* st, const RoundList& list, const double* part, int nblk, int restart,
                     unsigned long long* ftag, unsigned long long seq, double* est, hipStream_t s) {
-  hipLaunchKernelGGL(k_arnoldi, dim3(nactive), dim3(64), 0, s, st, active, part, nblk, restart, ftag, seq, est);
+  hipLaunchKernelGGL(k_arnoldi, dim3(list.n), dim3(ARN_WG), 0, s, st, list, part, nblk, restart, ftag, seq, est);
 }
 
 void launch_cycle_init(PoleState* st, const int* poles, int npoles_in, const double* part, int nblk, int first,
@@ -1510,8 +1564,7 @@ template <typename T>
 void launch_final(const c128* w, c128* out, const cx<T>* zbase, size_t zsp, size_t zsi, const c128* xacc, size_t xsp,
                   const PoleState* st, int npoles, c128 phase, c128 rinf_phase, double loss_coef, double eta, int W,
                   const c128* tw64, const Geo& g, hipStream_t s) {
-  const int rpw = row_blocks<double>(g.nx);
-  dim3 grid((g.ny + rpw - 1) / rpw, g.ncomp);
+  dim3 grid(g.ny, g.ncomp);
 #define L_(NN)                                                                                                     \
   hipLaunchKernelGGL((k_final<T, NN>), grid, dim3(RowCfg<NN>::WG), 0, s, w, out, zbase, zsp, zsi, xacc, xsp, st, \
                      npoles, phase, rinf_phase, loss_coef, eta, W, tw64, g.nx, g.ny, g.fsz)
@@ -1603,9 +1656,8 @@ void launch_rk4_stage(const c128* L, const c128* acc_in, c128* acc_out, const c1
 #define HP_INST(T)                                                                                                   \
   template int row_blocks<T>(int);                                                                                   \
   template int row_apply_blocks<T>(const Geo&);                                                                      \
-  template int row_apply_parts<T>(const Geo&);                                                                       \
-  template void launch_update<T>(const cx<T>*, size_t, cx<T>* const*, const PoleState*, const int*, int, double*,    \
-                                 int, const Geo&, hipStream_t);                                                      \
+  template void launch_update<T>(const cx<T>*, size_t, const Basis<cx<T>>&, const PoleState*, const RoundList&,      \
+                                 double*, int, const Geo&, hipStream_t);                                             \
   template void launch_final<T>(const c128*, c128*, const cx<T>*, size_t, size_t, const c128*, size_t,               \
                                 const PoleState*, int, c128, c128, double, double, int, const c128*, const Geo&,     \
                                 hipStream_t);                                                                        \
@@ -1621,11 +1673,11 @@ void launch_rk4_stage(const c128* L, const c128* acc_in, c128* acc_out, const c1
                                            double*, size_t, const cx<C>*, const Geo&, hipStream_t, int);             \
   template void launch_row_inv_batch<T, C>(const cx<T>*, size_t, const int*, int, c128*, size_t, const cx<C>*,       \
                                            const Geo&, int, hipStream_t);                                            \
-  template void launch_col<T, C>(const cx<T>* const*, cx<T>*, size_t, size_t, cx<T>*, size_t, const PoleState*,      \
-                                 const int*, int, int*, const double*, const double*, const cx<C>*, const Geo&,      \
+  template void launch_col<T, C>(const Basis<cx<T>>&, cx<T>*, size_t, size_t, cx<T>*, size_t, const PoleState*,      \
+                                 const RoundList&, const double*, const double*, const cx<C>*, const Geo&,           \
                                  const StencilCoef&, hipStream_t);                                                   \
   template void launch_row_apply<T, C>(const cx<T>*, size_t, size_t, const cx<T>*, size_t, cx<T>*, size_t,           \
-                                       const cx<T>* const*, const C*, const PoleState*, const int*, int, double2*,   \
+                                       const Basis<cx<T>>&, const C*, const PoleState*, const RoundList&, double2*,  \
                                        const cx<C>*, const Geo&, const StencilCoef&, hipStream_t);
 
 HP_INST(double)

@@ -45,44 +45,38 @@ void launch_row_inv_batch(const cx<T>* in, size_t in_bs, const int* sel, int n, 
                           const cx<C>* tw, const Geo& g, int tile_w, hipStream_t s);
 
 // Column pass: z = sigma_m * S_y diag(1/(mu_y + mu_x - b_k)) S_y u_m for the
-// poles poles[0..nactive) (a host array, passed by value in the kernel
-// arguments; the kernel also stores it to active_out, when not null, for the
-// kernels after it on the stream).  Vector fields also get dz = D1y z (the y
-// derivative the row pass needs).
+// poles of the list.  Vector fields also get dz = D1y z (the y derivative the row
+// pass needs).
 template <typename T, typename C = T>
-void launch_col(const cx<T>* const* uptr, cx<T>* zbase, size_t zsp, size_t zsi, cx<T>* dzbase, size_t dzsp,
-                const PoleState* st, const int* poles, int nactive, int* active_out, const double* mu_x,
-                const double* mu_y, const cx<C>* tw, const Geo& g, const StencilCoef& sc, hipStream_t s);
+void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi, cx<T>* dzbase, size_t dzsp,
+                const PoleState* st, const RoundList& list, const double* mu_x, const double* mu_y, const cx<C>* tw,
+                const Geo& g, const StencilCoef& sc, hipStream_t s);
 
 // Row pass: p = S_x (P (S_x z_m)) with P the medium part of Zbar, plus the
-// partial inner products <u_i, p>, i = 0..m.  coef: the coefficient planes in
-// the working precision.
+// partial inner products <u_i, p> and <u_i, u_m>, i = 0..m (one per workgroup).
+// coef: the coefficient planes in the working precision.
 template <typename T, typename C = T>
 void launch_row_apply(const cx<T>* zbase, size_t zsp, size_t zsi, const cx<T>* dzbase, size_t dzsp, cx<T>* pbase,
-                      size_t psp, const cx<T>* const* uptr, const C* coef, const PoleState* st,
-                      const int* active, int nactive, double2* part, const cx<C>* tw, const Geo& g,
-                      const StencilCoef& sc, hipStream_t s);
+                      size_t psp, const Basis<cx<T>>& basis, const C* coef, const PoleState* st,
+                      const RoundList& list, double2* part, const cx<C>* tw, const Geo& g, const StencilCoef& sc,
+                      hipStream_t s);
+// workgroups per pole of the row pass: the partial sums of each inner product
 template <typename T>
 int row_apply_blocks(const Geo& g);
-// partial sums per inner product written by the row pass (one per wave)
-template <typename T>
-int row_apply_parts(const Geo& g);
 // elements per 128-byte tile row of a column-tiled R-domain field
 template <typename T>
 constexpr int tile_width() {
   return 128 / (int)sizeof(cx<T>);
 }
 
-// hc_i = sigma_i * sum of the partial inner products, then (in the same
-// launch, by each pole's last workgroup) the correction algebra that gives the
-// update coefficients.  done: HP_MAXPOLES device counters, zero between calls.
-void launch_reduce_dots(const double2* part, int nblk, PoleState* st, const int* active, int nactive, int maxm,
-                        int* done, hipStream_t s);
+// Sums of the partial inner products and the correction algebra that gives the
+// update coefficients, one workgroup per pole.
+void launch_reduce_dots(const double2* part, int nparts, PoleState* st, const RoundList& list, hipStream_t s);
 
-// u_{m+1} = p - sum_i hc_i v_i and partial |u_{m+1}|^2.
+// u_{m+1} = p - sum_i hc_i v_i and partial |u_{m+1}|^2; rewrites u_m (m > 0).
 template <typename T>
-void launch_update(const cx<T>* pbase, size_t psp, cx<T>* const* uptr, const PoleState* st, const int* active,
-                   int nactive, double* part, int nblk, const Geo& g, hipStream_t s);
+void launch_update(const cx<T>* pbase, size_t psp, const Basis<cx<T>>& basis, const PoleState* st,
+                   const RoundList& list, double* part, int nblk, const Geo& g, hipStream_t s);
 int update_blocks(size_t total);
 
 // Hessenberg column, Givens rotation, residual estimate, convergence flag and
@@ -91,7 +85,7 @@ int update_blocks(size_t total);
 // on, 1: converged, 2: restart length reached, 3: the true residual decides,
 // 4: a non-finite value reached the Krylov space), stored with system scope to
 // host-coherent memory.
-void launch_arnoldi(PoleState* st, const int* active, int nactive, const double* part, int nblk, int restart,
+void launch_arnoldi(PoleState* st, const RoundList& list, const double* part, int nblk, int restart,
                     unsigned long long* ftag, unsigned long long seq, double* est, hipStream_t s);
 
 // Start a cycle: beta = sqrt(sum part), g = beta e1, sigma_0 = 1/beta.

@@ -35,8 +35,6 @@ struct PoleState {
   double sigma[HP_MAXM + 1];          // scale of the stored vector: v_i = sigma_i u_i
   c128 cu[HP_MAXM + 2];               // update coefficients: u_i (i < m), ~v_m at m, p at m+1
   c128 cv[HP_MAXM + 1];               // correction of ~v_m: v_m = sum_i cv_i u_i (i <= m)
-  int correct;                        // 1 when the update also rewrites u_m
-  int pad2;
   c128 H[(HP_MAXM + 1) * HP_MAXM];    // rotated Hessenberg (R factor), column-major (i + col * (MAXM+1))
   c128 Hraw[(HP_MAXM + 1) * HP_MAXM]; // unrotated Hessenberg
   c128 Rc[(HP_MAXM + 1) * HP_MAXM];   // ~v_l = Rc[l][l] v_l + sum_{i<l} Rc[i][l] v_i
@@ -54,6 +52,30 @@ struct PoleState {
 struct PoleList {
   int n;
   int k[HP_MAXPOLES];
+};
+
+// The poles of one round, by value in its kernels' arguments: pole, its Arnoldi
+// index m (the host knows it, so no kernel waits for it from the device) and
+// whether its first basis vector is the step's shared S_x w.
+struct RoundList {
+  int n;
+  int e[HP_MAXPOLES];
+};
+__host__ __device__ __forceinline__ int round_entry(int k, int m, bool shared) {
+  return k | (m << 8) | ((shared ? 1 : 0) << 16);
+}
+__host__ __device__ __forceinline__ int round_pole(int e) { return e & 0xff; }
+__host__ __device__ __forceinline__ int round_m(int e) { return (e >> 8) & 0xff; }
+__host__ __device__ __forceinline__ bool round_shared(int e) { return (e >> 16) & 1; }
+
+// Krylov vectors: u_i of pole k at base + k sp + i si, u_0 at sh where it is shared.
+template <typename E>
+struct Basis {
+  E *sh, *base;
+  size_t sp, si;
+  __device__ __forceinline__ E* at(int e, int i) const {
+    return (i == 0 && round_shared(e)) ? sh : base + (size_t)round_pole(e) * sp + (size_t)i * si;
+  }
 };
 
 // Shifts b_k of the fields of one batched launch of the explicit operator.

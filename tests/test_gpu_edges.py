@@ -1,0 +1,84 @@
+"""The solve's kernels at the edges of their tiles, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import operator as op
+from oracle import precond
+from oracle import step as st
+from paper_2410_17446_amd import inputs
+
+from helpers import gpu_plan, oracle_grid, rel_l2, to_gpu, workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _solve_both(N, ncomp, amp, period, steps=None, restart=64, tol=1e-12):
+    """(GPU solution, oracle solution, bound of converged solves) of the pole nearest the real axis;
+    `steps` replays that many Arnoldi steps of one cycle on both sides."""
+    wl = workload(N=N, ncomp=ncomp, W=8, medium=("sine", amp, period), w0=2.0, tol=tol, restart=restart)
+    k = int(np.argmin(np.abs(wl["fit"]["poles"].imag)))
+    b = wl["fit"]["poles"][k]
+    g = oracle_grid(wl)
+    co = op.coefficients(g, wl["n2"], ncomp == 2)
+    ref = st.solve_pole(g, co, wl["w"], b, tol, restart=restart, schedule=None if steps is None else [steps])
+    plan = gpu_plan(wl)
+    if steps is not None:
+        plan.set_fixed_iters([steps] * plan.npoles)
+    plan.set_medium(to_gpu(wl["n2"]))
+    x = plan.solve(k, to_gpu(wl["w"])).cpu().numpy()
+    plan.close()
+    xr = op.unpack(ref.x, ncomp, N)
+    return x, xr, 4 * tol * np.linalg.norm(wl["w"]) / (abs(b.imag) * np.linalg.norm(xr)), ref
+
+
+# Cycles of up to 64 steps: inner products are collected 16 at a time and summed by 16
+# waves, a basis holds up to 65 vectors.  Both sides stop at relative residuals of tol, and
+# the scalar operator is real symmetric, so ||A^-1|| <= 1/|Im b| bounds the difference
+# by 2 tol ||w|| / (|Im b| ||x||); twice that for the estimates the stops are made on.
+# (The vector operator is symmetric up to the small psi terms: the same with 10 more.)
+@pytest.mark.parametrize("N,ncomp,amp,least", [(64, 1, 0.1, 40), (64, 2, 0.1, 50), (128, 1, 0.05, 50),
+                                               (64, 1, 0.2, 64)])
+def test_long_cycles_match_oracle(N, ncomp, amp, least):
+    _cuda()
+    x, xr, bound, ref = _solve_both(N, ncomp, amp, 1.5)
+    assert max(ref.cycle_iters) >= least  # the case reaches the long cycles it is here for
+    assert rel_l2(x, xr) < bound * (10 if ncomp == 2 else 1)
+
+
+# Every transform length's row and column passes: segments of the prefix scan (8, 16, 32
+# and 64 lanes, one to four of them), rows per workgroup and update shapes.  After three
+# steps both sides differ by rounding only: a few eps per vector, amplified into x by at
+# most kappa(M_k), about 2e4, so 16 * 2.2e-16 * 2e4 < 1e-10.
+@pytest.mark.parametrize("N,ncomp", [(128, 1), (128, 2), (192, 1), (192, 2), (256, 1), (256, 2), (384, 1), (384, 2),
+                                     (512, 1), (512, 2), (768, 1)])
+def test_row_and_column_passes_match_oracle(N, ncomp):
+    _cuda()
+    x, xr, _, _ = _solve_both(N, ncomp, 0.02, 1.0, steps=3)
+    assert rel_l2(x, xr) < 1e-10
+
+
+@pytest.mark.parametrize("N", [64, 128, 192, 256, 384, 512, 768, 1024, 1536, 2048])
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_preconditioner_at_every_length(N, precision):
+    """M_k^-1 within 20 kappa + 50 log2 N roundings of the oracle (kappa amplifies the input's)."""
+    torch = _cuda()
+    wl = workload(N=N, W=8, restart=1)
+    g = oracle_grid(wl)
+    x = inputs.random_field(N, 1, seed=4)
+    lam = precond.spectrum(g)
+    eps = 2.2e-16 if precision == 0 else 1.2e-7
+    plan = gpu_plan(wl, precision=precision, restart=1)
+    b = wl["fit"]["poles"][3]
+    kappa = np.abs(lam - b).max() / np.abs(lam - b).min()
+    ref = precond.apply_minv(g, x, b)
+    y = torch.zeros_like(to_gpu(x))
+    plan.apply_preconditioner(3, to_gpu(x), y)
+    plan.close()
+    assert rel_l2(y.cpu().numpy(), ref) < eps * (20 * kappa + 50 * np.log2(N))
