@@ -31,6 +31,9 @@ thread_local std::string g_thread_error;
 
 constexpr double kInnerRtolMixed = 1e-5;  // cycle tolerance of the complex64 inner solves
 
+// pinned host memory of a plan: two slots of round flags and the spectrum check's maxima
+constexpr size_t kPinBytes = 2 * HP_MAXPOLES * sizeof(unsigned long long) + kSpectrumBlocks * sizeof(double);
+
 struct Ws {
   char* base = nullptr;
   size_t off = 0;
@@ -83,9 +86,8 @@ struct hp_plan_s {
   unsigned long long* ftag_h = nullptr;
   unsigned long long* ftag_hd = nullptr;  // its device address
   unsigned long long seq = 0;             // rounds launched (the tags)
-  double* est_h = nullptr;
-  int* active_h = nullptr;
-  double* misc_h = nullptr;
+  double* chk_h = nullptr;     // behind ftag_h: what the spectrum check reads back
+  bool own_pin = false;        // ftag_h is the plan's (a batch worker lends its own)
   std::vector<void*> uptr_h;
   std::vector<int> fixed;
   std::vector<double> relres;
@@ -269,7 +271,7 @@ void layout(hp_plan p, Ws& w) {
   p->st_scratch = w.take<PoleState>(1);
   p->uptr = w.take<void*>((size_t)K * (HP_MAXM + 1));
   p->uptr_scratch = w.take<void*>(HP_MAXM + 1);
-  p->active_d = w.take<int>(3 * HP_MAXPOLES);
+  p->active_d = w.take<int>(2 * HP_MAXPOLES);
   p->est_d = w.take<double>(HP_MAXPOLES);
   p->part_dots = w.take<double2>((size_t)K * (HP_MAXM + 1) * 2 * p->napplyblk);
   p->part_norm = w.take<double>((size_t)K * p->nupdblk);
@@ -324,40 +326,63 @@ std::vector<cx<T>> twiddles(int n) {
   return t;
 }
 
-std::complex<double> rat(hp_plan p, double z) {
-  std::complex<double> r(p->d.r_inf.re, p->d.r_inf.im);
-  for (int k = 0; k < p->d.npoles; ++k) {
-    std::complex<double> a(p->residues[k].re, p->residues[k].im), b(p->poles[k].re, p->poles[k].im);
-    r += a / (z - b);
-  }
-  return r;
-}
-
+// The tables at the head of the workspace (mu_x .. tw64_x) in one copy.
 template <typename C>
-int upload_tables(hp_plan p) {
+int upload_tables(hp_plan p, const std::vector<double>& mx, const std::vector<double>& my) {
   const hp_plan_desc& d = p->d;
-  const double s = 1.0 / ((d.k0 * d.n0) * (d.k0 * d.n0));
-  auto mx = mu_table(d.nx, d.dx, p->c2, s), my = mu_table(d.ny, d.dy, p->c2, s);
-  HPCHK(hipMemcpy(p->mu_x, mx.data(), mx.size() * sizeof(double), hipMemcpyHostToDevice));
-  HPCHK(hipMemcpy(p->mu_y, my.data(), my.size() * sizeof(double), hipMemcpyHostToDevice));
-  auto tx = twiddles<C>(d.nx), ty = twiddles<C>(d.ny);
-  auto t64 = twiddles<double>(d.nx);
-  HPCHK(hipMemcpy(p->tw_x, tx.data(), tx.size() * sizeof(cx<C>), hipMemcpyHostToDevice));
-  HPCHK(hipMemcpy(p->tw_y, ty.data(), ty.size() * sizeof(cx<C>), hipMemcpyHostToDevice));
-  HPCHK(hipMemcpy(p->tw64_x, t64.data(), t64.size() * sizeof(c128), hipMemcpyHostToDevice));
+  std::vector<char> h((char*)p->coef - (char*)p->mu_x, 0);
+  auto put = [&](const void* dev, const void* src, size_t bytes) {
+    memcpy(h.data() + ((const char*)dev - (const char*)p->mu_x), src, bytes);
+  };
+  const auto t64 = twiddles<double>(d.nx);
+  put(p->mu_x, mx.data(), mx.size() * sizeof(double));
+  put(p->mu_y, my.data(), my.size() * sizeof(double));
+  put(p->tw64_x, t64.data(), t64.size() * sizeof(c128));
+  auto put_tw = [&](void* dev, int n) {
+    if (sizeof(C) == sizeof(double) && n == d.nx) return put(dev, t64.data(), t64.size() * sizeof(c128));
+    const auto t = twiddles<C>(n);
+    put(dev, t.data(), t.size() * sizeof(cx<C>));
+  };
+  put_tw(p->tw_x, d.nx);
+  put_tw(p->tw_y, d.ny);
+  HPCHK(hipMemcpyAsync(p->mu_x, h.data(), h.size(), hipMemcpyHostToDevice, p->stream));
+  HPCHK(hipStreamSynchronize(p->stream));
   return HP_OK;
 }
 
+// Every pole's state cleared and its table entries set.
 int upload_state(hp_plan p) {
-  std::vector<PoleState> h(p->d.npoles);
+  StateInit h{};
   for (int k = 0; k < p->d.npoles; ++k) {
-    memset(&h[k], 0, sizeof(PoleState));
-    h[k].bk = mk(p->poles[k].re, p->poles[k].im);
-    h[k].ak = mk(p->residues[k].re, p->residues[k].im);
-    h[k].fixed = p->fixed.empty() ? 0 : p->fixed[k];
-    h[k].incons = p->incons[k];
+    h.bk[k] = mk(p->poles[k].re, p->poles[k].im);
+    h.ak[k] = mk(p->residues[k].re, p->residues[k].im);
+    h.fixed[k] = p->fixed.empty() ? 0 : p->fixed[k];
+    h.incons[k] = p->incons[k];
   }
-  HPCHK(hipMemcpyAsync(p->st, h.data(), h.size() * sizeof(PoleState), hipMemcpyHostToDevice, p->stream));
+  launch_state_init(p->st, h, p->d.npoles, p->stream);
+  HPCHK(hipGetLastError());
+  return HP_OK;
+}
+
+// max |f(r(z))| over 100001 samples z of [lo, hi], r the plan's partial fractions: f = r, or with
+// hk != 0 the RK4 polynomial of hk (r - 1).  One launch and one synchronisation (the same sums took
+// 25-30 ms of a host core at 16 poles, on every plan of a batch).
+int spectrum_max(hp_plan p, double lo, double hi, double hk, double* out) {
+  SpectrumCheck c{};
+  c.npoles = p->d.npoles;
+  c.r_inf = mk(p->d.r_inf.re, p->d.r_inf.im);
+  c.lo = lo;
+  c.hi = hi;
+  c.hk = hk;
+  for (int k = 0; k < p->d.npoles; ++k) {
+    c.b[k] = mk(p->poles[k].re, p->poles[k].im);
+    c.a[k] = mk(p->residues[k].re, p->residues[k].im);
+  }
+  launch_spectrum_max(c, p->part_misc, p->stream);
+  HPCHK(hipGetLastError());
+  HPCHK(hipMemcpyAsync(p->chk_h, p->part_misc, kSpectrumBlocks * sizeof(double), hipMemcpyDeviceToHost, p->stream));
+  HPCHK(hipStreamSynchronize(p->stream));
+  *out = *std::max_element(p->chk_h, p->chk_h + kSpectrumBlocks);
   return HP_OK;
 }
 
@@ -478,13 +503,7 @@ int restart_from_residuals(hp_plan p, const std::vector<int>& rs, const std::vec
     int rc = upload_uptr(p);
     if (rc) return rc;
   }
-  // the list goes through pinned slot 2; the host wrote it only after the
-  // caller's last synchronisation, and no copy from it is pending
-  int* list_h = p->active_h + 2 * HP_MAXPOLES;
-  int* list_d = p->active_d + 2 * HP_MAXPOLES;
-  for (int a = 0; a < nr; ++a) list_h[a] = rs[a];
-  HPCHK(hipMemcpyAsync(list_d, list_h, nr * sizeof(int), hipMemcpyHostToDevice, p->stream));
-  launch_cycle_init(p->st, list_d, nr, p->guess_rpart, (int)rblk, 0, p->d.tol, inner_rtol(p), p->stream, rblk, 1);
+  launch_cycle_init(p->st, rs.data(), nr, p->guess_rpart, (int)rblk, 0, p->d.tol, inner_rtol(p), p->stream, rblk, 1);
   return HP_OK;
 }
 
@@ -643,12 +662,8 @@ int run_poles(hp_plan p, const c128* w, const std::vector<int>& subset, bool* no
     int rc = upload_uptr(p);
     if (rc) return rc;
   }
-  int* act0 = p->active_h + 2 * HP_MAXPOLES;  // pinned slot for the initial list
-  const int ns = (int)subset.size();
-  for (int a = 0; a < ns; ++a) act0[a] = subset[a];
-  HPCHK(hipMemcpyAsync(p->active_d, act0, ns * sizeof(int), hipMemcpyHostToDevice, p->stream));
-  launch_cycle_init(p->st, p->active_d, ns, p->part_misc, p->nrowblk * d.ncomp, first, d.tol, inner_rtol(p),
-                    p->stream);
+  launch_cycle_init(p->st, subset.data(), (int)subset.size(), p->part_misc, p->nrowblk * d.ncomp, first, d.tol,
+                    inner_rtol(p), p->stream);
   std::vector<char> live(K, 0);
   for (int k : subset) live[k] = 1;
   std::vector<long> since(K, 0);  // iteration at which the pole's current cycle started
@@ -1164,7 +1179,8 @@ size_t hp_workspace_bytes(const hp_plan_desc* desc) {
   return w.off + 256;
 }
 
-int hp_plan_create(const hp_plan_desc* desc, void* stream, void* workspace, hp_plan* out) {
+// hp_plan_create; pin: kPinBytes of coherent pinned host memory to use, or NULL.
+static int plan_create(const hp_plan_desc* desc, void* stream, void* workspace, void* pin, hp_plan* out) {
   if (!out) return fail(nullptr, HP_EINVAL, "out is NULL");
   *out = nullptr;
   std::string v = validate(desc);
@@ -1213,11 +1229,6 @@ int hp_plan_create(const hp_plan_desc* desc, void* stream, void* workspace, hp_p
     const double far = std::max(std::abs(lo - b), std::abs(hi - b));
     p->incons[k] = dist > 0 ? eps * far / dist : 1.0;
   }
-  double rmax = 0.0;
-  for (int i = 0; i <= 100000; ++i) {
-    const double z = lo + (hi - lo) * i / 100000.0;
-    rmax = std::max(rmax, std::abs(rat(p, z)));
-  }
   // workspace
   Ws w;
   layout(p, w);
@@ -1240,29 +1251,40 @@ int hp_plan_create(const hp_plan_desc* desc, void* stream, void* workspace, hp_p
   w.base = p->ws;
   w.dry = false;
   layout(p, w);
-  if (hipHostMalloc(&p->ftag_h, 2 * HP_MAXPOLES * sizeof(unsigned long long),
-                    hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess ||
-      hipHostMalloc(&p->est_h, HP_MAXPOLES * sizeof(double)) != hipSuccess ||
-      hipHostMalloc(&p->active_h, 3 * HP_MAXPOLES * sizeof(int)) != hipSuccess ||
-      hipHostMalloc(&p->misc_h, (std::max(p->nopblk, p->nrowblk * 2) + 64) * sizeof(double)) != hipSuccess) {
-    hp_plan_destroy(p);
-    return fail(nullptr, HP_ENOMEM, "pinned host allocation failed");
+  if (pin) {
+    p->ftag_h = reinterpret_cast<unsigned long long*>(pin);
+  } else {
+    if (hipHostMalloc(&p->ftag_h, kPinBytes, hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess) {
+      p->ftag_h = nullptr;
+      hp_plan_destroy(p);
+      return fail(nullptr, HP_ENOMEM, "pinned host allocation failed");
+    }
+    p->own_pin = true;
   }
+  p->chk_h = reinterpret_cast<double*>(p->ftag_h + 2 * HP_MAXPOLES);
   if (hipHostGetDevicePointer(reinterpret_cast<void**>(&p->ftag_hd), p->ftag_h, 0) != hipSuccess) {
     hp_plan_destroy(p);
     return fail(nullptr, HP_EHIP, "no device address for the pinned flag buffer");
   }
   memset(p->ftag_h, 0, 2 * HP_MAXPOLES * sizeof(unsigned long long));
-  int rc = (p->mixed && !p->mixed64) ? upload_tables<float>(p) : upload_tables<double>(p);
+  int rc = (p->mixed && !p->mixed64) ? upload_tables<float>(p, mx, my) : upload_tables<double>(p, mx, my);
   if (rc) {
     g_thread_error = p->err;
     hp_plan_destroy(p);
     return rc;
   }
-  // zero every buffer once: row 0 and column 0 of all fields stay zero
-  if (hipMemsetAsync(p->coef, 0, (char*)(p->st) - (char*)(p->coef), p->stream) != hipSuccess) {
-    hp_plan_destroy(p);
-    return fail(nullptr, HP_EHIP, "workspace clear failed");
+  // Row 0 of every R-domain field (the first row of each tile) is never written by the
+  // transforms, so the updates carry it along: zero from the start.  Everything else in the
+  // workspace is written before it is read (clearing all of it took 3 ms of a 1024^2 plan's
+  // creation and 33 ms of a 2048^2 vector plan's).
+  {
+    const size_t es = p->mixed ? sizeof(c64) : sizeof(c128);
+    const size_t plane = p->geo.fsz * es;
+    const size_t planes = ((char*)p->X - (char*)p->U) / plane;  // U, Z, P, DZ, bR, tmpR, all of them
+    launch_clear_rows(p->U, planes, plane, desc->ny, 128, p->stream);
+    const int tw = 128 / (int)es;  // X: complex128 in the tiles of the working precision
+    launch_clear_rows(p->X, (size_t)desc->npoles * desc->ncomp, p->geo.fsz * sizeof(c128), desc->ny,
+                      tw * (int)sizeof(c128), p->stream);
   }
   // Krylov vector pointer table: u_i of pole k at U[k][i]
   const size_t es = p->mixed ? sizeof(c64) : sizeof(c128);
@@ -1276,13 +1298,18 @@ int hp_plan_create(const hp_plan_desc* desc, void* stream, void* workspace, hp_p
     hp_plan_destroy(p);
     return rc;
   }
-  if (hipStreamSynchronize(p->stream) != hipSuccess) {
+  double rmax = 0.0;
+  if (spectrum_max(p, lo, hi, 0.0, &rmax) != HP_OK) {  // synchronises
     hp_plan_destroy(p);
     return fail(nullptr, HP_EHIP, "plan upload failed");
   }
   scratch_setup(p);  // this device's static scratch (hp_apply_preconditioner_noalloc)
   *out = p;
   return (rmax > 1.0 + 1e-6) ? HP_WARN_UNSTABLE : HP_OK;
+}
+
+int hp_plan_create(const hp_plan_desc* desc, void* stream, void* workspace, hp_plan* out) {
+  return plan_create(desc, stream, workspace, nullptr, out);
 }
 
 int hp_set_medium(hp_plan p, const double* n2) {
@@ -1472,12 +1499,8 @@ int hp_set_form(hp_plan p, int form, int substeps) {
   auto mx = mu_table(d.nx, d.dx, p->c2, s), my = mu_table(d.ny, d.dy, p->c2, s);
   const double lo = *std::min_element(mx.begin() + 1, mx.end()) + *std::min_element(my.begin() + 1, my.end());
   const double hi = *std::max_element(mx.begin() + 1, mx.end()) + *std::max_element(my.begin() + 1, my.end());
-  const std::complex<double> hk(0.0, d.dz / substeps * d.k0 * d.n0);
   double gmax = 0.0;
-  for (int i = 0; i <= 100000; ++i) {
-    const std::complex<double> z = hk * (rat(p, lo + (hi - lo) * i / 100000.0) - 1.0);
-    gmax = std::max(gmax, std::abs(1.0 + z * (1.0 + z * (0.5 + z * (1.0 / 6.0 + z / 24.0)))));
-  }
+  if (int rc = spectrum_max(p, lo, hi, d.dz / substeps * d.k0 * d.n0, &gmax)) return rc;
   return gmax > 1.0 + 1e-6 ? HP_WARN_UNSTABLE : HP_OK;
 }
 
@@ -1710,9 +1733,11 @@ int hp_propagate(hp_plan p, const void* E_in, const double* n2, long n2_step_str
 
 int hp_get_stats(hp_plan p, int* iters_per_pole, double* final_relres) {
   if (!p) return fail(nullptr, HP_EINVAL, "plan is NULL");
-  std::vector<PoleState> h(p->d.npoles);
+  // the heads of the states (counts and estimates), not their 200 KB of matrices
+  std::vector<PoleHead> h(p->d.npoles);
+  HPCHK(hipMemcpy2DAsync(h.data(), sizeof(PoleHead), p->st, sizeof(PoleState), sizeof(PoleHead), p->d.npoles,
+                         hipMemcpyDeviceToHost, p->stream));
   HPCHK(hipStreamSynchronize(p->stream));
-  HPCHK(hipMemcpy(h.data(), p->st, h.size() * sizeof(PoleState), hipMemcpyDeviceToHost));
   for (int k = 0; k < p->d.npoles; ++k) {
     if (iters_per_pole) iters_per_pole[k] = h[k].total;
     if (final_relres) {
@@ -1826,10 +1851,7 @@ void hp_plan_destroy(hp_plan p) {
   if (p->stream) (void)hipStreamSynchronize(p->stream);
   else (void)hipDeviceSynchronize();
   if (p->own_ws && p->ws) (void)hipFree(p->ws);
-  if (p->ftag_h) (void)hipHostFree(p->ftag_h);
-  if (p->est_h) (void)hipHostFree(p->est_h);
-  if (p->active_h) (void)hipHostFree(p->active_h);
-  if (p->misc_h) (void)hipHostFree(p->misc_h);
+  if (p->ftag_h && p->own_pin) (void)hipHostFree(p->ftag_h);
   if (p->guess_r) (void)hipFree(p->guess_r);
   if (p->guess_part) (void)hipFree(p->guess_part);
   if (p->guess_x) (void)hipFree(p->guess_x);
@@ -1853,6 +1875,7 @@ struct hp_batch_s {
   int nworkers = 1;
   size_t ws_bytes = 0;                 // largest problem's workspace
   std::vector<void*> worker_ws;        // one workspace per worker, kept across calls
+  std::vector<void*> worker_pin;       // and the pinned block its plans use (freeing one drains the device)
   std::vector<long> iters;
   std::vector<double> seconds;
   std::vector<int> variant;            // column-pass launch variant per problem
@@ -1903,6 +1926,7 @@ int hp_batch_create(const hp_plan_desc* descs, int nprob, int nworkers, hp_batch
   b->variant.assign(nprob, 1);
   for (int i = 0; i < nprob; ++i) b->ws_bytes = std::max(b->ws_bytes, hp_workspace_bytes(&b->descs[i]));
   b->worker_ws.assign(nworkers, nullptr);
+  b->worker_pin.assign(nworkers, nullptr);
   *out = b;
   return HP_OK;
 }
@@ -1938,6 +1962,13 @@ int hp_batch_propagate(hp_batch b, const void* const* E_in, const double* const*
       if (worst >= 0) worst = HP_ENOMEM, first_err = "worker workspace allocation failed";
       return;
     }
+    if (!b->worker_pin[me] &&
+        hipHostMalloc(&b->worker_pin[me], kPinBytes, hipHostMallocCoherent | hipHostMallocMapped) != hipSuccess) {
+      b->worker_pin[me] = nullptr;
+      std::lock_guard<std::mutex> g(mu);
+      if (worst >= 0) worst = HP_ENOMEM, first_err = "worker pinned allocation failed";
+      return;
+    }
     hipStream_t s = nullptr;
     if (hipStreamCreate(&s) != hipSuccess) {
       std::lock_guard<std::mutex> g(mu);
@@ -1950,7 +1981,7 @@ int hp_batch_propagate(hp_batch b, const void* const* E_in, const double* const*
       const int i = order[slot];
       const auto t0 = std::chrono::steady_clock::now();
       hp_plan p = nullptr;
-      int rc = hp_plan_create(&b->descs[i], s, b->worker_ws[me], &p);
+      int rc = plan_create(&b->descs[i], s, b->worker_ws[me], b->worker_pin[me], &p);
       if (rc >= 0) {
         p->geo.col_variant = b->variant[i];
         const int mrc = hp_set_medium(p, n2[i]);
@@ -2015,6 +2046,8 @@ void hp_batch_destroy(hp_batch b) {
   (void)hipDeviceSynchronize();
   for (void* w : b->worker_ws)
     if (w) (void)hipFree(w);
+  for (void* w : b->worker_pin)
+    if (w) (void)hipHostFree(w);
   delete b;
 }
 

@@ -1049,10 +1049,10 @@ __global__ __launch_bounds__(ARN_WG) void k_arnoldi(PoleState* __restrict__ st, 
   }
 }
 
-__global__ __launch_bounds__(64) void k_cycle_init(PoleState* __restrict__ st, const int* __restrict__ poles,
+__global__ __launch_bounds__(64) void k_cycle_init(PoleState* __restrict__ st, const PoleList poles,
                                                    const double* __restrict__ part, int nblk, int first, double tol,
                                                    double rtol_cycle, size_t part_bs, int set_has_x) {
-  const int k = poles[blockIdx.x];
+  const int k = poles.k[blockIdx.x];
   part += (size_t)blockIdx.x * part_bs;
   double s = 0.0;
   for (int b = threadIdx.x; b < nblk; b += 64) s += part[b];
@@ -1350,6 +1350,54 @@ __global__ void k_mark_list(PoleState* __restrict__ st, const PoleList sel) {
 }
 
 
+// ------------------------------------------------------------------ plan set-up
+
+// One workgroup per pole: its state cleared, then the table's entries.
+__global__ __launch_bounds__(256) void k_state_init(PoleState* __restrict__ st, const StateInit h) {
+  static_assert(sizeof(PoleState) % 16 == 0, "cleared in 16-byte words");
+  const int k = blockIdx.x;
+  double2* w = reinterpret_cast<double2*>(st + k);
+  for (int i = threadIdx.x; i < (int)(sizeof(PoleState) / 16); i += 256) w[i] = make_double2(0.0, 0.0);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    st[k].bk = h.bk[k];
+    st[k].ak = h.ak[k];
+    st[k].fixed = h.fixed[k];
+    st[k].incons = h.incons[k];
+  }
+}
+
+__global__ __launch_bounds__(256) void k_clear_rows(char* __restrict__ base, size_t tiles, size_t tile_bytes,
+                                                    int words) {
+  const size_t n = tiles * words;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
+    reinterpret_cast<double2*>(base + i / words * tile_bytes)[i % words] = make_double2(0.0, 0.0);
+}
+
+__global__ __launch_bounds__(256) void k_spectrum_max(const SpectrumCheck c, double* __restrict__ out) {
+  __shared__ double red[4];
+  double best = 0.0;
+  for (int i = blockIdx.x * 256 + threadIdx.x; i <= 100000; i += kSpectrumBlocks * 256) {
+    const double z = c.lo + (c.hi - c.lo) * i / 100000.0;
+    c128 r = c.r_inf;
+    for (int k = 0; k < c.npoles; ++k) r = r + cdiv(c.a[k], mk(z - c.b[k].re, -c.b[k].im));
+    if (c.hk != 0.0) {
+      const c128 x = mk(-c.hk * r.im, c.hk * (r.re - 1.0));  // i hk (r - 1)
+      const c128 one = mk(1.0, 0.0);
+      c128 q = mk(1.0 / 6.0, 0.0) + (1.0 / 24.0) * x;
+      q = mk(0.5, 0.0) + x * q;
+      q = one + x * q;
+      r = one + x * q;
+    }
+    const double v = sqrt(abs2(r));
+    if (v > best) best = v;  // a NaN counts for nothing
+  }
+  for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_down(best, off, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;
+  __syncthreads();
+  if (threadIdx.x == 0) out[blockIdx.x] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+}
+
 // One stage of the classical fourth-order Runge-Kutta combination, over the
 // fields in physical layout [ncomp][ny][nx]: acc_out = acc_in + ca L and, when
 // v_out is given, v_out = u + cv L.  With loss_coef > 0, acc_out is multiplied
@@ -1556,7 +1604,10 @@ void launch_arnoldi(PoleState* st, const RoundList& list, const double* part, in
 
 void launch_cycle_init(PoleState* st, const int* poles, int npoles_in, const double* part, int nblk, int first,
                        double tol, double rtol_cycle, hipStream_t s, size_t part_bs, int set_has_x) {
-  hipLaunchKernelGGL(k_cycle_init, dim3(npoles_in), dim3(64), 0, s, st, poles, part, nblk, first, tol, rtol_cycle,
+  PoleList sel;
+  sel.n = npoles_in;
+  for (int a = 0; a < HP_MAXPOLES; ++a) sel.k[a] = a < npoles_in ? poles[a] : 0;
+  hipLaunchKernelGGL(k_cycle_init, dim3(npoles_in), dim3(64), 0, s, st, sel, part, nblk, first, tol, rtol_cycle,
                      part_bs, set_has_x);
 }
 
@@ -1643,6 +1694,22 @@ void launch_to_float(const double* a, float* b, size_t n, hipStream_t s) {
   hipLaunchKernelGGL(k_to_float, dim3(2048), dim3(256), 0, s, a, b, n);
 }
 
+
+void launch_state_init(PoleState* st, const StateInit& h, int npoles, hipStream_t s) {
+  hipLaunchKernelGGL(k_state_init, dim3(npoles), dim3(256), 0, s, st, h);
+}
+
+void launch_clear_rows(void* base, size_t planes, size_t plane_bytes, int ny, int row_bytes, hipStream_t s) {
+  const size_t tile = (size_t)ny * row_bytes, tiles = planes * (plane_bytes / tile);
+  const int words = row_bytes / 16;
+  const size_t nb = std::min<size_t>(4096, (tiles * words + 255) / 256);
+  hipLaunchKernelGGL(k_clear_rows, dim3((unsigned)nb), dim3(256), 0, s, reinterpret_cast<char*>(base), tiles, tile,
+                     words);
+}
+
+void launch_spectrum_max(const SpectrumCheck& c, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_spectrum_max, dim3(kSpectrumBlocks), dim3(256), 0, s, c, out);
+}
 
 void launch_rk4_stage(const c128* L, const c128* acc_in, c128* acc_out, const c128* u, c128* v_out, double ca,
                       double cv, double loss_coef, double eta, int W, const Geo& g, hipStream_t s) {

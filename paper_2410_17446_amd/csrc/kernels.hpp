@@ -95,6 +95,7 @@ void launch_arnoldi(PoleState* st, const RoundList& list, const double* part, in
 // Cycle tolerance on the estimate: max(tol * beta0, rtol_cycle * beta).
 // part_bs: stride between the poles' partial sums (0: all read the same);
 // set_has_x: the poles' X accumulators hold a solution so far.
+// poles: host array.
 void launch_cycle_init(PoleState* st, const int* poles, int npoles_in, const double* part, int nblk, int first,
                        double tol, double rtol_cycle, hipStream_t s, size_t part_bs = 0, int set_has_x = 0);
 
@@ -142,4 +143,10 @@ void launch_mark_list(PoleState* st, const int* poles, int n, hipStream_t s);
 // loss_coef > 0 acc_out is multiplied by the edge layer's loss factor.
 void launch_rk4_stage(const c128* L, const c128* acc_in, c128* acc_out, const c128* u, c128* v_out, double ca,
                       double cv, double loss_coef, double eta, int W, const Geo& g, hipStream_t s);
+// Plan set-up: every pole's state; zero the first row (row_bytes) of each tile of `planes`
+// column-tiled planes of plane_bytes with ny rows; per-block maxima of the spectrum check
+// (kSpectrumBlocks doubles).
+void launch_state_init(PoleState* st, const StateInit& h, int npoles, hipStream_t s);
+void launch_clear_rows(void* base, size_t planes, size_t plane_bytes, int ny, int row_bytes, hipStream_t s);
+void launch_spectrum_max(const SpectrumCheck& c, double* out, hipStream_t s);
 void launch_to_float(const double* a, float* b, size_t n, hipStream_t s);

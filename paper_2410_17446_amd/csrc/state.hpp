@@ -14,7 +14,7 @@
 // direction; the Hessenberg column m-1 and the solution coefficients are
 // corrected to match (Hraw holds the unrotated Hessenberg, Rc the triangular
 // map ~v = V Rc, so Z~ = Z Rc and x = Z~ Rc^{-1} y).
-struct PoleState {
+struct PoleHead {
   int m;          // Arnoldi columns completed in the current cycle
   int flag;       // 0 running, 1 converged / fixed count reached, 2 cycle ended unconverged,
                   // 3 converged on the estimate but the true residual must decide,
@@ -32,6 +32,8 @@ struct PoleState {
   double pad3;
   c128 bk;        // pole
   c128 ak;        // residue
+};
+struct PoleState : PoleHead {
   double sigma[HP_MAXM + 1];          // scale of the stored vector: v_i = sigma_i u_i
   c128 cu[HP_MAXM + 2];               // update coefficients: u_i (i < m), ~v_m at m, p at m+1
   c128 cv[HP_MAXM + 1];               // correction of ~v_m: v_m = sum_i cv_i u_i (i <= m)
@@ -46,6 +48,22 @@ struct PoleState {
   c128 Pd[HP_MAXM + 1];               // reduced <u_i, p> of the current step
   c128 Qd[HP_MAXM + 1];               // reduced <u_i, u_m> of the current step
 };
+
+// What sets every pole's state at a plan's creation (by value).
+struct StateInit {
+  c128 bk[HP_MAXPOLES], ak[HP_MAXPOLES];
+  double incons[HP_MAXPOLES];
+  int fixed[HP_MAXPOLES];
+};
+
+// Partial fractions and sample interval of the free-space spectrum check.
+struct SpectrumCheck {
+  int npoles;
+  c128 r_inf;
+  double lo, hi, hk;
+  c128 b[HP_MAXPOLES], a[HP_MAXPOLES];
+};
+constexpr int kSpectrumBlocks = 64;
 
 // The poles of one launch, passed by value in the kernel arguments (no copy to
 // the device before the launch).
