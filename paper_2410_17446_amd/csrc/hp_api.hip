@@ -364,6 +364,21 @@ int upload_state(hp_plan p) {
   return HP_OK;
 }
 
+// Row 0 of every R-domain field (the first row of each tile) is never written by the
+// transforms, so the updates carry it along: zero from the start (and again when the
+// absorbing layers, whose fields are physical, give the fields back).  Everything else in
+// the workspace is written before it is read (clearing all of it took 3 ms of a 1024^2 plan's
+// creation and 33 ms of a 2048^2 vector plan's).
+void clear_tile_rows(hp_plan p) {
+  const size_t es = p->mixed ? sizeof(c64) : sizeof(c128);
+  const size_t plane = p->geo.fsz * es;
+  const size_t planes = ((char*)p->X - (char*)p->U) / plane;  // U, Z, P, DZ, bR, tmpR, all of them
+  launch_clear_rows(p->U, planes, plane, p->d.ny, 128, p->stream);
+  const int tw = 128 / (int)es;  // X: complex128 in the tiles of the working precision
+  launch_clear_rows(p->X, (size_t)p->d.npoles * p->d.ncomp, p->geo.fsz * sizeof(c128), p->d.ny,
+                    tw * (int)sizeof(c128), p->stream);
+}
+
 // max |f(r(z))| over 100001 samples z of [lo, hi], r the plan's partial fractions: f = r, or with
 // hk != 0 the RK4 polynomial of hk (r - 1).  One launch and one synchronisation (the same sums took
 // 25-30 ms of a host core at 16 poles, on every plan of a batch).
@@ -1273,19 +1288,7 @@ static int plan_create(const hp_plan_desc* desc, void* stream, void* workspace, 
     hp_plan_destroy(p);
     return rc;
   }
-  // Row 0 of every R-domain field (the first row of each tile) is never written by the
-  // transforms, so the updates carry it along: zero from the start.  Everything else in the
-  // workspace is written before it is read (clearing all of it took 3 ms of a 1024^2 plan's
-  // creation and 33 ms of a 2048^2 vector plan's).
-  {
-    const size_t es = p->mixed ? sizeof(c64) : sizeof(c128);
-    const size_t plane = p->geo.fsz * es;
-    const size_t planes = ((char*)p->X - (char*)p->U) / plane;  // U, Z, P, DZ, bR, tmpR, all of them
-    launch_clear_rows(p->U, planes, plane, desc->ny, 128, p->stream);
-    const int tw = 128 / (int)es;  // X: complex128 in the tiles of the working precision
-    launch_clear_rows(p->X, (size_t)desc->npoles * desc->ncomp, p->geo.fsz * sizeof(c128), desc->ny,
-                      tw * (int)sizeof(c128), p->stream);
-  }
+  clear_tile_rows(p);
   // Krylov vector pointer table: u_i of pole k at U[k][i]
   const size_t es = p->mixed ? sizeof(c64) : sizeof(c128);
   p->uptr_h.assign((size_t)desc->npoles * (HP_MAXM + 1), nullptr);
@@ -1518,6 +1521,7 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
   if (!p) return fail(nullptr, HP_EINVAL, "plan is NULL");
   HPCHK(hipStreamSynchronize(p->stream));
   if (sigma_max == 0.0 && !Q && !Qinv && !lam) {
+    if (p->pml) clear_tile_rows(p);
     free_pml(p);
     return HP_OK;
   }

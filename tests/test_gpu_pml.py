@@ -205,6 +205,21 @@ def test_pml_mode_switches():
     assert np.isfinite(out.cpu().numpy()).all()
 
 
+def test_removed_layers_leave_no_trace():
+    """A step after the layers are removed equals a fresh plan's bit for bit (the layers' fields are
+    physical, the plain path's transformed, in the same memory)."""
+    torch = _cuda()
+    wl, g = _setup()
+    w, n2 = to_gpu(wl["w"]), to_gpu(wl["n2"])
+    plan, _ = _plan(wl, g)
+    plan.step(w, n2)
+    plan.set_pml(0.0)
+    got = plan.step(w, n2).cpu().numpy()
+    fresh, _ = _plan(wl, g)
+    fresh.set_pml(0.0)
+    assert np.array_equal(got, fresh.step(w, n2).cpu().numpy())
+
+
 def test_pml_failure_modes():
     """A NaN in n^2 stops every pole (HP_EINVAL with a message) and the plan then steps a valid
     medium as before; GMRES(2) with one cycle returns HP_WARN_NOCONV with each pole's one-cycle
