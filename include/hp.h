@@ -296,7 +296,11 @@ int hp_fit_exp_sqrt(double K, int degree, int lawson_steps, void* stream, hp_c12
  * round, and its byte figure counts floating-point operations instead
  * (8 (N-1)^3 ncomp per complex product: four per pole and round, except in a
  * round where every pole starts from the step's shared first basis vector,
- * whose first two products are pole-independent and run once). */
+ * whose first two products are pole-independent and run once).  The stretched
+ * operator commutes with the reflection of its axis, so where the given
+ * eigenvectors separate into even and odd ones (to rounding; an even and an
+ * odd one of equal eigenvalue may come mixed) the library makes the products on
+ * the even and odd halves, with half the operations (and counts half). */
 int hp_set_pml(hp_plan plan, double sigma_max, const void* Q, const void* Qinv, const void* lam);
 
 /* x_k of the last step, guess step or solve for pole k (Sec. 2 eq. W_k_def):

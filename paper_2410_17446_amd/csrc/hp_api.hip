@@ -10,6 +10,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -73,9 +74,6 @@ struct hp_plan_s {
   c128 *X = nullptr, *tmp1 = nullptr, *tmp2 = nullptr;
   PoleState* st = nullptr;
   PoleState* st_scratch = nullptr;
-  void** uptr = nullptr;
-  void** uptr_scratch = nullptr;
-  int* active_d = nullptr;
   double* est_d = nullptr;
   double2* part_dots = nullptr;
   double* part_norm = nullptr;
@@ -88,7 +86,7 @@ struct hp_plan_s {
   unsigned long long seq = 0;             // rounds launched (the tags)
   double* chk_h = nullptr;     // behind ftag_h: what the spectrum check reads back
   bool own_pin = false;        // ftag_h is the plan's (a batch worker lends its own)
-  std::vector<void*> uptr_h;
+  std::vector<char> own_u0;    // per pole: its first basis vector is its own (a restart), not the shared S_x w
   std::vector<int> fixed;
   std::vector<double> relres;
   std::vector<int> iters;
@@ -137,6 +135,9 @@ struct hp_plan_s {
   double pml_sigma = 0.0;
   char* pml_mem = nullptr;
   c128 *pml_q = nullptr, *pml_qi = nullptr, *pml_lam = nullptr, *pml_a2 = nullptr, *pml_a1 = nullptr;
+  // the same tables per parity (even block, then odd): matrices [2][N/2][N/2], eigenvalues [2][N/2]
+  bool pml_split = false;
+  c128 *pml_hq = nullptr, *pml_hqi = nullptr, *pml_hlam = nullptr;
   c128* pml_s = nullptr;
   c128* pml_shared = nullptr;  // two fields: the first round's pole-independent products
   double2* pml_part = nullptr;
@@ -269,9 +270,6 @@ void layout(hp_plan p, Ws& w) {
   p->tmp2 = w.take<c128>(fn);
   p->st = w.take<PoleState>(K);
   p->st_scratch = w.take<PoleState>(1);
-  p->uptr = w.take<void*>((size_t)K * (HP_MAXM + 1));
-  p->uptr_scratch = w.take<void*>(HP_MAXM + 1);
-  p->active_d = w.take<int>(2 * HP_MAXPOLES);
   p->est_d = w.take<double>(HP_MAXPOLES);
   p->part_dots = w.take<double2>((size_t)K * (HP_MAXM + 1) * 2 * p->napplyblk);
   p->part_norm = w.take<double>((size_t)K * p->nupdblk);
@@ -418,15 +416,6 @@ cx<T>* fld(void* base, size_t idx, size_t fieldn) {
   return reinterpret_cast<cx<T>*>(base) + idx * fieldn;
 }
 
-// The pointer table serves the absorbing layers' dense stages only.
-int upload_uptr(hp_plan p) {
-  if (!p->pml) return HP_OK;
-  hipError_t e = hipMemcpyAsync(p->uptr, p->uptr_h.data(), p->uptr_h.size() * sizeof(void*), hipMemcpyHostToDevice,
-                                p->stream);
-  if (e != hipSuccess) return hip_fail(p, e, "upload uptr");
-  return HP_OK;
-}
-
 // Cycle tolerance relative to the cycle's starting residual: complex64
 // transforms stop each cycle at 1e-5 (the FP64 true residual then restarts
 // the solve); with FP64 transforms a cycle runs to tol like FP64 mode.
@@ -451,27 +440,61 @@ void fold(hp_plan p, int k) {
   launch_mark_folded(p->st, k, 1, p->stream);
 }
 
-// Absorbing layers: z = sigma_m M_k^-1 u_m for the poles list[0..n) by the
+// The one-entry list of a single free-space solve (slot 0, m = 0, the shared vector).
+RoundList one_solve() {
+  RoundList l;
+  l.n = 1;
+  for (int a = 0; a < HP_MAXPOLES; ++a) l.e[a] = 0;
+  l.e[0] = round_entry(0, 0, true);
+  return l;
+}
+
+// Whether the dense stages of this plan and launch variant run on parity quadrants.
+bool pml_on_quadrants(hp_plan p) { return p->pml_split && p->geo.col_variant != 0; }
+
+// Absorbing layers: z = sigma_m M_k^-1 u_m for the poles of the list by the
 // eigen route of the Sylvester equation, Q [(Q^-1 u Q^-T) / (lam_p + lam_q - b_k)] Q^T,
-// in four dense stages through the pole's P field and its own scratch field.
-void pml_prec(hp_plan p, const PoleState* st, const int* list, int n, int* active_out, PmlRef in, PmlRef out,
-              c128* bufA, c128* bufB) {
-  const int N = p->d.nx;
+// in four dense stages through the pole's P field (bufA) and its own scratch field (bufB).
+void pml_prec(hp_plan p, const PoleState* st, const RoundList& l, PmlRef in, PmlRef out, c128* bufA, c128* bufB) {
+  const int N = p->d.nx, nc = p->d.ncomp;
   const size_t fn = p->fieldn;
   const PmlRef a{nullptr, bufA, fn, 0}, b{nullptr, bufB, fn, 0};
   const int v = p->geo.col_variant;  // the launch variant picks the dense stages' form
-  const int nc = p->d.ncomp;
-  launch_pml_gemm(v, true, 0, p->pml_qi, in, a, st, list, n, active_out, p->pml_lam, N, nc, p->stream);
-  launch_pml_gemm(v, false, 1, p->pml_qi, a, b, st, list, n, nullptr, p->pml_lam, N, nc, p->stream);
-  launch_pml_gemm(v, true, 0, p->pml_q, b, a, st, list, n, nullptr, p->pml_lam, N, nc, p->stream);
-  launch_pml_gemm(v, false, 2, p->pml_q, a, out, st, list, n, nullptr, p->pml_lam, N, nc, p->stream);
+  const bool sp = pml_on_quadrants(p);
+  const c128 *q = sp ? p->pml_hq : p->pml_q, *qi = sp ? p->pml_hqi : p->pml_qi, *lam = sp ? p->pml_hlam : p->pml_lam;
+  if (sp) launch_pml_fold(true, in, b, st, l, N, nc, p->stream);
+  launch_pml_gemm(v, sp, true, 0, false, qi, sp ? b : in, a, st, l, lam, N, nc, p->stream);
+  launch_pml_gemm(v, sp, false, 1, false, qi, a, b, st, l, lam, N, nc, p->stream);
+  launch_pml_gemm(v, sp, true, 0, false, q, b, a, st, l, lam, N, nc, p->stream);
+  launch_pml_gemm(v, sp, false, 2, false, q, a, sp ? b : out, st, l, lam, N, nc, p->stream);
+  if (sp) launch_pml_fold(false, b, out, st, l, N, nc, p->stream);
+}
+
+// The same in a round whose poles all start from the shared first basis vector u0: the first two
+// products once.
+void pml_prec_shared(hp_plan p, const RoundList& l, c128* u0, PmlRef out, c128* bufA, c128* bufB) {
+  const int N = p->d.nx, nc = p->d.ncomp, v = p->geo.col_variant;
+  const size_t fn = p->fieldn;
+  const PmlRef a{nullptr, bufA, fn, 0}, b{nullptr, bufB, fn, 0};
+  const PmlRef u{u0, nullptr, 0, 0}, t1{nullptr, p->pml_shared, 0, 0}, t2{nullptr, p->pml_shared + fn, 0, 0};
+  const bool sp = pml_on_quadrants(p);
+  const c128 *q = sp ? p->pml_hq : p->pml_q, *qi = sp ? p->pml_hqi : p->pml_qi, *lam = sp ? p->pml_hlam : p->pml_lam;
+  const RoundList one = one_solve();
+  launch_pml_shared_setup(p->st_scratch, mk(0.0, 0.0), p->stream);
+  if (sp) launch_pml_fold(true, u, t2, p->st_scratch, one, N, nc, p->stream);
+  launch_pml_gemm(v, sp, true, 0, false, qi, sp ? t2 : u, t1, p->st_scratch, one, lam, N, nc, p->stream);
+  launch_pml_gemm(v, sp, false, 0, false, qi, t1, t2, p->st_scratch, one, lam, N, nc, p->stream);
+  launch_pml_gemm(v, sp, true, 0, true, q, t2, a, p->st, l, lam, N, nc, p->stream);
+  launch_pml_gemm(v, sp, false, 2, false, q, a, sp ? b : out, p->st, l, lam, N, nc, p->stream);
+  if (sp) launch_pml_fold(false, b, out, p->st, l, N, nc, p->stream);
 }
 
 // Floating-point operations of one pole's four dense stages: 8 n^3 per complex
-// product of n x n matrices, n = N - 1 unknowns per axis, for each component.
+// product of n x n matrices, n = N - 1 unknowns per axis, for each component; half
+// of that on parity quadrants.
 double pml_flops(hp_plan p) {
   const double n = p->d.nx - 1.0;
-  return 4.0 * 8.0 * n * n * n * p->d.ncomp;
+  return (pml_on_quadrants(p) ? 0.5 : 1.0) * 4.0 * 8.0 * n * n * n * p->d.ncomp;
 }
 
 // Guess residuals for several poles at once: one buffer and one set of
@@ -506,18 +529,7 @@ int restart_from_residuals(hp_plan p, const std::vector<int>& rs, const std::vec
       launch_row_fwd_batch<T, C>(p->guess_r, fn, rj.data(), fld<T>(p->U, 0, fn), ustride, rs.data(), nr,
                                  p->guess_rpart, rblk, reinterpret_cast<const cx<C>*>(p->tw_x), p->geo, p->stream);
   }
-  bool changed = false;
-  for (int k : rs) {
-    void* u0 = fld<T>(p->U, (size_t)k * (p->d.restart + 1), fn);
-    if (p->uptr_h[(size_t)k * (HP_MAXM + 1)] != u0) {
-      p->uptr_h[(size_t)k * (HP_MAXM + 1)] = u0;
-      changed = true;
-    }
-  }
-  if (changed) {
-    int rc = upload_uptr(p);
-    if (rc) return rc;
-  }
+  for (int k : rs) p->own_u0[k] = 1;
   launch_cycle_init(p->st, rs.data(), nr, p->guess_rpart, (int)rblk, 0, p->d.tol, inner_rtol(p), p->stream, rblk, 1);
   return HP_OK;
 }
@@ -666,17 +678,7 @@ int run_poles(hp_plan p, const c128* w, const std::vector<int>& subset, bool* no
       launch_row_fwd<T, C>(w, bR, p->part_misc, twx, p->geo, p->stream);
     }
   }
-  bool changed = false;
-  for (int k : subset) {
-    if (p->uptr_h[(size_t)k * (HP_MAXM + 1)] != (void*)bR) {
-      p->uptr_h[(size_t)k * (HP_MAXM + 1)] = bR;
-      changed = true;
-    }
-  }
-  if (changed) {
-    int rc = upload_uptr(p);
-    if (rc) return rc;
-  }
+  p->own_u0.assign(K, 0);
   launch_cycle_init(p->st, subset.data(), (int)subset.size(), p->part_misc, p->nrowblk * d.ncomp, first, d.tol,
                     inner_rtol(p), p->stream);
   std::vector<char> live(K, 0);
@@ -765,23 +767,24 @@ int run_poles(hp_plan p, const c128* w, const std::vector<int>& subset, bool* no
   auto launch_iter = [&](const std::vector<int>& poles) -> int {
     const int slot = (int)(next_iter & 1);
     const int na = (int)poles.size();
-    int* ad = p->active_d + slot * HP_MAXPOLES;
     RoundList rl;
     rl.n = na;
     Flight fl{poles, slot, next_iter, 0, std::vector<int>(na), std::vector<char>(na), {-1, -1, -1}, false};
     for (int a = 0; a < na; ++a) {
       const int mk_ = (int)std::min<long>(next_iter - since[poles[a]], M - 1);
       fl.ms[a] = mk_;
-      fl.sh[a] = p->uptr_h[(size_t)poles[a] * (HP_MAXM + 1)] == (void*)bR;
+      fl.sh[a] = !p->own_u0[poles[a]];
       rl.e[a] = round_entry(poles[a], mk_, fl.sh[a]);
     }
     for (int a = na; a < HP_MAXPOLES; ++a) rl.e[a] = 0;
     if (p->pml) {
-      // absorbing layers: the dense stages (the first stores the list to ad),
-      // then p = A_k z - ~v_m with the inner products, on physical fields
+      // absorbing layers: the dense stages, then p = A_k z - ~v_m with the inner
+      // products, on physical fields
       c128* Zc = reinterpret_cast<c128*>(p->Z);
       c128* Pc = reinterpret_cast<c128*>(p->P);
-      c128* const* uc = reinterpret_cast<c128* const*>(p->uptr);
+      c128* uc = reinterpret_cast<c128*>(p->U);
+      c128* u0 = reinterpret_cast<c128*>(p->bR);
+      const size_t usp = (size_t)(M + 1) * fn;
       // a round in which every pole starts from the shared first basis vector shares
       // the first two dense products (matrix-core forms)
       bool shared = p->geo.col_variant != 0;
@@ -789,31 +792,16 @@ int run_poles(hp_plan p, const c128* w, const std::vector<int>& subset, bool* no
       fl.shared = shared;
       {
         Prof pr(p, HP_K_PML, -1.0, &fl.pslot[0]);
-        if (shared) {
-          const int zero = 0, N = d.nx, nc = d.ncomp;
-          c128* T1 = p->pml_shared;
-          c128* T2 = p->pml_shared + fn;
-          launch_pml_shared_setup(p->st_scratch, reinterpret_cast<c128**>(p->uptr_scratch),
-                                  reinterpret_cast<const c128*>(bR), p->stream);
-          launch_pml_gemm(p->geo.col_variant, true, 0, p->pml_qi,
-                          PmlRef{reinterpret_cast<c128* const*>(p->uptr_scratch), nullptr, 0, 0},
-                          PmlRef{nullptr, T1, 0, 0}, p->st_scratch, &zero, 1, nullptr, p->pml_lam, N, nc, p->stream);
-          launch_pml_gemm(p->geo.col_variant, false, 0, p->pml_qi, PmlRef{nullptr, T1, 0, 0},
-                          PmlRef{nullptr, T2, 0, 0}, p->st_scratch, &zero, 1, nullptr, p->pml_lam, N, nc, p->stream);
-          launch_pml_gemm_divided(p->pml_q, PmlRef{nullptr, T2, 0, 0}, PmlRef{nullptr, Pc, fn, 0}, p->st,
-                                  poles.data(), na, ad, p->pml_lam, N, nc, p->stream);
-          launch_pml_gemm(p->geo.col_variant, false, 2, p->pml_q, PmlRef{nullptr, Pc, fn, 0},
-                          PmlRef{nullptr, Zc, zsp, zsi}, p->st, poles.data(), na, nullptr, p->pml_lam, N, nc,
-                          p->stream);
-        } else {
-          pml_prec(p, p->st, poles.data(), na, ad, PmlRef{uc, nullptr, 0, 0}, PmlRef{nullptr, Zc, zsp, zsi}, Pc,
-                   p->pml_s);
-        }
+        const PmlRef z{nullptr, Zc, zsp, zsi};
+        if (shared)
+          pml_prec_shared(p, rl, u0, z, Pc, p->pml_s);
+        else
+          pml_prec(p, p->st, rl, PmlRef{u0, uc, usp, fn}, z, Pc, p->pml_s);
       }
       {
         Prof pr(p, HP_K_ROW_APPLY, -1.0, &fl.pslot[1]);
-        launch_pml_apply(Zc, zsp, zsi, Pc, psp, uc, p->coef, p->pml_a2, p->pml_a1, p->sc, p->st, ad, na, p->pml_part,
-                         d.nx, d.ncomp, p->stream);
+        launch_pml_apply(Zc, zsp, zsi, Pc, psp, Basis<c128>{u0, uc, usp, fn}, p->coef, p->pml_a2, p->pml_a1, p->sc,
+                         p->st, rl, p->pml_part, d.nx, d.ncomp, p->stream);
       }
       {
         Prof pr(p, HP_K_SMALL, 0.0);
@@ -1048,15 +1036,6 @@ __global__ void k_prec_setup(PoleState* st, c128 b) {
   st->sigma[0] = 1.0;
 }
 
-// The one-entry list of such a solve.
-RoundList one_solve() {
-  RoundList l;
-  l.n = 1;
-  for (int a = 0; a < HP_MAXPOLES; ++a) l.e[a] = 0;
-  l.e[0] = round_entry(0, 0, true);
-  return l;
-}
-
 // y = (Zbar_fs - b_k I)^{-1} x (pole < 0: b = 0), asynchronous, with the given
 // intermediate buffers: tmpR, zout (and dz for vector fields) R-domain fields,
 // st one pole state, part the row pass's partial norms.
@@ -1161,17 +1140,10 @@ int get_solution(hp_plan p, int k, c128* x) {
 template <typename T, typename C>
 int apply_prec(hp_plan p, int pole, const c128* x, c128* y) {
   if (p->pml) {
-    PoleState h;
-    memset(&h, 0, sizeof(h));
-    h.bk = pole < 0 ? mk(0.0, 0.0) : mk(p->poles[pole].re, p->poles[pole].im);
-    h.sigma[0] = 1.0;
-    void* tbl[HP_MAXM + 1] = {nullptr};
-    tbl[0] = const_cast<c128*>(x);
-    const int zero = 0;
-    HPCHK(hipMemcpyAsync(p->st_scratch, &h, sizeof(h), hipMemcpyHostToDevice, p->stream));
-    HPCHK(hipMemcpyAsync(p->uptr_scratch, tbl, sizeof(tbl), hipMemcpyHostToDevice, p->stream));
-    pml_prec(p, p->st_scratch, &zero, 1, nullptr, PmlRef{reinterpret_cast<c128* const*>(p->uptr_scratch), nullptr, 0, 0},
-             PmlRef{nullptr, y, 0, 0}, reinterpret_cast<c128*>(p->P), p->pml_s);
+    launch_pml_shared_setup(p->st_scratch, pole < 0 ? mk(0.0, 0.0) : mk(p->poles[pole].re, p->poles[pole].im),
+                            p->stream);
+    pml_prec(p, p->st_scratch, one_solve(), PmlRef{const_cast<c128*>(x), nullptr, 0, 0}, PmlRef{nullptr, y, 0, 0},
+             reinterpret_cast<c128*>(p->P), p->pml_s);
   } else {
     prec_ws<T, C>(p, pole, x, y);
   }
@@ -1289,14 +1261,7 @@ static int plan_create(const hp_plan_desc* desc, void* stream, void* workspace, 
     return rc;
   }
   clear_tile_rows(p);
-  // Krylov vector pointer table: u_i of pole k at U[k][i]
-  const size_t es = p->mixed ? sizeof(c64) : sizeof(c128);
-  p->uptr_h.assign((size_t)desc->npoles * (HP_MAXM + 1), nullptr);
-  for (int k = 0; k < desc->npoles; ++k)
-    for (int i = 0; i <= desc->restart; ++i)
-      p->uptr_h[(size_t)k * (HP_MAXM + 1) + i] =
-          reinterpret_cast<char*>(p->U) + ((size_t)k * (desc->restart + 1) + i) * p->fieldn * es;
-  if ((rc = upload_uptr(p)) || (rc = upload_state(p))) {
+  if ((rc = upload_state(p))) {
     g_thread_error = p->err;
     hp_plan_destroy(p);
     return rc;
@@ -1507,10 +1472,184 @@ int hp_set_form(hp_plan p, int form, int substeps) {
   return gmax > 1.0 + 1e-6 ? HP_WARN_UNSTABLE : HP_OK;
 }
 
+// ---- the eigen tables by parity
+
+// Q, Q^-1 and lam of the even and the odd subspace of the reflection j -> N - j (even block first),
+// in the coordinates of the folded fields: node j = 1..N/2 at entry j - 1, the odd block's last
+// entry padding (zero).  Empty when the given tables do not split.
+struct ParityTables {
+  std::vector<std::complex<double>> q, qi, lam;
+};
+
+// In place inverse of the n x n matrix a (row stride ld): LU with row pivots, then the columns of
+// the identity solved together (Gauss-Jordan, cheaper, loses four digits on these eigenvectors);
+// false if it meets a zero or non-finite pivot.
+static bool invert(std::complex<double>* a, int n, int ld) {
+  struct Rows {  // rows of real and imaginary parts, so that the row operations vectorise
+    int n;
+    std::vector<double> re, im;
+    explicit Rows(int n_) : n(n_), re((size_t)n_ * n_), im((size_t)n_ * n_) {}
+    // row r -= f * row k, from column c0 on
+    void axpy(int r, int k, double fr, double fi, int c0) {
+      double *__restrict__ ar = &re[(size_t)r * n], *__restrict__ ai = &im[(size_t)r * n];
+      const double *__restrict__ pr = &re[(size_t)k * n], *__restrict__ pi = &im[(size_t)k * n];
+      for (int c = c0; c < n; ++c) {
+        ar[c] -= fr * pr[c] - fi * pi[c];
+        ai[c] -= fr * pi[c] + fi * pr[c];
+      }
+    }
+    void swap(int r, int k) {
+      std::swap_ranges(&re[(size_t)r * n], &re[(size_t)r * n] + n, &re[(size_t)k * n]);
+      std::swap_ranges(&im[(size_t)r * n], &im[(size_t)r * n] + n, &im[(size_t)k * n]);
+    }
+  };
+  Rows m(n), x(n);
+  for (int r = 0; r < n; ++r) {
+    for (int c = 0; c < n; ++c) {
+      m.re[(size_t)r * n + c] = a[(size_t)r * ld + c].real();
+      m.im[(size_t)r * n + c] = a[(size_t)r * ld + c].imag();
+    }
+    x.re[(size_t)r * n + r] = 1.0;
+  }
+  for (int k = 0; k < n; ++k) {
+    int best = k;
+    double mag = -1.0;
+    for (int r = k; r < n; ++r) {
+      const double u = m.re[(size_t)r * n + k], v = m.im[(size_t)r * n + k], w = u * u + v * v;
+      if (w > mag) mag = w, best = r;
+    }
+    if (!(mag > 0.0) || !std::isfinite(mag)) return false;
+    if (best != k) m.swap(best, k), x.swap(best, k);
+    const double dr = m.re[(size_t)k * n + k] / mag, di = -m.im[(size_t)k * n + k] / mag;
+    for (int r = k + 1; r < n; ++r) {
+      const double u = m.re[(size_t)r * n + k], v = m.im[(size_t)r * n + k];
+      const double fr = u * dr - v * di, fi = u * di + v * dr;
+      m.axpy(r, k, fr, fi, k);
+      x.axpy(r, k, fr, fi, 0);
+    }
+  }
+  for (int k = n - 1; k >= 0; --k) {
+    const double u = m.re[(size_t)k * n + k], v = m.im[(size_t)k * n + k], w = u * u + v * v;
+    double *xr = &x.re[(size_t)k * n], *xi = &x.im[(size_t)k * n];
+    for (int c = 0; c < n; ++c) {
+      const double p = (xr[c] * u + xi[c] * v) / w, q = (xi[c] * u - xr[c] * v) / w;
+      xr[c] = p;
+      xi[c] = q;
+    }
+    for (int r = 0; r < k; ++r) x.axpy(r, k, m.re[(size_t)r * n + k], m.im[(size_t)r * n + k], 0);
+  }
+  for (int r = 0; r < n; ++r)
+    for (int c = 0; c < n; ++c) {
+      a[(size_t)r * ld + c] = {x.re[(size_t)r * n + c], x.im[(size_t)r * n + c]};
+      if (!std::isfinite(x.re[(size_t)r * n + c]) || !std::isfinite(x.im[(size_t)r * n + c])) return false;
+    }
+  return true;
+}
+
+// The operator commutes with the reflection, so each eigenvector is even or odd, except that an
+// eigensolver returns arbitrary mixtures where an even and an odd eigenvalue agree to rounding (modes
+// confined to the two layers).  Both columns of such a pair hold the same even and the same odd
+// vector, so one of them supplies each.  The halves' inverses are computed afresh: Q is so
+// ill-conditioned that folding the given inverse would not invert the folded vectors.
+static ParityTables parity_tables(const std::complex<double>* q, const std::complex<double>* l, int N) {
+  using cd = std::complex<double>;
+  const int n = N - 1, h = N / 2;
+  std::vector<double> ev(n, 0.0), od(n, 0.0);  // squared norms of each column's even and odd part
+  for (int j = 0; j < h; ++j)
+    for (int c = 0; c < n; ++c) {
+      const cd a = q[(size_t)j * n + c], b = q[(size_t)(n - 1 - j) * n + c];
+      const double w = j == h - 1 ? 0.25 : 0.5;  // the middle node is its own mirror image
+      ev[c] += w * std::norm(a + b);
+      od[c] += w * std::norm(a - b);
+    }
+  std::vector<int> role(n, -1), mixed;
+  int ne = 0, no = 0;
+  for (int c = 0; c < n; ++c) {
+    const double s = ev[c] + od[c];
+    if (!(s > 0.0) || !std::isfinite(s)) return {};
+    if (std::min(ev[c], od[c]) > 1e-6 * s)
+      mixed.push_back(c);
+    else if (ev[c] > od[c])
+      role[c] = 0, ++ne;
+    else
+      role[c] = 1, ++no;
+  }
+  for (int a : mixed) {
+    if (role[a] >= 0) continue;
+    int b = -1;
+    double gap = 1e300;
+    for (int c : mixed)
+      if (c != a && role[c] < 0 && std::norm(l[c] - l[a]) < gap) gap = std::norm(l[c] - l[a]), b = c;
+    if (b < 0) return {};
+    const bool first = ev[a] / (ev[a] + od[a]) >= ev[b] / (ev[b] + od[b]);
+    role[first ? a : b] = 0;
+    role[first ? b : a] = 1;
+    ++ne, ++no;
+  }
+  if (ne != h || no != h - 1) return {};
+  ParityTables t;
+  t.q.assign(2 * (size_t)h * h, cd(0.0));
+  t.lam.assign(2 * (size_t)h, cd(0.0));
+  int at[2] = {0, 0};
+  for (int c = 0; c < n; ++c) {
+    const int r = role[c], k = at[r]++;
+    for (int j = 0; j < h - r; ++j) {
+      const cd a = q[(size_t)j * n + c], b = q[(size_t)(n - 1 - j) * n + c];
+      t.q[((size_t)r * h + j) * h + k] = 0.5 * (r ? a - b : a + b);
+    }
+    t.lam[(size_t)r * h + k] = l[c];
+  }
+  t.qi = t.q;
+  bool ok[2] = {false, false};
+  auto odd = [&]() { ok[1] = invert(t.qi.data() + (size_t)h * h, h - 1, h); };
+  std::thread side;
+  try {
+    side = std::thread(odd);
+  } catch (const std::system_error&) {  // no thread to be had
+    odd();
+  }
+  ok[0] = invert(t.qi.data(), h, h);
+  if (side.joinable()) side.join();
+  return ok[0] && ok[1] ? t : ParityTables();
+}
+
+// Relative error of the split tables' operator on x against y = s D~ x.
+static double parity_error(const ParityTables& t, int N, const std::vector<std::complex<double>>& x,
+                           const std::vector<std::complex<double>>& y) {
+  using cd = std::complex<double>;
+  const int n = N - 1, h = N / 2;
+  std::vector<cd> out[2];
+  for (int r = 0; r < 2; ++r) {
+    const cd *q = t.q.data() + (size_t)r * h * h, *qi = t.qi.data() + (size_t)r * h * h;
+    std::vector<cd> f(h), m(h);
+    out[r].assign(h, cd(0.0));
+    for (int j = 0; j < h; ++j) f[j] = 0.5 * (r ? x[j] - x[n - 1 - j] : x[j] + x[n - 1 - j]);
+    for (int k = 0; k < h; ++k) {
+      cd s = 0.0;
+      for (int j = 0; j < h; ++j) s += qi[(size_t)k * h + j] * f[j];
+      m[k] = t.lam[(size_t)r * h + k] * s;
+    }
+    for (int j = 0; j < h; ++j)
+      for (int k = 0; k < h; ++k) out[r][j] += q[(size_t)j * h + k] * m[k];
+  }
+  double num = 0.0, den = 0.0;
+  for (int j = 0; j < h; ++j) {
+    num += std::norm(out[0][j] + out[1][j] - y[j]);
+    den += std::norm(y[j]);
+    if (j == h - 1) continue;
+    num += std::norm(out[0][j] - out[1][j] - y[n - 1 - j]);
+    den += std::norm(y[n - 1 - j]);
+  }
+  const double e = std::sqrt(num / den);
+  return std::isfinite(e) ? e : 1e300;
+}
+
 static void free_pml(hp_plan p) {
   if (p->pml_mem) (void)hipFree(p->pml_mem);
   p->pml_mem = nullptr;
   p->pml_q = p->pml_qi = p->pml_lam = p->pml_a2 = p->pml_a1 = p->pml_s = p->pml_shared = nullptr;
+  p->pml_hq = p->pml_hqi = p->pml_hlam = nullptr;
+  p->pml_split = false;
   p->pml_part = nullptr;
   p->pml = false;
   p->pml_sigma = 0.0;
@@ -1557,6 +1696,7 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
     a2[j] = mk(a2c[j].real(), a2c[j].imag());
     a1[j] = mk(a1c[j].real(), a1c[j].imag());
   }
+  ParityTables split = parity_tables(q, l, N);
   // the tables must decompose this library's stretched operator: compare
   // Q (lam .* (Q^-1 x)) with s D~ x for two pseudo-random x
   {
@@ -1565,6 +1705,7 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
       rs = rs * 6364136223846793005ull + 1442695040888963407ull;
       return (double)(rs >> 11) / 9007199254740992.0 - 0.5;
     };
+    double whole = 0.0, halves = 0.0;  // largest relative errors of the given and the split tables
     for (int probe = 0; probe < 2; ++probe) {
       std::vector<cd> x(n), t(n), ye(n, 0.0), yd(n);
       for (int j = 0; j < n; ++j) x[j] = cd(rnd(), rnd());
@@ -1607,20 +1748,30 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
         return fail(p, HP_EINVAL,
                     "Q diag(lam) Q^-1 does not reproduce the stretched operator s D~ of this plan (relative error " +
                         std::to_string(std::sqrt(num / den)) + ")");
+      whole = std::max(whole, std::sqrt(num / den));
+      if (!split.lam.empty()) halves = std::max(halves, parity_error(split, N, x, yd));
     }
+    // the split tables serve only where they decompose the operator as well as the given ones
+    if (!(halves <= 4.0 * whole + 1e-12)) split = ParityTables();
   }
   for (int k = 0; k < d.npoles; ++k) {
     const cd b(p->poles[k].re, p->poles[k].im);
     double mn = 1e300;
-    for (int a = 0; a < n; ++a)
-      for (int c = 0; c < n; ++c) mn = std::min(mn, std::abs(l[a] + l[c] - b));
-    if (!(mn > 1e-12 * (1.0 + std::abs(b))))
+    for (int a = 0; a < n; ++a) {
+      const double xr = l[a].real() - b.real(), xi = l[a].imag() - b.imag();
+      for (int c = 0; c < n; ++c) {  // squares: no hypot per pair
+        const double re = xr + l[c].real(), im = xi + l[c].imag();
+        const double v = re * re + im * im;
+        mn = v < mn ? v : mn;
+      }
+    }
+    if (!(std::sqrt(mn) > 1e-12 * (1.0 + std::abs(b))))
       return fail(p, HP_EINVAL, "pole " + std::to_string(k) + " lies on the stretched free-space spectrum");
   }
   const size_t NN = (size_t)N * N, fn = p->fieldn, K = (size_t)d.npoles;
   const size_t nparts = (size_t)pml_apply_parts(N);
   if (!p->pml_mem) {
-    const size_t bytes = (2 * NN + 3 * (size_t)N + (K + 2) * fn) * sizeof(c128) +
+    const size_t bytes = (2 * NN + NN + 4 * (size_t)N + (K + 2) * fn) * sizeof(c128) +
                          K * (HP_MAXM + 1) * 2 * nparts * sizeof(double2);
     hipError_t e = hipMalloc(&p->pml_mem, bytes);
     if (e != hipSuccess) {
@@ -1633,7 +1784,10 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
     p->pml_lam = c + 2 * NN;
     p->pml_a2 = p->pml_lam + N;
     p->pml_a1 = p->pml_a2 + N;
-    p->pml_s = p->pml_a1 + N;
+    p->pml_hq = p->pml_a1 + N;
+    p->pml_hqi = p->pml_hq + NN / 2;
+    p->pml_hlam = p->pml_hqi + NN / 2;
+    p->pml_s = p->pml_hlam + N;
     p->pml_shared = p->pml_s + K * fn;
     p->pml_part = reinterpret_cast<double2*>(p->pml_shared + 2 * fn);
   }
@@ -1653,13 +1807,17 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
   HPCHK(hipMemcpy(p->pml_lam, lp.data(), N * sizeof(c128), hipMemcpyHostToDevice));
   HPCHK(hipMemcpy(p->pml_a2, a2.data(), N * sizeof(c128), hipMemcpyHostToDevice));
   HPCHK(hipMemcpy(p->pml_a1, a1.data(), N * sizeof(c128), hipMemcpyHostToDevice));
+  if (!split.lam.empty()) {
+    HPCHK(hipMemcpy(p->pml_hq, split.q.data(), split.q.size() * sizeof(cd), hipMemcpyHostToDevice));
+    HPCHK(hipMemcpy(p->pml_hqi, split.qi.data(), split.qi.size() * sizeof(cd), hipMemcpyHostToDevice));
+    HPCHK(hipMemcpy(p->pml_hlam, split.lam.data(), split.lam.size() * sizeof(cd), hipMemcpyHostToDevice));
+  }
+  p->pml_split = !split.lam.empty();
   // the medium-pass slots and the dense stages' scratch start from zero (rows 0 and columns 0 stay so)
   HPCHK(hipMemset(p->pml_s, 0, (K + 2) * fn * sizeof(c128)));
   p->pml = true;
   p->pml_sigma = sigma_max;
   p->prev_valid = false;
-  if (int rc = upload_uptr(p)) return rc;  // kept on the device from here on
-  HPCHK(hipStreamSynchronize(p->stream));
   return HP_OK;
 }
 
@@ -1739,9 +1897,9 @@ int hp_get_stats(hp_plan p, int* iters_per_pole, double* final_relres) {
   if (!p) return fail(nullptr, HP_EINVAL, "plan is NULL");
   // the heads of the states (counts and estimates), not their 200 KB of matrices
   std::vector<PoleHead> h(p->d.npoles);
-  HPCHK(hipMemcpy2DAsync(h.data(), sizeof(PoleHead), p->st, sizeof(PoleState), sizeof(PoleHead), p->d.npoles,
-                         hipMemcpyDeviceToHost, p->stream));
   HPCHK(hipStreamSynchronize(p->stream));
+  HPCHK(hipMemcpy2D(h.data(), sizeof(PoleHead), p->st, sizeof(PoleState), sizeof(PoleHead), p->d.npoles,
+                    hipMemcpyDeviceToHost));
   for (int k = 0; k < p->d.npoles; ++k) {
     if (iters_per_pole) iters_per_pole[k] = h[k].total;
     if (final_relres) {

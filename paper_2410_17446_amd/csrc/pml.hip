@@ -3,6 +3,7 @@
 // operator (for the Arnoldi step with its inner products, and for true
 // residuals), copies and the residue-weighted sum.  FP64 throughout.
 #include "pml.hpp"
+#include "wave.hpp"
 
 namespace {
 
@@ -21,8 +22,9 @@ __device__ __forceinline__ double pml_block_sum(double v, double* red) {
   return threadIdx.x == 0 ? (red[0] + red[1]) + (red[2] + red[3]) : 0.0;
 }
 
-__device__ __forceinline__ const c128* pml_field(const PmlRef& r, int k, int m) {
-  return r.tbl ? r.tbl[(size_t)k * (HP_MAXM + 1) + m] : r.base + (size_t)k * r.sp + (size_t)m * r.si;
+__device__ __forceinline__ c128* pml_field(const PmlRef& r, int e) {
+  const int m = round_m(e);
+  return (r.sh && m == 0 && round_shared(e)) ? r.sh : r.base + (size_t)round_pole(e) * r.sp + (size_t)m * r.si;
 }
 
 // ------------------------------------------------------------------ dense stages
@@ -37,18 +39,15 @@ constexpr int GT = 64, GK = 16, GWG = 256;
 
 template <bool LEFT, int EPI>
 __global__ __launch_bounds__(GWG) void k_pml_gemm(const c128* __restrict__ mat, PmlRef in, PmlRef out,
-                                                  const PoleState* __restrict__ st, PoleList list,
-                                                  int* __restrict__ active_out, const c128* __restrict__ lam, int N,
-                                                  int ncomp) {
+                                                  const PoleState* __restrict__ st, RoundList list,
+                                                  const c128* __restrict__ lam, int N, int ncomp) {
   // blockIdx.z: pole list entry a, field component comp (components are N x N planes)
   const int a_ = blockIdx.z / ncomp, comp = blockIdx.z % ncomp;
-  const int k = list.k[a_];
-  if (active_out && comp == 0 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) active_out[a_] = k;
+  const int en = list.e[a_], k = round_pole(en), m = round_m(en);
   if (st[k].flag) return;
-  const int m = st[k].m;
   const size_t co = (size_t)comp * N * N;
-  const c128* __restrict__ X = pml_field(in, k, m) + co;
-  c128* __restrict__ Y = const_cast<c128*>(pml_field(out, k, m)) + co;
+  const c128* __restrict__ X = pml_field(in, en) + co;
+  c128* __restrict__ Y = pml_field(out, en) + co;
   const int r0 = blockIdx.y * GT, c0 = blockIdx.x * GT;
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   // A[r][j] = Mat[r][j] (left) or X[r][j] (right); B[j][c] = X[j][c] (left) or Mat[c][j] (right)
@@ -128,22 +127,32 @@ __global__ __launch_bounds__(GWG) void k_pml_gemm(const c128* __restrict__ mat, 
 // the bytes per multiply-add that the vector-ALU form needs.  BT x BT block
 // tile, four waves of BT/2 x BT/2, K staged through LDS in steps of 16 as there;
 // at most 128 registers per lane (accumulators included), four waves per SIMD.
+//
+// SPLIT: the operand planes are folded (k_pml_fold below) into the four parity
+// quadrants of H = N/2 rows and columns, so N here is H, blockIdx.z runs over the
+// quadrants too, and the matrix and eigenvalues are the row parity's (left) or
+// column parity's (right).  Entry H-1 of an odd axis is padding.  Without SPLIT
+// row and column 0 are.
 typedef double pml_d4 __attribute__((ext_vector_type(4)));
 
-template <bool LEFT, int EPI, int BT, bool DIVB = false>
+template <bool LEFT, int EPI, int BT, bool DIVB, bool SPLIT>
 __global__ __launch_bounds__(GWG, 4) void k_pml_gemm_mfma(const c128* __restrict__ mat, PmlRef in, PmlRef out,
-                                                       const PoleState* __restrict__ st, PoleList list,
-                                                       int* __restrict__ active_out, const c128* __restrict__ lam,
-                                                       int N, int ncomp) {
+                                                       const PoleState* __restrict__ st, RoundList list,
+                                                       const c128* __restrict__ lam, int N, int ncomp) {
   constexpr int WT = BT / 2, MB = WT / 16, LPT = BT * GK / GWG;
-  const int a_ = blockIdx.z / ncomp, comp = blockIdx.z % ncomp;
-  const int k = list.k[a_];
-  if (active_out && comp == 0 && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) active_out[a_] = k;
+  const int plane = blockIdx.z % (SPLIT ? 4 * ncomp : ncomp);  // component, or (component, quadrant)
+  const int en = list.e[blockIdx.z / (SPLIT ? 4 * ncomp : ncomp)], k = round_pole(en), m = round_m(en);
   if (st[k].flag) return;
-  const int m = st[k].m;
-  const size_t co = (size_t)comp * N * N;
-  const c128* __restrict__ X = pml_field(in, k, m) + co;
-  c128* __restrict__ Y = const_cast<c128*>(pml_field(out, k, m)) + co;
+  const int pr = SPLIT ? (plane >> 1) & 1 : 0, pc = SPLIT ? plane & 1 : 0;  // row and column parity (1: odd)
+  const size_t co = (size_t)plane * N * N;
+  if (SPLIT) mat += (size_t)(LEFT ? pr : pc) * N * N;
+  const c128* __restrict__ lr = lam + pr * N;
+  const c128* __restrict__ lc = lam + pc * N;
+  auto pad = [&](int r, int c) {
+    return SPLIT ? (pr && r == N - 1) || (pc && c == N - 1) : r == 0 || c == 0;
+  };
+  const c128* __restrict__ X = pml_field(in, en) + co;
+  c128* __restrict__ Y = pml_field(out, en) + co;
   // right products: consecutive workgroups (spread over the XCDs) take consecutive row
   // tiles, so each XCD keeps its row slabs of the field operand
   const int r0 = (LEFT ? blockIdx.y : blockIdx.x) * BT, c0 = (LEFT ? blockIdx.x : blockIdx.y) * BT;
@@ -164,7 +173,7 @@ __global__ __launch_bounds__(GWG, 4) void k_pml_gemm_mfma(const c128* __restrict
         const int jr = j0 + e / BT, jc = c0 + e % BT;
         rb[q] = Bg[(size_t)jr * N + jc];
         // the divide of the pole's middle stage, applied to a product shared by all poles
-        if (DIVB) rb[q] = (jr == 0 || jc == 0) ? mk(0.0, 0.0) : cdiv(rb[q], lam[jr] + lam[jc] - bk0);
+        if (DIVB) rb[q] = pad(jr, jc) ? mk(0.0, 0.0) : cdiv(rb[q], lr[jr] + lc[jc] - bk0);
       } else {
         rb[q] = Bg[(size_t)(c0 + e / GK) * N + j0 + e % GK];
       }
@@ -235,10 +244,67 @@ __global__ __launch_bounds__(GWG, 4) void k_pml_gemm_mfma(const c128* __restrict
       for (int r = 0; r < 4; ++r) {
         const int row = r0 + wr + a * 16 + 4 * r + lk, col = c0 + wc + b * 16 + li;
         c128 v = mk(cr[a][b][r], ci[a][b][r]);
-        if (EPI == 1) v = (row == 0 || col == 0) ? mk(0.0, 0.0) : cdiv(v, lam[row] + lam[col] - bk);
+        if (EPI == 1) v = pad(row, col) ? mk(0.0, 0.0) : cdiv(v, lr[row] + lc[col] - bk);
         if (EPI == 2) v = sg * v;
         Y[(size_t)row * N + col] = v;
       }
+}
+
+// The stretch is the same at both ends of an axis, so the one-axis operator
+// commutes with the reflection j -> N - j and its eigenvectors are even or odd:
+// a product with Q or Q^-1 splits into two of half the size, half the
+// arithmetic.  Fold: the plane's four parity quadrants (even/odd rows x
+// even/odd columns; entry j - 1 holds node j = 1..N/2),
+//   x_e(j) = (x_j + x_{N-j})/2, x_o(j) = (x_j - x_{N-j})/2  along each axis,
+// and back: x_j = x_e + x_o, x_{N-j} = x_e - x_o.  One pass over the field each
+// way, bound by the copy rate (25 us for 16 poles of 512^2), for half of the dense
+// work: a product of 16 poles of 512^2 went from 345-375 to 180-210 us.
+__global__ __launch_bounds__(256) void k_pml_fold(PmlRef in, PmlRef out, const PoleState* __restrict__ st,
+                                                  RoundList list, int N, int ncomp) {
+  const int comp = blockIdx.y % ncomp, en = list.e[blockIdx.y / ncomp], H = N / 2;
+  if (st[round_pole(en)].flag) return;
+  const c128* __restrict__ x = pml_field(in, en) + (size_t)comp * N * N;
+  c128* __restrict__ y = pml_field(out, en) + (size_t)comp * N * N;
+  const int i = 1 + blockIdx.x;
+  for (int j = 1 + threadIdx.x; j <= H; j += 256) {
+    const c128 a = x[(size_t)i * N + j], b = x[(size_t)i * N + N - j];
+    const c128 c = x[(size_t)(N - i) * N + j], d = x[(size_t)(N - i) * N + N - j];
+    const c128 pe = a + b, po = a - b, qe = c + d, qo = c - d;  // columns folded, rows i and N - i
+    const size_t o = (size_t)(i - 1) * H + j - 1, Q = (size_t)H * H;
+    y[o] = 0.25 * (pe + qe);
+    y[Q + o] = 0.25 * (po + qo);
+    y[2 * Q + o] = 0.25 * (pe - qe);
+    y[3 * Q + o] = 0.25 * (po - qo);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_pml_unfold(PmlRef in, PmlRef out, const PoleState* __restrict__ st,
+                                                    RoundList list, int N, int ncomp) {
+  const int comp = blockIdx.y % ncomp, en = list.e[blockIdx.y / ncomp], H = N / 2;
+  if (st[round_pole(en)].flag) return;
+  const c128* __restrict__ x = pml_field(in, en) + (size_t)comp * N * N;
+  c128* __restrict__ y = pml_field(out, en) + (size_t)comp * N * N;
+  const c128 zero = mk(0.0, 0.0);
+  if (blockIdx.x == 0) {  // the Dirichlet row
+    for (int j = threadIdx.x; j < N; j += 256) y[j] = zero;
+    return;
+  }
+  const int i = blockIdx.x;
+  for (int j = 1 + threadIdx.x; j <= H; j += 256) {
+    const size_t o = (size_t)(i - 1) * H + j - 1, Q = (size_t)H * H;
+    const c128 ee = x[o], eo = x[Q + o], oe = x[2 * Q + o], oo = x[3 * Q + o];
+    const c128 pe = ee + oe, po = eo + oo, qe = ee - oe, qo = eo - oo;  // rows i and N - i
+    y[(size_t)i * N + j] = pe + po;
+    if (j < H) y[(size_t)i * N + N - j] = pe - po;
+    if (i < H) {
+      y[(size_t)(N - i) * N + j] = qe + qo;
+      if (j < H) y[(size_t)(N - i) * N + N - j] = qe - qo;
+    }
+  }
+  if (threadIdx.x == 0) {
+    y[(size_t)i * N] = zero;
+    if (i < H) y[(size_t)(N - i) * N] = zero;
+  }
 }
 
 // ------------------------------------------------------------------ stretched explicit operator
@@ -375,21 +441,19 @@ __global__ __launch_bounds__(256) void k_pml_residual(const c128* __restrict__ x
 // takes four points of a tile column.  The inner products are summed per wave.
 template <int NC>
 __global__ __launch_bounds__(256) void k_pml_apply(const c128* __restrict__ zbase, size_t zsp, size_t zsi,
-                                                   c128* __restrict__ pbase, size_t psp, c128* const* __restrict__ uptr,
+                                                   c128* __restrict__ pbase, size_t psp, const Basis<c128> basis,
                                                    const double* __restrict__ coef, const c128* __restrict__ a2,
                                                    const c128* __restrict__ a1, StencilCoef sc,
-                                                   const PoleState* __restrict__ st, const int* __restrict__ active,
+                                                   const PoleState* __restrict__ st, const RoundList list,
                                                    double2* __restrict__ part, int nparts, int N) {
   __shared__ c128 tile[NC][AP_LY * AP_LX];
-  const int k = active[blockIdx.y];
+  const int en = list.e[blockIdx.y], k = round_pole(en), m = round_m(en);
   if (st[k].flag) return;
-  const int m = st[k].m;
   const size_t fsz = (size_t)N * N;
   const c128 bk = st[k].bk;
   const double sg = st[k].sigma[m];
   const c128* z = zbase + (size_t)k * zsp + (size_t)m * zsi;
   c128* p = pbase + (size_t)k * psp;
-  const c128* const* up = uptr + (size_t)k * (HP_MAXM + 1);
   const int ntx = N / AP_X;
   const int x0 = (blockIdx.x % ntx) * AP_X, y0 = (blockIdx.x / ntx) * AP_Y;
   const int tid = threadIdx.x, tx = tid & 63, tq = tid >> 6;
@@ -400,7 +464,7 @@ __global__ __launch_bounds__(256) void k_pml_apply(const c128* __restrict__ zbas
   __syncthreads();
   c128 pv[4][NC], um[4][NC];
   {
-    const c128* u = up[m];
+    const c128* u = basis.at(en, m);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int ty = tq + 4 * q, i = y0 + ty, j = x0 + tx;
@@ -427,7 +491,7 @@ __global__ __launch_bounds__(256) void k_pml_apply(const c128* __restrict__ zbas
   const int wave = tid >> 6, lane = tid & 63;
   const int slot = blockIdx.x * 4 + wave;
   for (int i = 0; i <= m; ++i) {
-    const c128* u = up[i];
+    const c128* u = basis.at(en, i);
     double pr = 0.0, pi = 0.0, qr = 0.0, qi = 0.0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -441,14 +505,10 @@ __global__ __launch_bounds__(256) void k_pml_apply(const c128* __restrict__ zbas
         qi += a.re * um[q][c].im - a.im * um[q][c].re;
       }
     }
-    pr = pml_wave_sum(pr);
-    pi = pml_wave_sum(pi);
-    qr = pml_wave_sum(qr);
-    qi = pml_wave_sum(qi);
-    if (lane == 0) {
-      const size_t b = (((size_t)k * (HP_MAXM + 1) + i) * 2) * nparts + slot;
-      part[b] = make_double2(pr, pi);
-      part[b + nparts] = make_double2(qr, qi);
+    const double r = wave_sum4(pr, pi, qr, qi);
+    if (lane < 4) {
+      const size_t b = (((size_t)k * (HP_MAXM + 1) + i) * 2 + (lane >> 1)) * nparts + slot;
+      reinterpret_cast<double*>(part + b)[lane & 1] = r;
     }
   }
 }
@@ -514,84 +574,100 @@ int flat_blocks(size_t n) {
 
 }  // namespace
 
-__global__ void k_pml_shared_setup(PoleState* st, c128** tbl, const c128* u0) {
+__global__ void k_pml_shared_setup(PoleState* st, c128 b) {
   if (threadIdx.x != 0) return;
   st->flag = 0;
   st->m = 0;
-  st->bk = mk(0.0, 0.0);
+  st->bk = b;
   st->sigma[0] = 1.0;
-  tbl[0] = const_cast<c128*>(u0);
 }
 
-void launch_pml_shared_setup(PoleState* st, c128** tbl, const c128* u0, hipStream_t s) {
-  hipLaunchKernelGGL(k_pml_shared_setup, dim3(1), dim3(64), 0, s, st, tbl, u0);
+void launch_pml_shared_setup(PoleState* st, c128 b, hipStream_t s) {
+  hipLaunchKernelGGL(k_pml_shared_setup, dim3(1), dim3(64), 0, s, st, b);
 }
 
-void launch_pml_gemm_divided(const c128* mat, PmlRef in, PmlRef out, const PoleState* st, const int* list, int n,
-                             int* active_out, const c128* lam, int N, int ncomp, hipStream_t s) {
-  const PoleList l = make_list(list, n);
-  const int big = n * ncomp * (N / 64) * (N / 64) >= 512;
-  const int bt = big ? 64 : 32;
-  const dim3 grid(N / bt, N / bt, n * ncomp);
-  if (bt == 64)
-    hipLaunchKernelGGL((k_pml_gemm_mfma<true, 0, 64, true>), grid, dim3(GWG), 0, s, mat, in, out, st, l, active_out,
-                       lam, N, ncomp);
-  else
-    hipLaunchKernelGGL((k_pml_gemm_mfma<true, 0, 32, true>), grid, dim3(GWG), 0, s, mat, in, out, st, l, active_out,
-                       lam, N, ncomp);
-}
-
-void launch_pml_gemm(int variant, bool left, int epilogue, const c128* mat, PmlRef in, PmlRef out,
-                     const PoleState* st, const int* list, int n, int* active_out, const c128* lam, int N, int ncomp,
+void launch_pml_fold(bool fold, PmlRef in, PmlRef out, const PoleState* st, const RoundList& list, int N, int ncomp,
                      hipStream_t s) {
-  const PoleList l = make_list(list, n);
-  // variant 1 takes 64 x 64 tiles while they give every CU two workgroups, else 32 x 32
-  const int big = n * ncomp * (N / 64) * (N / 64) >= 512;
-  const int bt = (variant == 2 || (variant == 1 && !big)) ? 32 : 64;
-  const dim3 grid(N / bt, N / bt, n * ncomp);
-#define G_(L, E)                                                                                                   \
-  do {                                                                                                             \
-    if (variant == 0)                                                                                              \
-      hipLaunchKernelGGL((k_pml_gemm<L, E>), grid, dim3(GWG), 0, s, mat, in, out, st, l, active_out, lam, N, ncomp); \
-    else if (bt == 32)                                                                                             \
-      hipLaunchKernelGGL((k_pml_gemm_mfma<L, E, 32>), grid, dim3(GWG), 0, s, mat, in, out, st, l, active_out, lam, \
-                         N, ncomp);                                                                                \
-    else                                                                                                           \
-      hipLaunchKernelGGL((k_pml_gemm_mfma<L, E, 64>), grid, dim3(GWG), 0, s, mat, in, out, st, l, active_out, lam, \
-                         N, ncomp);                                                                                \
-  } while (0)
-  if (left) {
-    if (epilogue == 1)
-      G_(true, 1);
-    else if (epilogue == 2)
-      G_(true, 2);
-    else
+  if (fold)
+    hipLaunchKernelGGL(k_pml_fold, dim3(N / 2, list.n * ncomp), dim3(256), 0, s, in, out, st, list, N, ncomp);
+  else
+    hipLaunchKernelGGL(k_pml_unfold, dim3(N / 2 + 1, list.n * ncomp), dim3(256), 0, s, in, out, st, list, N, ncomp);
+}
+
+namespace {
+
+// Block tile of the matrix-core products of n planes of size h: 64 while that
+// gives every CU two workgroups (512), else 32, where four times as many cover
+// the chip; variant 2 always 32, 3 always 64.  Sizes that 64 does not divide
+// (half of 64 and of 192) take 32.
+int pml_block_tile(int variant, int n, int h) {
+  if (h % 64) return 32;
+  const bool big = n * (h / 64) * (h / 64) >= 512;
+  return (variant == 2 || (variant == 1 && !big)) ? 32 : 64;
+}
+
+template <bool LEFT, int EPI, bool DIVB, bool SPLIT>
+void gemm_mfma(int variant, const c128* mat, PmlRef in, PmlRef out, const PoleState* st, const RoundList& list,
+               const c128* lam, int N, int ncomp, hipStream_t s) {
+  const int h = SPLIT ? N / 2 : N, planes = list.n * ncomp * (SPLIT ? 4 : 1);
+  const int bt = pml_block_tile(variant, planes, h);
+  const dim3 grid(h / bt, h / bt, planes);
+  if (bt == 64)
+    hipLaunchKernelGGL((k_pml_gemm_mfma<LEFT, EPI, 64, DIVB, SPLIT>), grid, dim3(GWG), 0, s, mat, in, out, st, list,
+                       lam, h, ncomp);
+  else
+    hipLaunchKernelGGL((k_pml_gemm_mfma<LEFT, EPI, 32, DIVB, SPLIT>), grid, dim3(GWG), 0, s, mat, in, out, st, list,
+                       lam, h, ncomp);
+}
+
+}  // namespace
+
+void launch_pml_gemm(int variant, bool split, bool left, int epilogue, bool divided, const c128* mat, PmlRef in,
+                     PmlRef out, const PoleState* st, const RoundList& list, const c128* lam, int N, int ncomp,
+                     hipStream_t s) {
+  if (variant == 0 && !split) {
+    const dim3 grid(N / GT, N / GT, list.n * ncomp);
+#define G_(L, E) \
+  hipLaunchKernelGGL((k_pml_gemm<L, E>), grid, dim3(GWG), 0, s, mat, in, out, st, list, lam, N, ncomp)
+    if (left)
       G_(true, 0);
-  } else {
-    if (epilogue == 1)
+    else if (epilogue == 1)
       G_(false, 1);
-    else if (epilogue == 2)
-      G_(false, 2);
     else
-      G_(false, 0);
-  }
+      G_(false, 2);
 #undef G_
+    return;
+  }
+#define M_(L, E, D)                                                                                  \
+  (split ? gemm_mfma<L, E, D, true>(variant, mat, in, out, st, list, lam, N, ncomp, s)             \
+         : gemm_mfma<L, E, D, false>(variant, mat, in, out, st, list, lam, N, ncomp, s))
+  if (left && divided)
+    M_(true, 0, true);
+  else if (left)
+    M_(true, 0, false);
+  else if (epilogue == 1)
+    M_(false, 1, false);
+  else if (epilogue == 2)
+    M_(false, 2, false);
+  else
+    M_(false, 0, false);
+#undef M_
 }
 
 int pml_tiles(int N) { return (N / AP_X) * (N / AP_Y); }
 
 int pml_apply_parts(int N) { return pml_tiles(N) * 4; }
 
-void launch_pml_apply(const c128* zbase, size_t zsp, size_t zsi, c128* pbase, size_t psp, c128* const* uptr,
+void launch_pml_apply(const c128* zbase, size_t zsp, size_t zsi, c128* pbase, size_t psp, const Basis<c128>& basis,
                       const double* coef, const c128* a2, const c128* a1, const StencilCoef& sc, const PoleState* st,
-                      const int* active, int nactive, double2* part, int N, int ncomp, hipStream_t s) {
+                      const RoundList& list, double2* part, int N, int ncomp, hipStream_t s) {
   const int nparts = pml_apply_parts(N);
   if (ncomp == 2)
-    hipLaunchKernelGGL(k_pml_apply<2>, dim3(nparts / 4, nactive), dim3(256), 0, s, zbase, zsp, zsi, pbase, psp,
-                       uptr, coef, a2, a1, sc, st, active, part, nparts, N);
+    hipLaunchKernelGGL(k_pml_apply<2>, dim3(nparts / 4, list.n), dim3(256), 0, s, zbase, zsp, zsi, pbase, psp, basis,
+                       coef, a2, a1, sc, st, list, part, nparts, N);
   else
-    hipLaunchKernelGGL(k_pml_apply<1>, dim3(nparts / 4, nactive), dim3(256), 0, s, zbase, zsp, zsi, pbase, psp,
-                       uptr, coef, a2, a1, sc, st, active, part, nparts, N);
+    hipLaunchKernelGGL(k_pml_apply<1>, dim3(nparts / 4, list.n), dim3(256), 0, s, zbase, zsp, zsi, pbase, psp, basis,
+                       coef, a2, a1, sc, st, list, part, nparts, N);
 }
 
 bool launch_pml_residual(const c128* x, size_t xbs, const c128* rhs, c128* y, size_t ybs, const double* coef,

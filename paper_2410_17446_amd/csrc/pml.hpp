@@ -20,48 +20,51 @@
 
 #include "kernels.hpp"
 
-// Where a dense stage reads or writes pole k's field (m = the pole's current
-// Arnoldi index): the basis table entry tbl[k (HP_MAXM + 1) + m] when tbl is
-// set, else base + k sp + m si.
+// Where a dense stage reads or writes the field of list entry e (pole k,
+// Arnoldi index m): base + k sp + m si, but sh (when set) where the entry's
+// first basis vector is the step's shared one and m = 0.
 struct PmlRef {
-  c128* const* tbl;
+  c128* sh;
   c128* base;
   size_t sp, si;
 };
 
 // One of the four dense stages of
 //   M_k^-1 y = Q [(Q^-1 y Q^-T) / (lam_p + lam_q - b_k)] Q^T,
-// over the poles list[0..n) (host array, by value; poles with a nonzero flag
-// skip themselves): left Out = Mat In, or right Out = In Mat^T; epilogue 0
-// none, 1 divide entry (p, q) by lam_p + lam_q - b_k, 2 scale by the pole's
-// sigma_m.  active_out (may be NULL) receives the list for later kernels.
-// variant: 0 vector-ALU products on 64 x 64 tiles; matrix-core products on
-// 1 64 x 64 tiles while n (N/64)^2 >= 512 (two workgroups per CU), else
+// over the poles of the list (poles with a nonzero flag skip themselves): left
+// Out = Mat In, or right Out = In Mat^T; epilogue 0 none, 1 (right) divide entry
+// (p, q) by lam_p + lam_q - b_k, 2 (right) scale by the pole's sigma_m; divided
+// (left): that divide applied to the operand as it is loaded.
+// variant: 0 vector-ALU products on 64 x 64 tiles (whole planes only); matrix-core
+// products on 1 64 x 64 tiles while they give every CU two workgroups, else
 // 32 x 32, 2 always 32 x 32 (four times the workgroups), 3 always 64 x 64.
+// split: the planes are folded into parity quadrants (launch_pml_fold), mat and
+// lam hold the even, then the odd block, (N/2)^2 and N/2 entries each.
 // Each component plane of a field is transformed on its own (the free-space
 // operator does not couple components).
-void launch_pml_gemm(int variant, bool left, int epilogue, const c128* mat, PmlRef in, PmlRef out,
-                     const PoleState* st, const int* list, int n, int* active_out, const c128* lam, int N, int ncomp,
-                     hipStream_t s);
-
+//
 // A round whose poles all start from the step's shared first basis vector u_0
-// shares the first two products: T = Q^-1 u_0 Q^-T once (one-entry pole list
-// with the state k_pml_shared_setup writes: m = 0, b = 0, sigma_0 = 1, tbl[0] =
-// u0), then per pole Q [T / (lam_p + lam_q - b_k)] with the divide applied as
-// the operand is loaded (launch_pml_gemm_divided, matrix cores; tiles as
-// variant 1), then the last stage as usual.
-void launch_pml_shared_setup(PoleState* st, c128** tbl, const c128* u0, hipStream_t s);
-void launch_pml_gemm_divided(const c128* mat, PmlRef in, PmlRef out, const PoleState* st, const int* list, int n,
-                             int* active_out, const c128* lam, int N, int ncomp, hipStream_t s);
+// shares the first two products: T = Q^-1 u_0 Q^-T once (one-entry list with the
+// state k_pml_shared_setup writes: flag 0, m = 0, sigma_0 = 1, shift b), then per
+// pole Q [T / (lam_p + lam_q - b_k)] by the divided left product, then the last
+// stage as usual.
+void launch_pml_gemm(int variant, bool split, bool left, int epilogue, bool divided, const c128* mat, PmlRef in,
+                     PmlRef out, const PoleState* st, const RoundList& list, const c128* lam, int N, int ncomp,
+                     hipStream_t s);
+void launch_pml_shared_setup(PoleState* st, c128 b, hipStream_t s);
+
+// The parity quadrants of the listed poles' planes (fold), and back.
+void launch_pml_fold(bool fold, PmlRef in, PmlRef out, const PoleState* st, const RoundList& list, int N, int ncomp,
+                     hipStream_t s);
 
 // p = (Zbar~ - b_k I) z_m - sigma_m u_m into P[k] (so that A_k z_m = ~v_m + p
 // for the z_m as stored) and the partial inner products <u_i, p>, <u_i, u_m>,
 // i = 0..m, in the layout the dot reduction reads (pml_apply_parts per product).
 // coef: the plan's coefficient planes (V; for ncomp = 2 also the psi planes).
 int pml_apply_parts(int N);
-void launch_pml_apply(const c128* zbase, size_t zsp, size_t zsi, c128* pbase, size_t psp, c128* const* uptr,
+void launch_pml_apply(const c128* zbase, size_t zsp, size_t zsi, c128* pbase, size_t psp, const Basis<c128>& basis,
                       const double* coef, const c128* a2, const c128* a1, const StencilCoef& sc, const PoleState* st,
-                      const int* active, int nactive, double2* part, int N, int ncomp, hipStream_t s);
+                      const RoundList& list, double2* part, int N, int ncomp, hipStream_t s);
 
 // y = rhs - (Zbar~ - b I) x (rhs NULL: y = (Zbar~ - b I) x) with the stretched
 // stencils, for n fields (field z at x + z xbs, y + z ybs, shift shifts[z], host

@@ -205,6 +205,62 @@ def test_pml_mode_switches():
     assert np.isfinite(out.cpu().numpy()).all()
 
 
+@pytest.mark.parametrize("N", [64, 128, 192])
+@pytest.mark.parametrize("ncomp", [1, 2])
+def test_parity_halves_equal_whole_planes(N, ncomp):
+    """The preconditioner on the even and odd halves (matrix-core variants, both tiles) against the
+    whole planes (variant 0), each within this file's 20 eps n cond(Q)^2 of the exact one; at larger
+    sizes that bound says nothing of a rough field (cond(Q) is 4e8 at 384), and the solves'
+    true residuals decide."""
+    torch = _cuda()
+    from paper_2410_17446_amd import hp
+    W, sig = N // 8, 10.0
+    wl = workload(N=N, ncomp=1, W=W, npoles=8)
+    f = wl["fit"]
+    plan = hp.Plan(nx=N, ny=N, dx=0.25, dy=0.25, k0=K0, n0=1.0, dz=1.0, ncomp=ncomp, poles=f["poles"],
+                   residues=f["residues"], r_inf=f["r_inf"], d2=wl["c"], d1=wl["d"], edge_width=W, edge_eta=0.25,
+                   tol=1e-10, restart=2, max_cycles=20, precision=0)
+    Q, Qi, lam = tables.pml_eigen(N, 0.25, K0, 1.0, W, sig, wl["c"], wl["d"])
+    plan.set_pml(sig, Q, Qi, lam)
+    rng = np.random.default_rng(5)
+    x = to_gpu(rng.standard_normal((ncomp, N, N)) + 1j * rng.standard_normal((ncomp, N, N)))
+    k = 3
+    bound = 40 * 2.2e-16 * N * np.linalg.cond(Q) ** 2
+    assert bound < 0.1
+    ys = []
+    for variant in (0, 1, 2, 3):
+        plan.set_launch(variant)
+        y = torch.zeros_like(x)
+        plan.apply_preconditioner(k, x, y)
+        ys.append(y.cpu().numpy())
+    for y in ys[1:]:
+        assert rel_l2(y, ys[0]) < bound
+        assert not y[:, 0, :].any() and not y[:, :, 0].any()
+
+
+def test_eigenvectors_in_any_order_and_scale():
+    """Any order and scaling of the eigenvectors is taken; with two columns of unequal eigenvalue
+    mixed the tables no longer decompose the operator and are refused as before."""
+    torch = _cuda()
+    from paper_2410_17446_amd import hp
+    wl, g = _setup()
+    plan, _ = _plan(wl, g)
+    rng = np.random.default_rng(6)
+    x = to_gpu(rng.standard_normal((1, 64, 64)) + 1j * rng.standard_normal((1, 64, 64)))
+    y0, y1 = torch.zeros_like(x), torch.zeros_like(x)
+    plan.apply_preconditioner(3, x, y0)
+    Q, Qi, lam = tables.pml_eigen(g.N, g.h, g.k0, g.n0, g.W, g.sigma_max, wl["c"], wl["d"])
+    perm = rng.permutation(63)
+    scale = np.exp(2j * np.pi * rng.random(63)) * 10.0 ** rng.uniform(-2, 2, 63)
+    plan.set_pml(g.sigma_max, Q[:, perm] * scale, Qi[perm] / scale[:, None], lam[perm])
+    plan.apply_preconditioner(3, x, y1)
+    assert rel_l2(y1.cpu().numpy(), y0.cpu().numpy()) < 40 * 2.2e-16 * 64 * np.linalg.cond(Q) ** 2
+    bad = Q.copy()
+    bad[:, 0] += bad[:, 1]
+    with pytest.raises(hp.HPError):
+        plan.set_pml(g.sigma_max, bad, np.linalg.inv(bad), lam)
+
+
 def test_removed_layers_leave_no_trace():
     """A step after the layers are removed equals a fresh plan's bit for bit (the layers' fields are
     physical, the plain path's transformed, in the same memory)."""
