@@ -383,9 +383,11 @@ __device__ __forceinline__ cx<C> row_d1x(const cx<C>* b, int j, const StencilCoe
 // Inner products a row workgroup collects in LDS between two barriers.
 constexpr int DOT_B = 16;
 
-// Threads of a row workgroup: 256, but 64 for n <= 128, where a field has too few
-// rows to give every CU a 256-thread workgroup.
-constexpr int apply_threads(int n) { return n <= 128 ? 64 : 256; }
+// Threads of a row workgroup: 256, but 64 (one wave, no waits between waves) for
+// n <= 384, where one pole's rows in workgroups of 256 reach a third of the CUs (77 of
+// them at 384).  At 512 and above the smaller workgroup lost 2-4 % (1024^2 16
+// poles 6.41 -> 6.70 ms).
+constexpr int apply_threads(int n) { return n <= 384 ? 64 : 256; }
 
 template <int N, int NC>
 struct ApplyCfg {
@@ -407,7 +409,7 @@ struct ApplyCfg {
 template <typename C, int N, int NC>
 struct ApplyWaves {
   static constexpr bool POW2 = (N & (N - 1)) == 0;
-  static constexpr int V = N <= 256 ? 2
+  static constexpr int V = N <= 384 ? 2
                            : NC == 2 ? 4
                                      : ((N <= 1024 && POW2) ? 4 : (sizeof(C) == 4 || N < 2048 ? 3 : 2));
 };
@@ -570,45 +572,39 @@ __global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) v
   }
   // <u_i, p> and <u_i, u_m>, i = 0..m: the new direction's projections and
   // the reorthogonalisation of the provisional u_m, from the same reads of the
-  // basis.  Up to 256 the next vector's loads are in flight while the current one's
-  // products are reduced (above, the other waves of the CU hide them); the waves'
-  // sums meet in LDS once per DOT_B vectors, so a workgroup leaves one partial sum
-  // per product.
-  constexpr bool AHEAD = N <= 256;
-  cx<T> um[PT], un[PT];
+  // basis.  The loads are unconditional (a row beyond the field reads row 0, and its p
+  // and u_m are zero; a vector beyond u_m reads u_m), so nothing waits for them
+  // before their products; up to 384, where a pole alone leaves the SIMDs one wave
+  // each, the next vector's are in flight during the current one's (one 384^2 pole,
+  // average over the cycle: 26.6 -> 18.7 us with the smaller workgroups).  The waves' sums
+  // meet in LDS once per DOT_B vectors, so a workgroup leaves one partial sum per
+  // product.
+  constexpr bool AHEAD = N <= 384;
   auto load_u = [&](int i, cx<T>* v) {
-    const cx<T>* __restrict__ u = basis.at(e, i);
+    const cx<T>* __restrict__ u = basis.at(e, min(i, m));
 #pragma unroll
-    for (int s = 0; s < PT; ++s) v[s] = valid ? u[toff.at(s)] : czero<T>();
+    for (int s = 0; s < PT; ++s) v[s] = u[toff.at(s)];
   };
+  cx<T> um[PT], ua[PT], ub[AHEAD ? PT : 1];
   load_u(m, um);
-  if (AHEAD && m > 0) load_u(0, un);
+  if (AHEAD) load_u(0, ua);
+#pragma unroll
+  for (int s = 0; s < PT; ++s) um[s] = valid ? um[s] : czero<T>();
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double* out = reinterpret_cast<double*>(part) + ((size_t)k * (HP_MAXM + 1) * 2 * nrb + rb) * 2;
   for (int i0 = 0; i0 <= m; i0 += DOT_B) {
     const int ie = min(m + 1, i0 + DOT_B);
-    for (int i = i0; i < ie; ++i) {
+    auto products = [&](int i, const cx<T>* uc) {
       double pr = 0.0, pi = 0.0, qr = 0.0, qi = 0.0;
-      cx<T> uc[PT];
-      if (i == m) {
-#pragma unroll
-        for (int s = 0; s < PT; ++s) uc[s] = um[s];
-      } else if constexpr (AHEAD) {
-#pragma unroll
-        for (int s = 0; s < PT; ++s) uc[s] = un[s];
-        if (i + 1 < m) load_u(i + 1, un);
-      } else {
-        load_u(i, uc);
-      }
 #pragma unroll
       for (int s = 0; s < PT; ++s) {
         const cx<double> a = cvt<double>(uc[s]);
         const cx<double> bp = cvt<double>(NC == 1 ? pv[s] : pval(s));
         const cx<double> bq = cvt<double>(um[s]);
-        pr += a.re * bp.re + a.im * bp.im;
-        pi += a.re * bp.im - a.im * bp.re;
-        qr += a.re * bq.re + a.im * bq.im;
-        qi += a.re * bq.im - a.im * bq.re;
+        pr = fma(a.re, bp.re, fma(a.im, bp.im, pr));
+        pi = fma(a.re, bp.im, fma(-a.im, bp.re, pi));
+        qr = fma(a.re, bq.re, fma(a.im, bq.im, qr));
+        qi = fma(a.re, bq.im, fma(-a.im, bq.re, qi));
       }
       const double r = wave_sum4(pr, pi, qr, qi);
       if (lane < 4) {
@@ -616,6 +612,19 @@ __global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) v
           out[((size_t)(2 * i + (lane >> 1)) * nrb) * 2 + (lane & 1)] = r;
         else
           dsum[i - i0][wave][lane] = r;
+      }
+    };
+    if constexpr (AHEAD) {
+      for (int i = i0; i < ie; i += 2) {
+        load_u(i + 1, ub);
+        products(i, ua);
+        load_u(i + 2, ua);
+        if (i + 1 < ie) products(i + 1, ub);
+      }
+    } else {
+      for (int i = i0; i < ie; ++i) {
+        load_u(i, ua);
+        products(i, ua);
       }
     }
     if constexpr (AC::WAVES > 1) {
@@ -1571,11 +1580,11 @@ void launch_reduce_dots(const double2* part, int nparts, PoleState* st, const Ro
   hipLaunchKernelGGL(k_reduce_dots, dim3(list.n), dim3(RED_WG), 0, s, part, nparts, st, list);
 }
 
-// Elements per thread of the update: one for fields of up to 2^16 elements, whose
+// Elements per thread of the update: one for fields of up to 384^2 elements, whose
 // workgroups of four elements a thread would leave CUs without work (64 of them at
-// 256^2), else four.  The rule looks at the field alone, so a pole's sums are
+// 256^2, 144 at 384^2: 12.0 us against 10.5), else four.  The rule looks at the field alone, so a pole's sums are
 // the same whatever the other poles do.
-static int update_elems(size_t total) { return total <= 65536 ? 1 : 4; }
+static int update_elems(size_t total) { return total <= 384 * 384 ? 1 : 4; }
 
 int update_blocks(size_t total) {
   const size_t chunk = (size_t)UPD_WG * update_elems(total);
