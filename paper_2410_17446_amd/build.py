@@ -15,7 +15,9 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OUT = os.path.join(PKG, "libhp.so")
 BUILD = os.path.join(ROOT, "_build")
-SOURCES = ["kernels.hip", "hp_api.hip", "unet.hip", "pml.hip", "fit.hip"]
+# (source, part): kernels.hip is compiled in parts, one precision of its transforms each
+SOURCES = [("kernels.hip", 1), ("kernels.hip", 2), ("kernels.hip", 3), ("kernels.hip", 0), ("hp_api.hip", None),
+           ("unet.hip", None), ("pml.hip", None), ("fit.hip", None)]
 ARCH = os.environ.get("HP_OFFLOAD_ARCH", "gfx950")
 
 
@@ -33,9 +35,11 @@ def flags() -> list[str]:
             "-I", os.path.join(ROOT, "include")]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc(), *flags(), "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(item: tuple) -> str:
+    src, part = item
+    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ("" if part is None else f"_{part}") + ".o")
+    define = [] if part is None else [f"-DHP_PART={part}"]
+    cmd = [hipcc(), *flags(), *define, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")

@@ -1576,23 +1576,11 @@ void launch_row_apply(const cx<T>* zbase, size_t zsp, size_t zsi, const cx<T>* d
 #undef L_
 }
 
-void launch_reduce_dots(const double2* part, int nparts, PoleState* st, const RoundList& list, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_dots, dim3(list.n), dim3(RED_WG), 0, s, part, nparts, st, list);
-}
-
 // Elements per thread of the update: one for fields of up to 384^2 elements, whose
 // workgroups of four elements a thread would leave CUs without work (64 of them at
 // 256^2, 144 at 384^2: 12.0 us against 10.5), else four.  The rule looks at the field alone, so a pole's sums are
 // the same whatever the other poles do.
 static int update_elems(size_t total) { return total <= 384 * 384 ? 1 : 4; }
-
-int update_blocks(size_t total) {
-  const size_t chunk = (size_t)UPD_WG * update_elems(total);
-  size_t b = (total + chunk - 1) / chunk;
-  if (b > 2048) b = 2048;
-  if (b < 1) b = 1;
-  return (int)b;
-}
 
 template <typename T>
 void launch_update(const cx<T>* pbase, size_t psp, const Basis<cx<T>>& basis, const PoleState* st,
@@ -1604,20 +1592,6 @@ void launch_update(const cx<T>* pbase, size_t psp, const Basis<cx<T>>& basis, co
   else
     hipLaunchKernelGGL((k_update<T, 4>), dim3(nblk, list.n), dim3(UPD_WG), 0, s, pbase, psp, basis, st, list, part,
                        nblk, total);
-}
-
-void launch_arnoldi(PoleState* st, const RoundList& list, const double* part, int nblk, int restart,
-                    unsigned long long* ftag, unsigned long long seq, double* est, hipStream_t s) {
-  hipLaunchKernelGGL(k_arnoldi, dim3(list.n), dim3(ARN_WG), 0, s, st, list, part, nblk, restart, ftag, seq, est);
-}
-
-void launch_cycle_init(PoleState* st, const int* poles, int npoles_in, const double* part, int nblk, int first,
-                       double tol, double rtol_cycle, hipStream_t s, size_t part_bs, int set_has_x) {
-  PoleList sel;
-  sel.n = npoles_in;
-  for (int a = 0; a < HP_MAXPOLES; ++a) sel.k[a] = a < npoles_in ? poles[a] : 0;
-  hipLaunchKernelGGL(k_cycle_init, dim3(npoles_in), dim3(64), 0, s, st, sel, part, nblk, first, tol, rtol_cycle,
-                     part_bs, set_has_x);
 }
 
 template <typename T>
@@ -1648,6 +1622,75 @@ void launch_accum(c128* xacc, const cx<T>* z, size_t zsi, const PoleState* st, i
                   hipStream_t s) {
   // xacc and z are pole k's already: a one-entry list with zero strides
   launch_accum_batch<T>(xacc, 0, z, 0, zsi, st, &pole, 1, g, s);
+}
+
+// explicit instantiations
+#define HP_INST(T)                                                                                                   \
+  template int row_blocks<T>(int);                                                                                   \
+  template int row_apply_blocks<T>(const Geo&);                                                                      \
+  template void launch_update<T>(const cx<T>*, size_t, const Basis<cx<T>>&, const PoleState*, const RoundList&,      \
+                                 double*, int, const Geo&, hipStream_t);                                             \
+  template void launch_final<T>(const c128*, c128*, const cx<T>*, size_t, size_t, const c128*, size_t,               \
+                                const PoleState*, int, c128, c128, double, double, int, const c128*, const Geo&,     \
+                                hipStream_t);                                                                        \
+  template void launch_accum<T>(c128*, const cx<T>*, size_t, const PoleState*, int, const Geo&, hipStream_t);      \
+  template void launch_accum_batch<T>(c128*, size_t, const cx<T>*, size_t, size_t, const PoleState*, const int*,     \
+                                      int, const Geo&, hipStream_t);
+
+// storage type T, compute type C of the transforms
+#define HP_INST2(T, C)                                                                                               \
+  template void launch_row_fwd<T, C>(const c128*, cx<T>*, double*, const cx<C>*, const Geo&, hipStream_t, int);      \
+  template void launch_row_inv<T, C>(const cx<T>*, c128*, const cx<C>*, const Geo&, int, hipStream_t);               \
+  template void launch_row_fwd_batch<T, C>(const c128*, size_t, const int*, cx<T>*, size_t, const int*, int,       \
+                                           double*, size_t, const cx<C>*, const Geo&, hipStream_t, int);             \
+  template void launch_row_inv_batch<T, C>(const cx<T>*, size_t, const int*, int, c128*, size_t, const cx<C>*,       \
+                                           const Geo&, int, hipStream_t);                                            \
+  template void launch_col<T, C>(const Basis<cx<T>>&, cx<T>*, size_t, size_t, cx<T>*, size_t, const PoleState*,      \
+                                 const RoundList&, const double*, const double*, const cx<C>*, const Geo&,           \
+                                 const StencilCoef&, hipStream_t);                                                   \
+  template void launch_row_apply<T, C>(const cx<T>*, size_t, size_t, const cx<T>*, size_t, cx<T>*, size_t,           \
+                                       const Basis<cx<T>>&, const C*, const PoleState*, const RoundList&, double2*,  \
+                                       const cx<C>*, const Geo&, const StencilCoef&, hipStream_t);
+
+// The build compiles this file once per part (a third of the time of one
+// compilation); without HP_PART it is whole.
+#if !defined(HP_PART) || HP_PART == 1
+HP_INST2(double, double)
+#endif
+#if !defined(HP_PART) || HP_PART == 2
+HP_INST2(float, float)
+#endif
+#if !defined(HP_PART) || HP_PART == 3
+HP_INST2(float, double)
+#endif
+#if !defined(HP_PART) || HP_PART == 0
+HP_INST(double)
+HP_INST(float)
+
+void launch_reduce_dots(const double2* part, int nparts, PoleState* st, const RoundList& list, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_dots, dim3(list.n), dim3(RED_WG), 0, s, part, nparts, st, list);
+}
+
+int update_blocks(size_t total) {
+  const size_t chunk = (size_t)UPD_WG * update_elems(total);
+  size_t b = (total + chunk - 1) / chunk;
+  if (b > 2048) b = 2048;
+  if (b < 1) b = 1;
+  return (int)b;
+}
+
+void launch_arnoldi(PoleState* st, const RoundList& list, const double* part, int nblk, int restart,
+                    unsigned long long* ftag, unsigned long long seq, double* est, hipStream_t s) {
+  hipLaunchKernelGGL(k_arnoldi, dim3(list.n), dim3(ARN_WG), 0, s, st, list, part, nblk, restart, ftag, seq, est);
+}
+
+void launch_cycle_init(PoleState* st, const int* poles, int npoles_in, const double* part, int nblk, int first,
+                       double tol, double rtol_cycle, hipStream_t s, size_t part_bs, int set_has_x) {
+  PoleList sel;
+  sel.n = npoles_in;
+  for (int a = 0; a < HP_MAXPOLES; ++a) sel.k[a] = a < npoles_in ? poles[a] : 0;
+  hipLaunchKernelGGL(k_cycle_init, dim3(npoles_in), dim3(64), 0, s, st, sel, part, nblk, first, tol, rtol_cycle,
+                     part_bs, set_has_x);
 }
 
 int op_blocks(const Geo& g) { return ((g.nx + OP_TX - 1) / OP_TX) * ((g.ny + OP_TY - 1) / OP_TY); }
@@ -1703,7 +1746,6 @@ void launch_to_float(const double* a, float* b, size_t n, hipStream_t s) {
   hipLaunchKernelGGL(k_to_float, dim3(2048), dim3(256), 0, s, a, b, n);
 }
 
-
 void launch_state_init(PoleState* st, const StateInit& h, int npoles, hipStream_t s) {
   hipLaunchKernelGGL(k_state_init, dim3(npoles), dim3(256), 0, s, st, h);
 }
@@ -1728,36 +1770,4 @@ void launch_rk4_stage(const c128* L, const c128* acc_in, c128* acc_out, const c1
                      g.nx, g.ny, (unsigned)g.fsz, total);
 }
 
-// explicit instantiations
-#define HP_INST(T)                                                                                                   \
-  template int row_blocks<T>(int);                                                                                   \
-  template int row_apply_blocks<T>(const Geo&);                                                                      \
-  template void launch_update<T>(const cx<T>*, size_t, const Basis<cx<T>>&, const PoleState*, const RoundList&,      \
-                                 double*, int, const Geo&, hipStream_t);                                             \
-  template void launch_final<T>(const c128*, c128*, const cx<T>*, size_t, size_t, const c128*, size_t,               \
-                                const PoleState*, int, c128, c128, double, double, int, const c128*, const Geo&,     \
-                                hipStream_t);                                                                        \
-  template void launch_accum<T>(c128*, const cx<T>*, size_t, const PoleState*, int, const Geo&, hipStream_t);      \
-  template void launch_accum_batch<T>(c128*, size_t, const cx<T>*, size_t, size_t, const PoleState*, const int*,     \
-                                      int, const Geo&, hipStream_t);
-
-// storage type T, compute type C of the transforms
-#define HP_INST2(T, C)                                                                                               \
-  template void launch_row_fwd<T, C>(const c128*, cx<T>*, double*, const cx<C>*, const Geo&, hipStream_t, int);      \
-  template void launch_row_inv<T, C>(const cx<T>*, c128*, const cx<C>*, const Geo&, int, hipStream_t);               \
-  template void launch_row_fwd_batch<T, C>(const c128*, size_t, const int*, cx<T>*, size_t, const int*, int,       \
-                                           double*, size_t, const cx<C>*, const Geo&, hipStream_t, int);             \
-  template void launch_row_inv_batch<T, C>(const cx<T>*, size_t, const int*, int, c128*, size_t, const cx<C>*,       \
-                                           const Geo&, int, hipStream_t);                                            \
-  template void launch_col<T, C>(const Basis<cx<T>>&, cx<T>*, size_t, size_t, cx<T>*, size_t, const PoleState*,      \
-                                 const RoundList&, const double*, const double*, const cx<C>*, const Geo&,           \
-                                 const StencilCoef&, hipStream_t);                                                   \
-  template void launch_row_apply<T, C>(const cx<T>*, size_t, size_t, const cx<T>*, size_t, cx<T>*, size_t,           \
-                                       const Basis<cx<T>>&, const C*, const PoleState*, const RoundList&, double2*,  \
-                                       const cx<C>*, const Geo&, const StencilCoef&, hipStream_t);
-
-HP_INST(double)
-HP_INST(float)
-HP_INST2(double, double)
-HP_INST2(float, float)
-HP_INST2(float, double)
+#endif  // part 0
