@@ -45,6 +45,10 @@ __host__ __device__ __forceinline__ cx<T> cdiv(cx<T> a, cx<T> b) {
   T d = b.re * b.re + b.im * b.im;
   return mk((a.re * b.re + a.im * b.im) / d, (a.im * b.re - a.re * b.im) / d);
 }
+// a * b + c in four multiply-adds
+__host__ __device__ __forceinline__ cx<double> cfma(cx<double> a, cx<double> b, cx<double> c) {
+  return mk(fma(a.re, b.re, fma(-a.im, b.im, c.re)), fma(a.re, b.im, fma(a.im, b.re, c.im)));
+}
 template <typename Tout, typename Tin>
 __host__ __device__ __forceinline__ cx<Tout> cvt(cx<Tin> a) {
   return mk((Tout)a.re, (Tout)a.im);

@@ -719,7 +719,7 @@ int run_poles(hp_plan p, const c128* w, const std::vector<int>& subset, bool* no
       ++nw;
       col += 1.0 + outs;                                         // u_m read, z (+ D1y z) written
       row += (d.ncomp == 2 && !p->pml ? 3.0 : 2.0) + (mm + 1.0);  // z (+ D1y z), p, u_0..u_m
-      upd += 1.0 + (mm + 1.0) + 1.0 + (mm > 0 ? 1.0 : 0.0);     // p, u_0..u_m, u_{m+1}, rewritten u_m
+      upd += 1.0 + (mm + 1.0) + 1.0;                             // p, u_0..u_m, u_{m+1}
       if (f.sh[a]) {
         ++shared;
         if (mm == 0) ++shared_m0;

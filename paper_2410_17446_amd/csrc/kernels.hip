@@ -644,44 +644,36 @@ __global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) v
 
 constexpr int UPD_WG = 256;
 
-// u_{m+1} = cu_{m+1} p + sum_{i<=m} cu_i u_i, and (delayed reorthogonalisation)
-// u_m <- sum_{i<=m} cv_i u_i in place; partial |u_{m+1}|^2.  E elements per thread,
-// UPD_WG apart, and two basis vectors at a time, so that their loads are in flight
-// together.
+// u_{m+1} = cu_{m+1} p + sum_{i<=m} cu_i u_i and partial |u_{m+1}|^2.  Bound by
+// the copy rate (m + 3 fields; the stored vectors stay as they are, their
+// reorthogonalisation is in the coefficients).  E elements per thread, UPD_WG apart,
+// and two basis vectors at a time, so that their loads are in flight together.
 template <typename T, int E>
 __global__ __launch_bounds__(UPD_WG) void k_update(const cx<T>* __restrict__ pbase, size_t psp,
                                                    const Basis<cx<T>> basis, const PoleState* __restrict__ st,
                                                    const RoundList list, double* __restrict__ part, int nblk,
                                                    size_t total) {
   __shared__ c128 cf[HP_MAXM + 2];
-  __shared__ c128 cv[HP_MAXM + 1];
   __shared__ double red[UPD_WG / 64];
   const int en = list.e[blockIdx.y], k = round_pole(en), m = round_m(en);
   if (st[k].flag) return;
-  const int corr = m > 0;
   if ((int)threadIdx.x <= m + 1) cf[threadIdx.x] = st[k].cu[threadIdx.x];
-  if ((int)threadIdx.x <= m) cv[threadIdx.x] = st[k].cv[threadIdx.x];
   __syncthreads();
   const cx<T>* p = pbase + k * psp;
   cx<T>* out = basis.at(en, m + 1);
-  cx<T>* um = basis.at(en, m);
   double nrm = 0.0;
   const size_t chunk = (size_t)UPD_WG * E;
   for (size_t base = (size_t)blockIdx.x * chunk + threadIdx.x; base < total; base += (size_t)gridDim.x * chunk) {
-    cx<double> v[E], c[E];
+    cx<double> v[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const size_t idx = base + (size_t)e * UPD_WG;
       v[e] = (idx < total) ? cf[m + 1] * cvt<double>(p[idx]) : mk(0.0, 0.0);
-      c[e] = mk(0.0, 0.0);
     }
     auto add = [&](int i, const cx<T>* a) {
-      const c128 fi = cf[i], gi = cv[i];
+      const c128 fi = cf[i];
 #pragma unroll
-      for (int e = 0; e < E; ++e) {
-        v[e] = v[e] + fi * cvt<double>(a[e]);
-        c[e] = c[e] + gi * cvt<double>(a[e]);
-      }
+      for (int e = 0; e < E; ++e) v[e] = cfma(fi, cvt<double>(a[e]), v[e]);
     };
     auto load = [&](int i, cx<T>* a) {
       const cx<T>* ui = basis.at(en, i);
@@ -710,7 +702,6 @@ __global__ __launch_bounds__(UPD_WG) void k_update(const cx<T>* __restrict__ pba
       if (idx >= total) continue;
       const cx<T> r = cvt<T>(v[e]);
       out[idx] = r;
-      if (corr) um[idx] = cvt<T>(c[e]);
       nrm += abs2(cvt<double>(r));
     }
   }
@@ -720,6 +711,9 @@ __global__ __launch_bounds__(UPD_WG) void k_update(const cx<T>* __restrict__ pba
 
 // ------------------------------------------------------------------ reductions / small FP64 kernels
 
+// Upper triangle of an n x n matrix packed by columns: (r, c), r <= c.
+__device__ __forceinline__ int pk(int r, int c) { return c * (c + 1) / 2 + r; }
+
 // v of lane l of the wave (l uniform)
 __device__ __forceinline__ double lane_get(double v, int l) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
@@ -728,9 +722,14 @@ __device__ __forceinline__ double lane_get(double v, int l) {
 __device__ __forceinline__ c128 lane_get(c128 v, int l) { return mk(lane_get(v.re, l), lane_get(v.im, l)); }
 
 // Sum the partial inner products of one pole, then the delayed
-// reorthogonalisation algebra of its step m in FP64:
+// reorthogonalisation algebra of its step m in FP64.  The stored vectors are the
+// provisional ones and are never rewritten: with ~v_l the stored vector l scaled to
+// diagonal 1 (sigma_l u_l), ~v_l = v_l + sum_{i<l} R_il v_i, so <v, x> = R^-H <~v, x>
+// and sum_l c_l v_l = ~V R^-1 c; R^-1 grows by the column -R^-1 r_m per step, so both
+// are matrix-vector products.  (Rewriting u_m in place cost the update a write of a
+// field in every step: 1024^2 16 poles 6.45 -> 6.11 ms, 2048^2 vector 14.2 -> 13.5.)
 //   s_i = <v_i, ~v_m>, t = <~v_m, ~v_m>, rho^2 = t - sum |s_i|^2,
-//   v_m = (~v_m - sum s_i v_i) / rho,
+//   v_m = (~v_m - sum s_i v_i) / rho,  R_im = s_i / rho,
 //   column m-1:  H[i][m-1] += h~ s_i,  H[m][m-1] = h~ rho  (h~ = old H[m][m-1]),
 //   c_i = <v_i, p>, c_m = (<~v_m, p> - sum conj(s_i) c_i) / rho,
 //   A M^-1 v_m = (~v_m + p - sum_i s_i A M^-1 v_i) / rho   (A M^-1 ~v_m = ~v_m + p),
@@ -738,28 +737,42 @@ __device__ __forceinline__ c128 lane_get(c128 v, int l) { return mk(lane_get(v.r
 // expressed as coefficients of the stored vectors for the update kernel.
 //
 // One workgroup per pole (the row pass leaves one partial per workgroup, so a
-// wave sums a product of 1024^2 in eight loads a lane): wave w takes the products
-// i = w, w + 16, ..., then every wave holds s and c, lane i entry i, and the rows
-// l = w, w + 16, ... of the Hessenberg column are wave sums too, so the chain has
-// two barriers and no loop over the basis in one thread.  Latency-bound: 9.5 us
-// at 64^2 and 11.5 us at 1024^2 when 2 (m + 1) workgroups a pole met in an
-// atomic counter and one thread ran the sums.
+// wave sums a product of 1024^2 in eight loads a lane).  Wave w takes the products
+// i = w, w + 16, ..., and the same rows of each matrix-vector product as wave sums
+// (lane l entry l), so the chain has three barriers and no loop over the basis in one
+// thread (substitutions with R took 5 % of a 384^2 solve of 30-vector cycles).
+// Latency-bound: 9.5 us at 64^2 and 11.5 us at 1024^2 when 2 (m + 1) workgroups a pole
+// met in an atomic counter and one thread ran the sums, 4.3 and 5.9 us now.
 constexpr int RED_WG = 1024;
 __global__ __launch_bounds__(RED_WG) void k_reduce_dots(const double2* __restrict__ part, int nparts,
                                                         PoleState* __restrict__ st, const RoundList list) {
   constexpr int LD = HP_MAXM + 1, NW = RED_WG / 64;
   __shared__ c128 PQ[HP_MAXM + 1][2];
-  __shared__ c128 R[HP_MAXM + 1];
+  __shared__ c128 SC[HP_MAXM][2];
+  __shared__ c128 G[HP_MAXM + 1];
+  // H (entries 0..c+1 of column c) and the strict upper part of R^-1, packed by columns:
+  // columns come in whole lines, rows are read here (64 lines a row from memory)
+  __shared__ c128 Hs[HP_MAXM * (HP_MAXM + 3) / 2], Rs[HP_MAXM * (HP_MAXM - 1) / 2];
+  auto hx = [](int r, int c) { return c * (c + 3) / 2 + r; };
+  auto rx = [](int r, int c) { return c * (c - 1) / 2 + r; };
   const int e = list.e[blockIdx.x], k = round_pole(e), m = round_m(e);
   PoleState& S = st[k];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   // what the algebra needs of the state, in flight during the sums
   const double sig = lane <= m ? S.sigma[lane] : 0.0;
-  const c128* Hr = S.Hraw;
-  const c128 h0 = (lane < m && wave <= m) ? Hr[wave + lane * LD] : mk(0.0, 0.0);
+  const c128 *Hr = S.Hraw, *Ri = S.Ri;
+  const c128 zero = mk(0.0, 0.0);
+  auto h_at = [&](int l) { return (lane < m && l <= lane + 1) ? Hs[hx(l, lane)] : zero; };
+  auto ri_at = [&](int i) { return (lane > i && lane < m) ? Rs[rx(i, lane)] : lane == i ? mk(1.0, 0.0) : zero; };
+  auto rh_at = [&](int i) { return lane < i ? Rs[rx(lane, i)] : lane == i ? mk(1.0, 0.0) : zero; };
   const double hsub = m > 0 ? Hr[m + (m - 1) * LD].re : 0.0;
   const c128 g0 = S.g[0];
   if (S.flag) return;
+  // columns from the last wave down, products from the first up: a short cycle's waves have one each
+  for (int c = NW - 1 - wave; c < m; c += NW) {
+    if (lane <= c + 1) Hs[hx(lane, c)] = Hr[lane + c * LD];
+    if (lane < c) Rs[rx(lane, c)] = Ri[lane + c * LD];
+  }
   for (int i = wave; i <= m; i += NW) {
     const double2* src = part + (((size_t)k * LD + i) * 2) * nparts;
     double a[4][4] = {};
@@ -787,14 +800,20 @@ __global__ __launch_bounds__(RED_WG) void k_reduce_dots(const double2* __restric
     if (lane < 4) reinterpret_cast<double*>(&PQ[i][lane >> 1])[lane & 1] = r;
   }
   __syncthreads();
-  // lane i: s_i, c_i (i < m); every wave
   const double sm = lane_get(sig, m);
   const c128 Pm = PQ[m][0], Qm = PQ[m][1];
-  c128 sv = mk(0.0, 0.0), cc = mk(0.0, 0.0);
-  if (lane < m) {
-    sv = (sig * sm) * PQ[lane][1];
-    cc = sig * PQ[lane][0];
+  {
+    // s and c: R^-H of the products with the stored vectors
+    const c128 q = lane < m ? (sig * sm) * PQ[lane][1] : zero, p = lane < m ? sig * PQ[lane][0] : zero;
+    for (int i = wave; i < m; i += NW) {
+      const c128 r = rh_at(i), x = cmulc(r, q), y = cmulc(r, p);
+      const double t = wave_sum4(x.re, x.im, y.re, y.im);
+      if (lane < 4) reinterpret_cast<double*>(&SC[i][lane >> 1])[lane & 1] = t;
+    }
   }
+  __syncthreads();
+  // lane i: s_i, c_i (i < m); every wave
+  const c128 sv = lane < m ? SC[lane][0] : zero, cc = lane < m ? SC[lane][1] : zero;
   const c128 sc = cmulc(sv, cc);
   const double t = wave_sum4(abs2(sv), sc.re, sc.im, 0.0);
   double rho2 = sm * sm * Qm.re - lane_get(t, 0);
@@ -804,25 +823,34 @@ __global__ __launch_bounds__(RED_WG) void k_reduce_dots(const double2* __restric
   // column m: h_l = (<v_l, ~v_m> + <v_l, p> - A_l) / rho, A_l = sum_{i<m, i>=l-1} s_i H[l][i],
   // with column m-1 of H as corrected
   for (int l = wave; l <= m; l += NW) {
-    c128 hv = l == wave ? h0 : (lane < m ? Hr[l + lane * LD] : mk(0.0, 0.0));
+    c128 hv = h_at(l);
     const c128 sl = l < m ? lane_get(sv, l) : mk(rho, 0.0);
     if (lane == m - 1) hv = l < m ? hv + hsub * sl : mk(hsub * rho, 0.0);
-    const c128 a = (lane < m && lane >= l - 1) ? sv * hv : mk(0.0, 0.0);
+    const c128 a = (lane < m && lane >= l - 1) ? sv * hv : zero;
     const double r = wave_sum4(a.re, a.im, 0.0, 0.0);
     const c128 A = mk(lane_get(r, 0), lane_get(r, 1));
     const c128 h = irho * (sl + (l < m ? lane_get(cc, l) : cm) - A);
     if (lane == 0) {
       S.Hraw[l + m * LD] = h;
-      R[l] = irho * A + h;
+      G[l] = irho * A + h;
     }
   }
   __syncthreads();
+  const c128 gam = G[m];
+  // u_{m+1} = (1/rho) p + (1 - gam)/rho ~v_m + sum_{l<m} (gam s_l / rho - A_l / rho - h_l) v_l,
+  // the v_l's coefficients taken to the stored vectors by R^-1, and R^-1's column m
+  const c128 rm = irho * sv, d = lane < m ? gam * rm - G[lane] : zero;
+  for (int i = wave; i < m; i += NW) {
+    const c128 r = ri_at(i), x = r * d, y = r * rm;
+    const double w = wave_sum4(x.re, x.im, y.re, y.im);
+    const c128 ci = mk(lane_get(w, 0), lane_get(w, 1)), col = mk(lane_get(w, 2), lane_get(w, 3));
+    if (lane == i) {
+      S.cu[i] = sig * ci;
+      S.Ri[i + m * LD] = -col;
+    }
+  }
   if (wave != 0) return;
-  const c128 gam = R[m];
-  // u_{m+1} = (1/rho) p + (1 - gam)/rho ~v_m + sum_{l<m} (gam s_l / rho - A_l / rho - h_l) v_l
   if (lane < m) {
-    S.cu[lane] = sig * (irho * (gam * sv) - R[lane]);
-    S.cv[lane] = (-sig * irho) * sv;
     S.Rc[lane + m * LD] = sv;
     S.Hraw[lane + (m - 1) * LD] = Hr[lane + (m - 1) * LD] + hsub * sv;
   }
@@ -830,15 +858,11 @@ __global__ __launch_bounds__(RED_WG) void k_reduce_dots(const double2* __restric
     S.Rc[m + m * LD] = mk(rho, 0.0);
     S.cu[m] = (sm * irho) * (mk(1.0, 0.0) - gam);
     S.cu[m + 1] = mk(irho, 0.0);
-    if (m == 0) {
-      // v_0 = ~v_0 / rho rescales the (possibly shared) stored vector
+    S.sigma[m] = sm * irho;  // ~v_m with diagonal 1
+    if (m == 0)
       S.g[0] = rho * g0;
-      S.sigma[0] = sm * irho;
-    } else {
+    else
       S.Hraw[m + (m - 1) * LD] = mk(hsub * rho, 0.0);
-      S.cv[m] = mk(sm * irho, 0.0);
-      S.sigma[m] = 1.0;
-    }
   }
 }
 
@@ -857,9 +881,6 @@ __device__ __forceinline__ void givens(c128 a, double b, double& c, c128& sn, c1
   }
   r = c * a + b * sn;
 }
-
-// Upper triangle of an n x n matrix packed by columns: (r, c), r <= c.
-__device__ __forceinline__ int pk(int r, int c) { return c * (c + 1) / 2 + r; }
 
 // Back substitution R x = rhs (R packed upper triangular, n <= 64) by the first
 // wave of the block: lane l keeps rhs[l] in a register and x[i] reaches it by a
@@ -1128,7 +1149,7 @@ __global__ __launch_bounds__(RowCfg<N>::WG) void k_final(const c128* __restrict_
       if (next == 0) {
         const c128* xk = xacc + k * xsp;
 #pragma unroll
-        for (int s = 0; s < PT; ++s) acc[s] = acc[s] + ak * xk[toff.at(s)];
+        for (int s = 0; s < PT; ++s) acc[s] = cfma(ak, xk[toff.at(s)], acc[s]);
         next += RPW;
       }
     }
@@ -1138,7 +1159,7 @@ __global__ __launch_bounds__(RowCfg<N>::WG) void k_final(const c128* __restrict_
       const c128 cf = ak * st[k].y[i];
       const cx<T>* zi = zk + i * zsi;
 #pragma unroll
-      for (int s = 0; s < PT; ++s) acc[s] = acc[s] + cf * cvt<double>(zi[toff.at(s)]);
+      for (int s = 0; s < PT; ++s) acc[s] = cfma(cf, cvt<double>(zi[toff.at(s)]), acc[s]);
     }
     next -= nt;
   }
@@ -1182,7 +1203,7 @@ __global__ __launch_bounds__(256) void k_accum(c128* __restrict__ xacc, const cx
   const int hx = st[pole].has_x;
   for (size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (size_t)gridDim.x * 256) {
     c128 acc = hx ? xacc[idx] : mk(0.0, 0.0);
-    for (int i = 0; i < m; ++i) acc = acc + st[pole].y[i] * cvt<double>(z[i * zsi + idx]);
+    for (int i = 0; i < m; ++i) acc = cfma(st[pole].y[i], cvt<double>(z[i * zsi + idx]), acc);
     xacc[idx] = acc;
   }
 }

@@ -73,7 +73,7 @@ constexpr int tile_width() {
 // update coefficients, one workgroup per pole.
 void launch_reduce_dots(const double2* part, int nparts, PoleState* st, const RoundList& list, hipStream_t s);
 
-// u_{m+1} = p - sum_i hc_i v_i and partial |u_{m+1}|^2; rewrites u_m (m > 0).
+// u_{m+1} = sum of the step's update coefficients and partial |u_{m+1}|^2.
 template <typename T>
 void launch_update(const cx<T>* pbase, size_t psp, const Basis<cx<T>>& basis, const PoleState* st,
                    const RoundList& list, double* part, int nblk, const Geo& g, hipStream_t s);

@@ -34,12 +34,12 @@ struct PoleHead {
   c128 ak;        // residue
 };
 struct PoleState : PoleHead {
-  double sigma[HP_MAXM + 1];          // scale of the stored vector: v_i = sigma_i u_i
-  c128 cu[HP_MAXM + 2];               // update coefficients: u_i (i < m), ~v_m at m, p at m+1
-  c128 cv[HP_MAXM + 1];               // correction of ~v_m: v_m = sum_i cv_i u_i (i <= m)
+  double sigma[HP_MAXM + 1];          // scale of the stored vector: sigma_i u_i = v_i + (terms in v_l, l < i)
+  c128 cu[HP_MAXM + 2];               // update coefficients: u_i (i <= m), p at m+1
   c128 H[(HP_MAXM + 1) * HP_MAXM];    // rotated Hessenberg (R factor), column-major (i + col * (MAXM+1))
   c128 Hraw[(HP_MAXM + 1) * HP_MAXM]; // unrotated Hessenberg
   c128 Rc[(HP_MAXM + 1) * HP_MAXM];   // ~v_l = Rc[l][l] v_l + sum_{i<l} Rc[i][l] v_i
+  c128 Ri[(HP_MAXM + 1) * HP_MAXM];   // inverse of Rc with its columns scaled to diagonal 1 (strict upper part)
   double cs[HP_MAXM];                 // Givens cosines
   c128 sn[HP_MAXM];                   // Givens sines
   c128 g[HP_MAXM + 1];                // rotated beta e1
