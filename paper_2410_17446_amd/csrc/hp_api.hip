@@ -812,7 +812,8 @@ int run_poles(hp_plan p, const c128* w, const std::vector<int>& subset, bool* no
         // every kernel of the round takes the list in its arguments (no
         // host-to-device copy per round)
         Prof pr(p, HP_K_COL, -1.0, &fl.pslot[0]);
-        launch_col<T, C>(basis, Zb, zsp, zsi, DZb, dzsp, p->st, rl, p->mu_x, p->mu_y, twy, p->geo, p->sc, p->stream);
+        launch_col<T, C>(basis, Zb, zsp, zsi, DZb, dzsp, p->st, rl, p->mu_x, p->mu_y, twy, p->geo, p->sc,
+                         reinterpret_cast<cx<T>*>(p->tmpR), p->stream);
       }
       {
         Prof pr(p, HP_K_ROW_APPLY, -1.0, &fl.pslot[1]);
@@ -1046,7 +1047,7 @@ void prec_into(hp_plan p, int pole, const c128* x, c128* y, cx<T>* tmpR, cx<T>* 
   hipLaunchKernelGGL(k_prec_setup, dim3(1), dim3(64), 0, p->stream, st, b);
   launch_row_fwd<T, C>(x, tmpR, part, reinterpret_cast<const cx<C>*>(p->tw_x), p->geo, p->stream);
   launch_col<T, C>(Basis<cx<T>>{tmpR, nullptr, 0, 0}, zout, 0, 0, dz, 0, st, one_solve(), p->mu_x, p->mu_y,
-                   reinterpret_cast<const cx<C>*>(p->tw_y), p->geo, p->sc, p->stream);
+                   reinterpret_cast<const cx<C>*>(p->tw_y), p->geo, p->sc, nullptr, p->stream);
   launch_row_inv<T, C>(zout, y, reinterpret_cast<const cx<C>*>(p->tw_x), p->geo, tile_width<T>(), p->stream);
 }
 

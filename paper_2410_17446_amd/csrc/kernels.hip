@@ -240,7 +240,13 @@ struct ColWaves {
   static constexpr int V = (N <= 1024 && POW2) ? 4 : 2;
 };
 
-template <typename T, typename C, int N, int NC, int LB>
+// MODE: the whole pass (COL_WHOLE), or its two halves for a round whose poles all
+// start from the shared first basis vector: S_y u_0 once (COL_FORWARD, left in z's
+// place as transformed), then each pole's divide and inverse from it (COL_INVERSE,
+// u being that field).
+enum { COL_WHOLE = 0, COL_FORWARD = 1, COL_INVERSE = 2 };
+
+template <typename T, typename C, int N, int NC, int LB, int MODE>
 __global__ __launch_bounds__((ColCfg<T, C, N, LB>::WG), (ColWaves<C, N>::V)) void k_col(
     const Basis<cx<T>> basis, cx<T>* __restrict__ zbase, size_t zsp, size_t zsi, cx<T>* __restrict__ dzbase,
     size_t dzsp, const PoleState* __restrict__ st, const RoundList list, const double* __restrict__ mu_x,
@@ -280,35 +286,44 @@ __global__ __launch_bounds__((ColCfg<T, C, N, LB>::WG), (ColWaves<C, N>::V)) voi
     return (scale * X) * mk<C>((C)(lr * inv), (C)(-li * inv));
   };
   {
-    // load fused with the first transform's pre-processing: thread (c, r0) takes the
-    // row pairs (j, N - j), j = r0 + i NT < N/2, of its column, and row N/2 when r0 = 0
+    if constexpr (MODE != COL_INVERSE) {
+      // load fused with the first transform's pre-processing: thread (c, r0) takes the
+      // row pairs (j, N - j), j = r0 + i NT < N/2, of its column, and row N/2 when r0 = 0
 #pragma unroll 2
-    for (int i = 0; i < N / (2 * NT); ++i) {
-      const int j = r0 + i * NT;
-      if (j == 0) {
-        bc[pidx<C>(0)] = czero<C>();
-        bc[pidx<C>(N / 2)] = (C)2 * cvt<C>(u[(size_t)(N / 2) * TW + c0 + c]);
-        continue;
+      for (int i = 0; i < N / (2 * NT); ++i) {
+        const int j = r0 + i * NT;
+        if (j == 0) {
+          bc[pidx<C>(0)] = czero<C>();
+          bc[pidx<C>(N / 2)] = (C)2 * cvt<C>(u[(size_t)(N / 2) * TW + c0 + c]);
+          continue;
+        }
+        cx<C> ya, yb;
+        dst1_pair(cvt<C>(u[(size_t)j * TW + c0 + c]), cvt<C>(u[(size_t)(N - j) * TW + c0 + c]), sintab[j].re, ya, yb);
+        bc[at(i)] = ya;
+        bc[pidx<C>(N - j)] = yb;
       }
-      cx<C> ya, yb;
-      dst1_pair(cvt<C>(u[(size_t)j * TW + c0 + c]), cvt<C>(u[(size_t)(N - j) * TW + c0 + c]), sintab[j].re, ya,
-                yb);
-      bc[at(i)] = ya;
-      bc[pidx<C>(N - j)] = yb;
+      __syncthreads();
+      dst1_core<C, N>(lds + g * PL, tw, scr + g * CC::SCR, t);
     }
-    __syncthreads();
-    dst1_core<C, N>(lds + g * PL, tw, scr + g * CC::SCR, t);
+    if constexpr (MODE == COL_FORWARD) {
+#pragma unroll 2
+      for (int i = 0; i < N / NT; ++i) z[(size_t)(r0 + i * NT) * TW + c0 + c] = cvt<T>(bc[at(i)]);
+      return;
+    }
     // the divide fused with the inverse transform's pre-processing, same pairs
+    auto first = [&](int p, int at_p) {
+      return MODE == COL_INVERSE ? cvt<C>(u[(size_t)p * TW + c0 + c]) : bc[at_p];
+    };
 #pragma unroll 1
     for (int i = 0; i < N / (2 * NT); ++i) {
       const int j = r0 + i * NT;
       if (j == 0) {
         bc[pidx<C>(0)] = czero<C>();
-        bc[pidx<C>(N / 2)] = (C)2 * divide(bc[pidx<C>(N / 2)], N / 2);
+        bc[pidx<C>(N / 2)] = (C)2 * divide(first(N / 2, pidx<C>(N / 2)), N / 2);
         continue;
       }
       cx<C> ya, yb;
-      dst1_pair(divide(bc[at(i)], j), divide(bc[pidx<C>(N - j)], N - j), sintab[j].re, ya, yb);
+      dst1_pair(divide(first(j, at(i)), j), divide(first(N - j, pidx<C>(N - j)), N - j), sintab[j].re, ya, yb);
       bc[at(i)] = ya;
       bc[pidx<C>(N - j)] = yb;
     }
@@ -1540,16 +1555,36 @@ void launch_row_inv(const cx<T>* in, c128* out, const cx<C>* tw, const Geo& g, i
 template <typename T, typename C>
 void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi, cx<T>* dzbase, size_t dzsp,
                 const PoleState* st, const RoundList& list, const double* mu_x, const double* mu_y, const cx<C>* tw,
-                const Geo& g, const StencilCoef& sc, hipStream_t s) {
+                const Geo& g, const StencilCoef& sc, cx<T>* scratch, hipStream_t s) {
+#define COLM_(NN, LB, MODE, ENTRIES, IN, OUT, OSP, OSI)                                                         \
+  {                                                                                                            \
+    dim3 grid(g.nx / ColCfg<T, C, NN, LB>::GC, g.ncomp * (ENTRIES));                                           \
+    if (g.ncomp == 1)                                                                                          \
+      hipLaunchKernelGGL((k_col<T, C, NN, 1, LB, MODE>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, IN, OUT,  \
+                         OSP, OSI, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
+    else                                                                                                       \
+      hipLaunchKernelGGL((k_col<T, C, NN, 2, LB, MODE>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, IN, OUT,  \
+                         OSP, OSI, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
+  }
+  // The poles of a round that all start from the shared first basis vector share its
+  // forward transform (scratch: one R-domain field) where that is worth a launch of
+  // its own (a launch costs about as much as half the column work of 2^20 elements), from
+  // 2^21 elements over all poles on, and the storage keeps the transform's precision.
+  // 2048^2 vector, 8 poles: 13.54 -> 13.27 ms a step of three rounds.
+  bool shared = scratch && sizeof(T) == sizeof(C) && list.n > 1 &&
+                (size_t)list.n * g.ncomp * g.fsz >= (size_t)1 << 21;
+  for (int a = 0; a < list.n && shared; ++a) shared = round_shared(list.e[a]) && round_m(list.e[a]) == 0;
+  const Basis<cx<T>> once{scratch, nullptr, 0, 0};
 #define COLV_(NN, LB)                                                                                          \
   {                                                                                                            \
-    dim3 grid(g.nx / ColCfg<T, C, NN, LB>::GC, g.ncomp * list.n);                                              \
-    if (g.ncomp == 1)                                                                                          \
-      hipLaunchKernelGGL((k_col<T, C, NN, 1, LB>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, basis, zbase,   \
-                         zsp, zsi, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
-    else                                                                                                       \
-      hipLaunchKernelGGL((k_col<T, C, NN, 2, LB>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, basis, zbase,   \
-                         zsp, zsi, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
+    if constexpr (sizeof(T) == sizeof(C)) {                                                                    \
+      if (shared) {                                                                                            \
+        COLM_(NN, kColLds[0], COL_FORWARD, 1, basis, scratch, 0, 0)                                            \
+        COLM_(NN, LB, COL_INVERSE, list.n, once, zbase, zsp, zsi)                                              \
+        break;                                                                                                 \
+      }                                                                                                        \
+    }                                                                                                          \
+    COLM_(NN, LB, COL_WHOLE, list.n, basis, zbase, zsp, zsi)                                                   \
   }
 #define L_(NN)                                                                                                 \
   {                                                                                                            \
@@ -1563,6 +1598,7 @@ void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi,
   HP_DISPATCH_N(g.ny, L_)
 #undef L_
 #undef COLV_
+#undef COLM_
 }
 
 static int apply_groups(const Geo& g) {
@@ -1668,7 +1704,7 @@ void launch_accum(c128* xacc, const cx<T>* z, size_t zsi, const PoleState* st, i
                                            const Geo&, int, hipStream_t);                                            \
   template void launch_col<T, C>(const Basis<cx<T>>&, cx<T>*, size_t, size_t, cx<T>*, size_t, const PoleState*,      \
                                  const RoundList&, const double*, const double*, const cx<C>*, const Geo&,           \
-                                 const StencilCoef&, hipStream_t);                                                   \
+                                 const StencilCoef&, cx<T>*, hipStream_t);                                           \
   template void launch_row_apply<T, C>(const cx<T>*, size_t, size_t, const cx<T>*, size_t, cx<T>*, size_t,           \
                                        const Basis<cx<T>>&, const C*, const PoleState*, const RoundList&, double2*,  \
                                        const cx<C>*, const Geo&, const StencilCoef&, hipStream_t);

@@ -46,11 +46,12 @@ void launch_row_inv_batch(const cx<T>* in, size_t in_bs, const int* sel, int n, 
 
 // Column pass: z = sigma_m * S_y diag(1/(mu_y + mu_x - b_k)) S_y u_m for the
 // poles of the list.  Vector fields also get dz = D1y z (the y derivative the row
-// pass needs).
+// pass needs).  scratch (may be null): one R-domain field for the first transform of a
+// round whose poles all start from the shared first basis vector.
 template <typename T, typename C = T>
 void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi, cx<T>* dzbase, size_t dzsp,
                 const PoleState* st, const RoundList& list, const double* mu_x, const double* mu_y, const cx<C>* tw,
-                const Geo& g, const StencilCoef& sc, hipStream_t s);
+                const Geo& g, const StencilCoef& sc, cx<T>* scratch, hipStream_t s);
 
 // Row pass: p = S_x (P (S_x z_m)) with P the medium part of Zbar, plus the
 // partial inner products <u_i, p> and <u_i, u_m>, i = 0..m (one per workgroup).
