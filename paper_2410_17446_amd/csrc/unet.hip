@@ -260,110 +260,201 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(const float* __restrict__ x
 // v_mfma_f32_16x16x32_bf16 takes 32 pixels of one image row (lane group kg
 // holds the 8 consecutive pixels 8 kg .. 8 kg + 7 of the segment) for 16 output
 // channels (A = dy, row = lane % 16) against 16 input channels (B = x moved by
-// the tap, column = lane % 16).  A workgroup owns 32 output x 16 input
-// channels and a contiguous share of the row segments; its four waves take
-// every fourth segment (the next one's operands loaded while the current one
-// is multiplied), sum through LDS in wave order, and the workgroup writes
-// part[split][co][ci][tap]; workgroups of the first input-channel block also
-// sum dy for the bias gradient into part[split][cout * cin * 9 + co].
-// k_wgrad_sum adds the splits in a fixed order, so the result does not depend
-// on scheduling.
+// the tap, column = lane % 16).  A workgroup owns 32 output x 16 input channels
+// and a share of the segments, ordered down the columns of 32 pixels, so that a
+// wave walks down rows: row r of x is loaded and converted once and meets the dy
+// rows r - 1, r, r + 1 (taps ky = 2, 1, 0), which stay in LDS;
+// the taps kx = 0 and 2 are the same fragment moved by one pixel, the pixel at
+// either end taken from the neighbouring lane group.  The waves' sums are added
+// through LDS in wave order, and the workgroup writes part[split][co][ci][tap];
+// workgroups of the first input-channel block also sum dy for the bias gradient
+// into part[split][cout * cin * 9 + co].  k_wgrad_sum adds the splits in a fixed
+// order, so the result does not depend on scheduling.
 namespace wgm {
 constexpr int CO = 32, CI = 16, SEG = 32;
 constexpr int SUM_WAVES = 16;  // waves per output chunk in k_wgrad_sum
 }
 
-// v[j] = p[j] for j < valid, else 0; vec: p is 16-byte aligned (two float4 loads when valid >= 8)
-__device__ __forceinline__ void ld8(const float* __restrict__ p, int vec, int valid, float* v) {
-  if (vec && valid >= 8) {
-    const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
-    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = j < valid ? p[j] : 0.f;
-  }
-}
-
-// Operands of one row segment as loaded: dy of the lane's two output channels
-// (8 pixels each) and x of its input channel on the three rows around, pixels
-// px - 1 .. px + 8.
-struct WgSeg {
-  float a[2][8];
-  float b[3][10];
+// One step of a wave: x row r of column (b, xs) against the dy rows of [y0, y1).
+struct WgPos {
+  int b, xs, r, y0, y1;
 };
 
-__device__ __forceinline__ void wg_load(WgSeg& g, const float* __restrict__ x, const float* __restrict__ dy, long q,
-                                        int ws, int B, int cin, int cout, int H, int W, int co0, int ci, int l16, int kg,
-                                        int vec) {
-  const size_t plane = (size_t)H * W;
-  const int xs = (int)(q % ws);
-  const long r = q / ws;
-  const int yy = (int)(r % H), b = (int)(r / H);
-  const int px = xs * wgm::SEG + kg * 8;
-  const int nv = W - px;
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int co = co0 + 16 * c + l16;
-    const bool cv = co < cout;
-    ld8(dy + ((size_t)b * cout + (cv ? co : 0)) * plane + (size_t)yy * W + px, vec, cv ? nv : 0, g.a[c]);
-  }
-#pragma unroll
-  for (int ky = 0; ky < 3; ++ky) {
-    const int sy = yy + ky - 1;
-    const bool rv = ci < cin && sy >= 0 && sy < H;
-    const float* s = x + ((size_t)b * cin + (rv ? ci : 0)) * plane + (size_t)(rv ? sy : 0) * W;
-    ld8(s + px, vec, rv ? nv : 0, g.b[ky] + 1);
-    g.b[ky][0] = (rv && px >= 1 && px - 1 < W) ? s[px - 1] : 0.f;
-    g.b[ky][9] = (rv && px + 8 < W) ? s[px + 8] : 0.f;
-  }
+// Operands of a step as loaded, lane l: pixels 4 (l % 8) .. + 3 of channel l / 8 + 8 i,
+// dy row r + 1 in a (output channels) and x row r in b (input channels); e: the pixel
+// left (l % 32 < 16) or right of the segment, input channel l % 16.
+struct WgRow {
+  float4 a[4], b[2];
+  float e;
+};
+
+// Every load is taken, from a valid address next to the wanted one where that is
+// outside: under a lane's condition each would be waited for before the next is sent.
+// VEC: W % 4 == 0, 16-byte aligned rows, and 8 planes within 4 GB, so that a lane's part
+// of an address is a 32-bit offset.
+template <bool VEC>
+__device__ __forceinline__ float4 wg_load4(const float* __restrict__ img, int c0, int nc, int lc, size_t plane, int px,
+                                           int W) {
+  const int c = min(c0, nc - 1);
+  lc = min(lc, nc - 1 - c);
+  const float* base = img + c * plane;
+  if (VEC)
+    return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) +
+                                            ((unsigned)lc * (unsigned)plane + min(px, W - 4)) * 4u);
+  const float* row = base + lc * plane;
+  return float4{row[min(px, W - 1)], row[min(px + 1, W - 1)], row[min(px + 2, W - 1)], row[min(px + 3, W - 1)]};
 }
 
-__global__ __launch_bounds__(256) void k_conv3_wgrad_mfma(const float* __restrict__ x, const float* __restrict__ dy,
-                                                          float* __restrict__ part, int B, int cin, int cout, int H,
-                                                          int W, int nsplit, int vec) {
-  __shared__ float red[2 * 9 * 256];
-  __shared__ float bred[4][2][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <bool VEC>
+__device__ __forceinline__ void wg_load(WgRow& g, const float* __restrict__ x, const float* __restrict__ dy,
+                                        const WgPos& p, int cin, int cout, int H, int W, int co0, int ci0, int lane) {
+  const size_t plane = (size_t)H * W;
+  const int x0 = p.xs * wgm::SEG, px = x0 + (lane & 7) * 4;
+  const int yd = min(p.r + 1, H - 1), yx = min(max(p.r, 0), H - 1);
+  const float* db = dy + (size_t)p.b * cout * plane + (size_t)yd * W;
+  const float* xb = x + (size_t)p.b * cin * plane + (size_t)yx * W;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) g.a[i] = wg_load4<VEC>(db, co0 + 8 * i, cout, lane / 8, plane, px, W);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) g.b[i] = wg_load4<VEC>(xb, ci0 + 8 * i, cin, lane / 8, plane, px, W);
+  g.e = xb[min(ci0 + (lane & 15), cin - 1) * plane + min(max((lane & 16) ? x0 + wgm::SEG : x0 - 1, 0), W - 1)];
+}
+
+// v with the pixels from the nv-th on 0
+__device__ __forceinline__ float4 wg_mask(const float4& v, int nv) {
+  return float4{nv > 0 ? v.x : 0.f, nv > 1 ? v.y : 0.f, nv > 2 ? v.z : 0.f, nv > 3 ? v.w : 0.f};
+}
+
+// bf16 pair, `lo` in the low half
+__device__ __forceinline__ unsigned bf2(float lo, float hi) {
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  b2 v;
+  v[0] = (__bf16)lo;
+  v[1] = (__bf16)hi;
+  return __builtin_bit_cast(unsigned, v);
+}
+
+typedef unsigned mf_u4 __attribute__((ext_vector_type(4)));
+typedef unsigned mf_u2 __attribute__((ext_vector_type(2)));
+
+// A wave's rows in LDS as bf16, written and read by that wave only: a ring of three dy rows
+// [32][80 bytes], x [16][96 bytes] with the pixels from byte 16 on
+// and their neighbours around them.
+namespace wgm {
+constexpr int DS = 20, XS = 24;  // dwords per channel
+constexpr int ROW = CO * DS;
+constexpr int WAVE = 3 * ROW + CI * XS;
+}
+
+// Bound: memory.  A step loads 6.2 KB for 18 products (288 cycles of a matrix core), x once
+// for every 32 output channels and dy once for every 16 input channels, those of one split
+// on one XCD (split = block id mod nsplit, a multiple of 8 where it can be).  Global loads
+// take 8 lanes per channel, a whole line each; a lane group per channel quarter, as the
+// fragments want it, touches 16 lines with every 16 lanes.  Batch 8, 256 x 256, 96 -> 32
+// channels: 238 us (three rows of x with every row of dy, loads under lane conditions) -> 131
+// (rows walked, unconditional) -> 121 (line-wise loads), 2.2 TB/s; 384 -> 128 channels on
+// 64 x 64: 234 -> 92 -> 59 us; all of a four-level step's, 1506 -> 659 us.
+template <bool VEC>
+__global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const float* __restrict__ x,
+                                                             const float* __restrict__ dy, float* __restrict__ part,
+                                                             int B, int cin, int cout, int H, int W, int nsplit) {
+  __shared__ __attribute__((aligned(16))) unsigned buf[4 * wgm::WAVE > 2 * 9 * 256 ? 4 * wgm::WAVE : 2 * 9 * 256];
+  __shared__ float bred[4][4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, kg = lane >> 4;
-  const int co0 = blockIdx.x * wgm::CO, ci0 = blockIdx.y * wgm::CI, split = blockIdx.z;
+  const int split = blockIdx.x % nsplit, blk = blockIdx.x / nsplit;
+  const int ncob = (cout + wgm::CO - 1) / wgm::CO;
+  const int co0 = (blk % ncob) * wgm::CO, ci0 = (blk / ncob) * wgm::CI;
   const int ws = (W + wgm::SEG - 1) / wgm::SEG;
   const long nseg = (long)B * H * ws;
-  const long q0 = nseg * split / nsplit, q1 = nseg * (split + 1) / nsplit;
-  const int ci = ci0 + l16;
+  const long share = (long)split * 4 + wave;
+  long q = nseg * share / (4L * nsplit);
+  const long q1 = nseg * (share + 1) / (4L * nsplit);
   const size_t stride = (size_t)cout * cin * 9 + cout;  // floats per split
   mf_f4 acc[2][9];
 #pragma unroll
   for (int c = 0; c < 2; ++c)
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[c][t] = mf_f4{0.f, 0.f, 0.f, 0.f};
-  float bs[2] = {0.f, 0.f};
-  WgSeg cur;
-  long q = q0 + wave;
-  if (q < q1) wg_load(cur, x, dy, q, ws, B, cin, cout, H, W, co0, ci, l16, kg, vec);
-  for (; q < q1; q += 4) {
-    WgSeg nxt;
-    if (q + 4 < q1) wg_load(nxt, x, dy, q + 4, ws, B, cin, cout, H, W, co0, ci, l16, kg, vec);
-    mf_b8 a[2];
+  float bs[4] = {0.f, 0.f, 0.f, 0.f};
+  // the rows of one column in this wave's share: the next piece
+  auto piece = [&]() {
+    WgPos p;
+    const long col = q / H;
+    p.y0 = (int)(q - col * H);
+    p.y1 = (int)min((long)H, p.y0 + (q1 - q));
+    p.b = (int)(col / ws);
+    p.xs = (int)(col - (long)p.b * ws);
+    p.r = p.y0 - 1;
+    q += p.y1 - p.y0;
+    return p;
+  };
+  unsigned* da = buf + wave * wgm::WAVE;
+  unsigned* dx = da + 3 * wgm::ROW;
+  if (q < q1) {
+    WgPos p = piece();
+    WgRow g;
+    wg_load<VEC>(g, x, dy, p, cin, cout, H, W, co0, ci0, lane);
+    int slot = 0;  // of dy row r + 1
+    for (;;) {
+      // pixels past the row's end and x rows outside the image are zeros
+      const int x0 = p.xs * wgm::SEG, nv = W - (x0 + (lane & 7) * 4);
+      const bool in = p.r >= 0 && p.r < H, h0 = p.r + 1 < p.y1, h1 = p.r >= p.y0 && p.r < p.y1, h2 = p.r > p.y0;
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        a[c][j] = (__bf16)cur.a[c][j];
-        bs[c] += cur.a[c][j];
+      for (int i = 0; i < 4; ++i) {
+        const float4 v = wg_mask(g.a[i], nv);
+        *reinterpret_cast<mf_u2*>(da + slot * wgm::ROW + (8 * i + lane / 8) * wgm::DS + (lane & 7) * 2) =
+            mf_u2{bf2(v.x, v.y), bf2(v.z, v.w)};
+        if (ci0 == 0 && h0) bs[i] += (v.x + v.y) + (v.z + v.w);
       }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const float4 v = wg_mask(g.b[i], in ? nv : 0);
+        *reinterpret_cast<mf_u2*>(dx + (8 * i + lane / 8) * wgm::XS + 4 + (lane & 7) * 2) =
+            mf_u2{bf2(v.x, v.y), bf2(v.z, v.w)};
+      }
+      const bool ev = in && ((lane & 16) ? x0 + wgm::SEG < W : x0 > 0);
+      dx[l16 * wgm::XS + ((lane & 16) ? 20 : 3)] = ev ? bf2(g.e, g.e) : 0u;
+      // the next step's operands, in flight during the products (the last step's again)
+      bool more = true;
+      WgPos n = p;
+      if (p.r < p.y1)
+        ++n.r;
+      else if (q < q1)
+        n = piece();
+      else
+        more = false;
+      wg_load<VEC>(g, x, dy, n, cin, cout, H, W, co0, ci0, lane);
+      const unsigned* xr = dx + l16 * wgm::XS + 4 + kg * 4;
+      const mf_u4 b1 = *reinterpret_cast<const mf_u4*>(xr);
+      const unsigned left = xr[-1], right = xr[4];
+      const unsigned s1 = __builtin_amdgcn_alignbit(b1[1], b1[0], 16), s2 = __builtin_amdgcn_alignbit(b1[2], b1[1], 16),
+                     s3 = __builtin_amdgcn_alignbit(b1[3], b1[2], 16);
+      const mf_u4 b0 = {(unsigned)__builtin_amdgcn_alignbit(b1[0], left, 16), s1, s2, s3};
+      const mf_u4 b2 = {s1, s2, s3, (unsigned)__builtin_amdgcn_alignbit(right, b1[3], 16)};
+      auto row = [&](int sl, int ky) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const mf_b8 av = __builtin_bit_cast(
+              mf_b8, *reinterpret_cast<const mf_u4*>(da + sl * wgm::ROW + (16 * c + l16) * wgm::DS + kg * 4));
+          acc[c][ky * 3 + 0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(mf_b8, b0),
+                                                                       acc[c][ky * 3 + 0], 0, 0, 0);
+          acc[c][ky * 3 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(mf_b8, b1),
+                                                                       acc[c][ky * 3 + 1], 0, 0, 0);
+          acc[c][ky * 3 + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(mf_b8, b2),
+                                                                       acc[c][ky * 3 + 2], 0, 0, 0);
+        }
+      };
+      if (h0) row(slot, 0);
+      if (h1) row(slot == 0 ? 2 : slot - 1, 1);
+      if (h2) row(slot == 2 ? 0 : slot + 1, 2);
+      if (!more) break;
+      slot = slot == 2 ? 0 : slot + 1;
+      p = n;
     }
-#pragma unroll
-    for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-      for (int kx = 0; kx < 3; ++kx) {
-        mf_b8 bv;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) bv[j] = (__bf16)cur.b[ky][j + kx];
-        acc[0][ky * 3 + kx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], bv, acc[0][ky * 3 + kx], 0, 0, 0);
-        acc[1][ky * 3 + kx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], bv, acc[1][ky * 3 + kx], 0, 0, 0);
-      }
-    cur = nxt;
   }
+  float* red = reinterpret_cast<float*>(buf);
+  __syncthreads();
   // D lane layout: column (input channel) lane % 16, rows (output channels) 4 kg + i
   for (int w = 0; w < 4; ++w) {
     if (wave == w) {
@@ -385,15 +476,15 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad_mfma(const float* __restric
     const int co = co0 + 16 * c + col, cc = ci0 + cil;
     if (co < cout && cc < cin) out[((size_t)co * cin + cc) * 9 + t] = red[e];
   }
-  if (blockIdx.y == 0) {
-    bred[wave][0][lane] = bs[0];
-    bred[wave][1][lane] = bs[1];
+  if (ci0 == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bred[wave][i][lane] = bs[i];
     __syncthreads();
-    if (threadIdx.x < 32) {
-      const int c = threadIdx.x >> 4, col = threadIdx.x & 15, co = co0 + threadIdx.x;
+    if (threadIdx.x < wgm::CO) {
+      const int i = threadIdx.x / 8, l0 = threadIdx.x % 8 * 8, co = co0 + threadIdx.x;
       float a = 0.f;
       for (int w = 0; w < 4; ++w)
-        for (int g = 0; g < 4; ++g) a += bred[w][c][g * 16 + col];
+        for (int j = 0; j < 8; ++j) a += bred[w][i][l0 + j];
       if (co < cout) out[(size_t)cout * cin * 9 + co] = a;
     }
   }
@@ -754,11 +845,13 @@ int ufail(hp_unet n, int code, const std::string& msg) {
 int ch(const hp_unet_s* n, int l) { return n->base << l; }
 
 // Splits of the pixel contraction in the matrix-core weight gradient: about
-// 1024 workgroups in all, each with at least 16 row segments (four per wave).
+// 768 workgroups in all, the three per CU that their registers allow, each with at
+// least 32 row segments (eight per wave: a share of n rows reads n + 2).
 int wgrad_splits(int B, int H, int W, int cin, int cout) {
   const long nseg = (long)B * H * ((W + wgm::SEG - 1) / wgm::SEG);
   const long blocks = (long)((cout + wgm::CO - 1) / wgm::CO) * ((cin + wgm::CI - 1) / wgm::CI);
-  return (int)std::max(1L, std::min(nseg / 16, 1024 / blocks));
+  const long s = std::max(1L, std::min(nseg / 32, 768 / blocks));
+  return (int)(s > 8 ? s / 8 * 8 : s);
 }
 
 // Splits of the 1x1 weight and bias gradients: about 1024 workgroups, each
@@ -900,10 +993,14 @@ void conv3_bwd(hp_unet n, const float* x, const float* dy, const hp_unet_s::Conv
   if (dx) conv3_any(n, dy, n->P + c.w, nullptr, dx, c.co, c.ci, B, H, W, 9, c.ci * 9, 1, 0);
   if (n->bf16) {
     const int ns = wgrad_splits(B, H, W, c.ci, c.co);
-    const int vec = (W % 8 == 0) && ((uintptr_t)x % 16 == 0) && ((uintptr_t)dy % 16 == 0);
-    const dim3 grid((c.co + wgm::CO - 1) / wgm::CO, (c.ci + wgm::CI - 1) / wgm::CI, ns);
-    hipLaunchKernelGGL(k_conv3_wgrad_mfma, grid, dim3(256), 0, n->stream, x, dy, n->wgpart, B, c.ci, c.co, H, W, ns,
-                       vec);
+    const bool vec = (W % 4 == 0) && (size_t)H * W < ((size_t)1 << 27) && ((uintptr_t)x % 16 == 0) && ((uintptr_t)dy % 16 == 0);
+    const dim3 grid((unsigned)(((c.co + wgm::CO - 1) / wgm::CO) * ((c.ci + wgm::CI - 1) / wgm::CI) * ns));
+    if (vec)
+      hipLaunchKernelGGL((k_conv3_wgrad_mfma<true>), grid, dim3(256), 0, n->stream, x, dy, n->wgpart, B, c.ci, c.co, H,
+                         W, ns);
+    else
+      hipLaunchKernelGGL((k_conv3_wgrad_mfma<false>), grid, dim3(256), 0, n->stream, x, dy, n->wgpart, B, c.ci, c.co, H,
+                         W, ns);
     // weights then bias: contiguous in the parameter layout
     const size_t nw = (size_t)c.co * c.ci * 9 + c.co;
     hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)((nw + 63) / 64)), dim3(64 * wgm::SUM_WAVES), 0, n->stream,

@@ -82,3 +82,38 @@ def test_preconditioner_at_every_length(N, precision):
     plan.apply_preconditioner(3, to_gpu(x), y)
     plan.close()
     assert rel_l2(y.cpu().numpy(), ref) < eps * (20 * kappa + 50 * np.log2(N))
+
+
+@pytest.mark.parametrize("base,B,H,W", [(5, 1, 1, 1), (20, 2, 5, 3), (33, 1, 33, 34), (20, 2, 7, 36), (5, 3, 130, 31),
+                                        (33, 1, 40, 100), (16, 2, 3, 64), (8, 9, 1, 4)])
+def test_weight_gradient_exact_at_segment_edges(base, B, H, W):
+    """bf16 weight gradient of the second convolution of a one-level net, exact by construction:
+    integer activations, output weights in {-1, 0, 1} into one channel, and output errors in
+    {-1, 0, 1}, so dy is 0 or +-s, s = 2 / n, which bf16 rounds to s' of 8 bits; every sum is s'
+    times an integer below 2^16.  Rows of one to four 32-pixel segments (the last one whole, short
+    by one, of one to four pixels), of widths that do and don't allow vector loads; one row, fewer
+    rows than waves, columns shared by several waves; channel counts around the tiles of 8, 16, 32.
+    The bias gradient sums float32 dy: at most n roundings of 2^-24."""
+    torch = _cuda()
+    from oracle import unet as ounet
+    from paper_2410_17446_amd.unet import HP_UNET_BF16, UNet
+    rng = np.random.default_rng(base + 100 * W + H)
+    cin = 3
+    net = UNet(1, base, cin, 1, seed=0, precision=HP_UNET_BF16)
+    p = (rng.integers(-1, 2, size=net.nparam) * (rng.random(net.nparam) < 0.25)).astype(np.float32)
+    net.load_state(p)
+    x = rng.integers(-2, 3, size=(B, cin, H, W))
+    ref = ounet.UNet(1, base, cin, 1, p.astype(np.float64))
+    y, _ = ref.forward(x.astype(np.float64))
+    t = y - rng.integers(-1, 2, size=y.shape)
+    net.grad(to_gpu(x.astype(np.float32)), to_gpu(t.astype(np.float32)))
+    g = net.state()["grads"].astype(np.float64)
+    _, rg = ref.loss_and_grad(x.astype(np.float64), t)
+    s = float(np.float32(2.0 / y.size))
+    sb = float(torch.tensor(s, dtype=torch.float32).to(torch.bfloat16).to(torch.float32))
+    o = (cin * 9 + 1) * base  # the second convolution: weights, then bias
+    ints = np.rint(rg * y.size / 2.0)
+    w, b = slice(o, o + base * base * 9), slice(o + base * base * 9, o + base * (base * 9 + 1))
+    assert np.abs(rg * y.size / 2.0 - ints).max() < 1e-6 and np.abs(ints).max() < 2**16
+    assert np.array_equal(g[w], (sb * ints[w]).astype(np.float32).astype(np.float64))
+    assert np.abs(g[b] - s * ints[b]).max() <= y.size * 2.0**-24 * s * y.size
