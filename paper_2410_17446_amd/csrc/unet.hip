@@ -24,6 +24,28 @@ namespace {
 constexpr int TILE = 16;  // 16 x 16 output pixels per workgroup
 constexpr int COB = 8;    // output channels per workgroup
 
+// What a 3x3 convolution does with its sums besides storing them: + bias (forward), max(., 0)
+// (relu), 0 where `mask` <= 0 (the ReLU derivative of the layer whose output the mask is; at 0
+// it is taken as 0), channels from csplit on into y2 (the skip part of a concatenated input's
+// gradient).  Each was a pass over the tensor of its own.
+struct ConvOut {
+  const float* bias;
+  const float* mask;
+  float* y;
+  float* y2;
+  int csplit, relu;
+};
+
+__device__ __forceinline__ void conv_store(const ConvOut& o, float v, int b, int co, int cout, size_t plane, size_t p) {
+  v += o.bias ? o.bias[co] : 0.f;
+  if (o.relu) v = fmaxf(v, 0.f);
+  if (o.mask && o.mask[((size_t)b * cout + co) * plane + p] <= 0.f) v = 0.f;
+  if (co < o.csplit)
+    o.y[((size_t)b * o.csplit + co) * plane + p] = v;
+  else
+    o.y2[((size_t)b * (cout - o.csplit) + co - o.csplit) * plane + p] = v;
+}
+
 __device__ __forceinline__ double wsum(double v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
   return v;
@@ -39,8 +61,8 @@ __device__ __forceinline__ float wsumf(float v) {
 // wsi = 9; the data gradient runs the same loop with the channel roles swapped
 // and the taps flipped.
 __global__ __launch_bounds__(256) void k_conv3(const float* __restrict__ x, const float* __restrict__ w,
-                                               const float* __restrict__ bias, float* __restrict__ y, int cin,
-                                               int cout, int H, int W, int wso, int wsi, int flip, int relu) {
+                                               const ConvOut out, int cin, int cout, int H, int W, int wso, int wsi,
+                                               int flip) {
   __shared__ float tile[(TILE + 2) * (TILE + 2)];
   __shared__ float ws[COB * 9];
   const int tx = threadIdx.x % TILE, ty = threadIdx.x / TILE;
@@ -78,9 +100,7 @@ __global__ __launch_bounds__(256) void k_conv3(const float* __restrict__ x, cons
   for (int c = 0; c < COB; ++c) {
     const int co = co0 + c;
     if (co >= cout) break;
-    float v = acc[c] + (bias ? bias[co] : 0.f);
-    if (relu) v = fmaxf(v, 0.f);
-    y[((size_t)b * cout + co) * plane + (size_t)oy * W + ox] = v;
+    conv_store(out, acc[c], b, co, cout, plane, (size_t)oy * W + ox);
   }
 }
 
@@ -99,73 +119,108 @@ __global__ __launch_bounds__(256) void k_conv3(const float* __restrict__ x, cons
 // the weights as bf16 A fragments in lane order ([co tile][chunk][tap][block]
 // [lane][8]), so a wave reads each fragment as one contiguous 1 KB block.
 //
-// A workgroup (4 waves) computes 64 output channels x an 8 x 16 pixel tile:
-// wave w takes the channel blocks 2 (w % 2), + 1 and the pixel rows 4 (w / 2)
-// .. + 3 (one 16-pixel row per MFMA column block): 8 accumulators, 2 A and 4 B
-// fragments per tap.  The halo patch (10 x 18 pixels) of each chunk goes
-// through LDS with 40-element pixel rows (80 bytes: the 16 lanes of one
-// reduction group read disjoint banks).
+// A workgroup (4 waves) computes an output tile of WC * 32 channels x 16 / WC rows of
+// 16 pixels: wave w takes the channel blocks 2 (w % WC), + 1 and the pixel rows
+// 4 (w / WC) .. + 3 (one 16-pixel row per MFMA column block): 8 accumulators, 2 A and
+// 4 B fragments per tap.  The halo patch (2 more rows and columns) of each chunk goes
+// through LDS with 40-element pixel rows (80 bytes: the 16 lanes of one reduction
+// group read disjoint banks).
 namespace mf {
-constexpr int TH = 8, TWD = 16;           // pixel tile
-constexpr int CO = 64, CK = 32, CS = 40;  // channels per tile, per chunk, LDS pixel stride
-constexpr int CB = CO / 16;               // 16-channel blocks per tile
-constexpr int HX = TH + 2, HY = TWD + 2;  // halo rows, columns
+constexpr int TWD = 16;                   // pixel columns of a tile
+constexpr int CO = 64, CK = 32, CS = 40;  // channels per fragment tile, per chunk, LDS pixel stride
+constexpr int CB = CO / 16;               // 16-channel blocks per fragment tile
+constexpr int HY = TWD + 2;               // halo columns
+constexpr int rows(int wc) { return 16 / wc; }
 }  // namespace mf
 
 typedef float mf_f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 mf_b8 __attribute__((ext_vector_type(8)));
 
-// x [B][C][H][W] float -> xb [B][ceil(C/32)][H][W][32] bf16 (channels past C are 0)
-__global__ void k_to_bf16c(const float* __restrict__ x, __bf16* __restrict__ xb, int B, int C, int H, int W) {
-  const int nch = (C + mf::CK - 1) / mf::CK;
-  const size_t plane = (size_t)H * W;
-  const size_t n = (size_t)B * nch * plane;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
-    const size_t p = e % plane;
-    const int ch = (int)((e / plane) % nch), b = (int)(e / (plane * nch));
-    mf_b8 v[4];
-#pragma unroll
-    for (int c = 0; c < mf::CK; ++c) {
-      const int ci = ch * mf::CK + c;
-      v[c / 8][c % 8] = (__bf16)(ci < C ? x[((size_t)b * C + ci) * plane + p] : 0.f);
-    }
-    mf_b8* o = reinterpret_cast<mf_b8*>(xb + e * mf::CK);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) o[q] = v[q];
-  }
-}
+// The input of a convolution or of its weight gradient: x [B][C - cu][H][W], behind the
+// nearest-neighbour 2x upsampling of low [B][cu][H/2][W/2] (cu = 0: none) as the first cu
+// channels.  cu > 0: cu % 32 == 0, H even, W % 8 == 0.
+struct ConvIn {
+  const float* x;
+  const float* low;
+  int cu;
+};
 
-// A fragments of the weights: wp[(((ct * nch + ch) * 9 + tap) * CB + blk) * 64 + lane][j] =
+// The operands of one convolution, in one launch (apart, the weights took 5 us a launch).
+// Bound: memory; 32 channels of batch 8, 256 x 256 in 17 us, 5.9 TB/s (in cache), 23 us with a
+// thread a pixel, whose stores were 16 bytes of every 64.  Blocks below nbx: in -> xb [B][ceil(C/32)][H][W][32] bf16 (channels past C
+// are 0); four lanes a pixel, 8 channels each, so that a wave stores 1 KB in a row.
+//
+// The others: A fragments of the weights, wp[(((ct * nch + ch) * 9 + tap) * CB + blk) * 64 + lane][j] =
 // w(co, ci, tap) with co = 64 ct + 16 blk + lane % 16, ci = 32 ch + 8 (lane / 16) + j, the
 // weight of (co, ci, tap) read at co * wso + ci * wsi + (flip ? 8 - tap : tap); 0 outside.
-__global__ void k_pack_w(const float* __restrict__ w, __bf16* __restrict__ wp, int cin, int cout, int wso, int wsi,
-                         int flip) {
-  const int nch = (cin + mf::CK - 1) / mf::CK, nct = (cout + mf::CO - 1) / mf::CO;
+__global__ __launch_bounds__(256) void k_conv3_prep(const ConvIn in, __bf16* __restrict__ xb, int B, int C, int H,
+                                                    int W, unsigned nbx, const float* __restrict__ w,
+                                                    __bf16* __restrict__ wp, int cout, int wso, int wsi, int flip) {
+  const int nch = (C + mf::CK - 1) / mf::CK;
+  if (blockIdx.x < nbx) {
+    const size_t plane = (size_t)H * W, n = (size_t)B * nch * plane;
+    const int q = threadIdx.x & 3;
+    for (size_t e = (size_t)blockIdx.x * 64 + threadIdx.x / 4; e < n; e += (size_t)nbx * 64) {
+      const unsigned bc = (unsigned)(e / plane);
+      const size_t p = e - bc * plane;
+      const int b = bc / nch, ci = (int)(bc - (unsigned)b * nch) * mf::CK + q * 8;
+      const float* src;
+      size_t cs;  // channel stride
+      int nc;     // channels there are
+      if (ci < in.cu) {
+        const unsigned yy = (unsigned)p / (unsigned)W, xx = (unsigned)p - yy * W;
+        cs = plane / 4;
+        nc = in.cu - ci;
+        src = in.low + ((size_t)b * in.cu + ci) * cs + (size_t)(yy / 2) * (W / 2) + xx / 2;
+      } else {
+        cs = plane;
+        nc = C - ci;
+        src = in.x + ((size_t)b * (C - in.cu) + (ci - in.cu)) * cs + p;
+      }
+      mf_b8 v;
+      if (nc >= 8) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = (__bf16)src[c * cs];
+      } else {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = (__bf16)(c < nc ? src[c * cs] : 0.f);
+      }
+      *reinterpret_cast<mf_b8*>(xb + e * mf::CK + q * 8) = v;
+    }
+    return;
+  }
+  const int nct = (cout + mf::CO - 1) / mf::CO;
   const size_t n = (size_t)nct * nch * 9 * mf::CB * 64 * 8;
-  for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
+  for (size_t e = (size_t)(blockIdx.x - nbx) * 256 + threadIdx.x; e < n; e += (size_t)(gridDim.x - nbx) * 256) {
     const int j = (int)(e % 8), lane = (int)((e / 8) % 64), blk = (int)((e / 512) % mf::CB);
     const size_t r = e / (512 * mf::CB);
     const int tap = (int)(r % 9), ch = (int)((r / 9) % nch), ct = (int)(r / (9 * (size_t)nch));
     const int co = ct * mf::CO + blk * 16 + lane % 16, ci = ch * mf::CK + (lane / 16) * 8 + j;
     float v = 0.f;
-    if (co < cout && ci < cin) v = w[(size_t)co * wso + (size_t)ci * wsi + (flip ? 8 - tap : tap)];
+    if (co < cout && ci < C) v = w[(size_t)co * wso + (size_t)ci * wsi + (flip ? 8 - tap : tap)];
     wp[e] = (__bf16)v;
   }
 }
 
+// WC = 2: 64 channels; WC = 1: 32, for channel counts whose last 64 would be half empty
+// (batch 8, 256 x 256: 32 -> 32 channels 39 us with 64, 27 with 32; 96 -> 32, 78 and 54;
+// 32 -> 96, 85 and 70).  MASK: out.mask is set; its values are loaded before any is used, here
+// and not before the products, where they take the registers of a wave (56 and 62 us at
+// 32 -> 32; the mask read one by one, 90; a pass of its own, 27 + 22, but also a launch).
+template <int WC, bool MASK>
 __global__ __launch_bounds__(256) void k_conv3_mfma(const __bf16* __restrict__ xb, const __bf16* __restrict__ wp,
-                                                    const float* __restrict__ bias, float* __restrict__ y, int cin,
-                                                    int cout, int H, int W, int relu) {
+                                                    const ConvOut out, int cin, int cout, int H, int W) {
   using namespace mf;
+  constexpr int TH = rows(WC), HX = TH + 2;
   __shared__ __attribute__((aligned(16))) __bf16 xs[HX * HY * CS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int ntx = (W + TWD - 1) / TWD;
   const int x0 = (blockIdx.x % ntx) * TWD, y0 = (blockIdx.x / ntx) * TH;
-  const int ct = blockIdx.y, b = blockIdx.z;
+  const int cb = blockIdx.y * 2 * WC + (wave % WC) * 2;  // first 16-channel block of this wave
+  const int ct = cb / CB, cb0 = cb % CB, b = blockIdx.z;
   const int nch = (cin + CK - 1) / CK;
   const size_t plane = (size_t)H * W;
-  const int cb0 = (wave & 1) * 2;  // first channel block of this wave
-  const int r0 = (wave >> 1) * 4;  // first pixel row of this wave
+  const int r0 = (wave / WC) * 4;  // first pixel row of this wave
   const int col = lane & 15, kg = lane >> 4;
   mf_f4 acc[2][4];
 #pragma unroll
@@ -177,16 +232,16 @@ __global__ __launch_bounds__(256) void k_conv3_mfma(const __bf16* __restrict__ x
     __syncthreads();
     // halo patch of this chunk: 4 x 16 bytes per pixel
     const mf_b8* src = reinterpret_cast<const mf_b8*>(xb) + ((size_t)b * nch + ch) * plane * 4;
-    for (int e = tid; e < HX * HY * 4; e += 256) {
+#pragma unroll
+    for (int k = 0; k < (HX * HY * 4 + 255) / 256; ++k) {
+      const int e = tid + k * 256;
       const int q = e & 3, r = e >> 2;
       const int gy = y0 + r / HY - 1, gx = x0 + r % HY - 1;
-      mf_b8 v;
-      if (gy >= 0 && gy < H && gx >= 0 && gx < W)
-        v = src[((size_t)gy * W + gx) * 4 + q];
-      else
+      const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
+      mf_b8 v = src[((size_t)min(max(gy, 0), H - 1) * W + min(max(gx, 0), W - 1)) * 4 + q];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (__bf16)0.f;
-      *reinterpret_cast<mf_b8*>(&xs[r * CS + q * 8]) = v;
+      for (int j = 0; j < 8; ++j) v[j] = in ? v[j] : (__bf16)0.f;
+      if (e < HX * HY * 4) *reinterpret_cast<mf_b8*>(&xs[r * CS + q * 8]) = v;
     }
     __syncthreads();
     const mf_b8* wc = wf + (size_t)ch * 9 * CB * 64;
@@ -203,21 +258,35 @@ __global__ __launch_bounds__(256) void k_conv3_mfma(const __bf16* __restrict__ x
       }
     }
   }
-  // D: column = pixel x0 + col of row y0 + r0 + r; rows = channels 16 (cb0 + c) + 4 kg + i
+  // D: column = pixel x0 + col of row y0 + r0 + r; rows = channels 16 (cb + c) + 4 kg + i
+  const int ox = x0 + col;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int oy = y0 + r0 + r, ox = x0 + col;
-    if (oy >= H || ox >= W) continue;
+  for (int c = 0; c < 2; ++c) {
+    const int co0 = (cb + c) * 16 + kg * 4;
+    float mk[4][4], bv[4];
+    float* dst[4];
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int i = 0; i < 4; ++i) {
+      const int co = min(co0 + i, cout - 1);
+      dst[i] = co < out.csplit ? out.y + ((size_t)b * out.csplit + co) * plane
+                               : out.y2 + ((size_t)b * (cout - out.csplit) + co - out.csplit) * plane;
+      bv[i] = out.bias ? out.bias[co] : 0.f;
+      if (MASK)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          mk[r][i] = out.mask[((size_t)b * cout + co) * plane + (size_t)min(y0 + r0 + r, H - 1) * W + min(ox, W - 1)];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int oy = y0 + r0 + r;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int co = ct * CO + (cb0 + c) * 16 + kg * 4 + i;
-        if (co >= cout) continue;
-        float v = acc[c][r][i] + (bias ? bias[co] : 0.f);
-        if (relu) v = fmaxf(v, 0.f);
-        y[((size_t)b * cout + co) * plane + (size_t)oy * W + ox] = v;
+        float v = acc[c][r][i] + bv[i];
+        if (out.relu) v = fmaxf(v, 0.f);
+        if (MASK && mk[r][i] <= 0.f) v = 0.f;
+        if (oy < H && ox < W && co0 + i < cout) dst[i][(size_t)oy * W + ox] = v;
       }
+    }
   }
 }
 
@@ -305,19 +374,32 @@ __device__ __forceinline__ float4 wg_load4(const float* __restrict__ img, int c0
   return float4{row[min(px, W - 1)], row[min(px + 1, W - 1)], row[min(px + 2, W - 1)], row[min(px + 3, W - 1)]};
 }
 
+// The upsampled part of a concatenated input (VEC): the aligned four pixels of the low row
+// that hold the lane's two, picked by wg_up.
 template <bool VEC>
-__device__ __forceinline__ void wg_load(WgRow& g, const float* __restrict__ x, const float* __restrict__ dy,
-                                        const WgPos& p, int cin, int cout, int H, int W, int co0, int ci0, int lane) {
+__device__ __forceinline__ void wg_load(WgRow& g, const ConvIn& in, const float* __restrict__ dy, const WgPos& p,
+                                        int cin, int cout, int H, int W, int co0, int ci0, int lane) {
   const size_t plane = (size_t)H * W;
   const int x0 = p.xs * wgm::SEG, px = x0 + (lane & 7) * 4;
   const int yd = min(p.r + 1, H - 1), yx = min(max(p.r, 0), H - 1);
   const float* db = dy + (size_t)p.b * cout * plane + (size_t)yd * W;
-  const float* xb = x + (size_t)p.b * cin * plane + (size_t)yx * W;
 #pragma unroll
   for (int i = 0; i < 4; ++i) g.a[i] = wg_load4<VEC>(db, co0 + 8 * i, cout, lane / 8, plane, px, W);
+  const bool low = ci0 < in.cu;
+  const int sh = low ? 1 : 0, nc = low ? in.cu : cin - in.cu, c0 = low ? ci0 : ci0 - in.cu, wx = W >> sh;
+  const size_t px_plane = plane >> (2 * sh);
+  const float* xb = (low ? in.low : in.x) + (size_t)p.b * nc * px_plane + (size_t)(yx >> sh) * wx;
+  const int pxx = VEC ? (px >> sh) & ~3 : px;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) g.b[i] = wg_load4<VEC>(xb, ci0 + 8 * i, cin, lane / 8, plane, px, W);
-  g.e = xb[min(ci0 + (lane & 15), cin - 1) * plane + min(max((lane & 16) ? x0 + wgm::SEG : x0 - 1, 0), W - 1)];
+  for (int i = 0; i < 2; ++i) g.b[i] = wg_load4<VEC>(xb, c0 + 8 * i, nc, lane / 8, px_plane, pxx, wx);
+  g.e = xb[min(c0 + (lane & 15), nc - 1) * px_plane +
+           (min(max((lane & 16) ? x0 + wgm::SEG : x0 - 1, 0), W - 1) >> sh)];
+}
+
+// the lane's four pixels of v (see wg_load); low: each low pixel twice
+__device__ __forceinline__ float4 wg_up(const float4& v, bool low, int lane) {
+  const float a = (lane & 1) ? v.z : v.x, b = (lane & 1) ? v.w : v.y;
+  return low ? float4{a, a, b, b} : v;
 }
 
 // v with the pixels from the nv-th on 0
@@ -355,9 +437,9 @@ constexpr int WAVE = 3 * ROW + CI * XS;
 // (rows walked, unconditional) -> 121 (line-wise loads), 2.2 TB/s; 384 -> 128 channels on
 // 64 x 64: 234 -> 92 -> 59 us; all of a four-level step's, 1506 -> 659 us.
 template <bool VEC>
-__global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const float* __restrict__ x,
-                                                             const float* __restrict__ dy, float* __restrict__ part,
-                                                             int B, int cin, int cout, int H, int W, int nsplit) {
+__global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const ConvIn in_x, const float* __restrict__ dy,
+                                                             float* __restrict__ part, int B, int cin, int cout,
+                                                             int H, int W, int nsplit) {
   __shared__ __attribute__((aligned(16))) unsigned buf[4 * wgm::WAVE > 2 * 9 * 256 ? 4 * wgm::WAVE : 2 * 9 * 256];
   __shared__ float bred[4][4][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -394,7 +476,7 @@ __global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const float* __rest
   if (q < q1) {
     WgPos p = piece();
     WgRow g;
-    wg_load<VEC>(g, x, dy, p, cin, cout, H, W, co0, ci0, lane);
+    wg_load<VEC>(g, in_x, dy, p, cin, cout, H, W, co0, ci0, lane);
     int slot = 0;  // of dy row r + 1
     for (;;) {
       // pixels past the row's end and x rows outside the image are zeros
@@ -409,7 +491,7 @@ __global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const float* __rest
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const float4 v = wg_mask(g.b[i], in ? nv : 0);
+        const float4 v = wg_mask(wg_up(g.b[i], ci0 < in_x.cu, lane), in ? nv : 0);
         *reinterpret_cast<mf_u2*>(dx + (8 * i + lane / 8) * wgm::XS + 4 + (lane & 7) * 2) =
             mf_u2{bf2(v.x, v.y), bf2(v.z, v.w)};
       }
@@ -424,7 +506,7 @@ __global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const float* __rest
         n = piece();
       else
         more = false;
-      wg_load<VEC>(g, x, dy, n, cin, cout, H, W, co0, ci0, lane);
+      wg_load<VEC>(g, in_x, dy, n, cin, cout, H, W, co0, ci0, lane);
       const unsigned* xr = dx + l16 * wgm::XS + 4 + kg * 4;
       const mf_u4 b1 = *reinterpret_cast<const mf_u4*>(xr);
       const unsigned left = xr[-1], right = xr[4];
@@ -527,20 +609,45 @@ __global__ __launch_bounds__(256) void k_bias_grad(const float* __restrict__ dy,
 }
 
 // 1x1 convolution y[b][co](p) = sum_ci w[co][ci] x[b][ci](p) (+ bias); transpose:
-// y[b][ci](p) = sum_co w[co][ci] x[b][co](p) (the data gradient).
+// y[b][ci](p) = sum_co w[co][ci] x[b][co](p) (the data gradient), 0 where mask <= 0.
+// A thread takes V consecutive pixels (V = 4: plane % 4 == 0, 16-byte aligned) and four output
+// channels at a time.
+template <int V>
 __global__ __launch_bounds__(256) void k_conv1(const float* __restrict__ x, const float* __restrict__ w,
-                                               const float* __restrict__ bias, float* __restrict__ y, int B, int cin,
-                                               int cout, size_t plane, int transpose) {
-  const size_t n = (size_t)B * plane;
+                                               const float* __restrict__ bias, const float* __restrict__ mask,
+                                               float* __restrict__ y, int B, int cin, int cout, size_t plane,
+                                               int transpose) {
+  typedef float vec __attribute__((ext_vector_type(V)));
+  const size_t n = (size_t)B * plane / V;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-    const int b = (int)(i / plane);
-    const size_t p = i % plane;
-    for (int co = 0; co < cout; ++co) {
-      float acc = bias ? bias[co] : 0.f;
-      for (int ci = 0; ci < cin; ++ci)
-        acc += (transpose ? w[(size_t)ci * cout + co] : w[(size_t)co * cin + ci]) *
-               x[((size_t)b * cin + ci) * plane + p];
-      y[((size_t)b * cout + co) * plane + p] = acc;
+    const size_t b = i / (plane / V), p = (i - b * (plane / V)) * V;
+    for (int co0 = 0; co0 < cout; co0 += 4) {
+      vec acc[4], mk[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int co = min(co0 + c, cout - 1);
+        if (mask) mk[c] = *reinterpret_cast<const vec*>(mask + (b * cout + co) * plane + p);
+        acc[c] = (vec)(bias ? bias[co] : 0.f);
+      }
+#pragma unroll 4
+      for (int ci = 0; ci < cin; ++ci) {
+        const vec xv = *reinterpret_cast<const vec*>(x + (b * cin + ci) * plane + p);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int co = min(co0 + c, cout - 1);
+          const float wv = transpose ? w[(size_t)ci * cout + co] : w[(size_t)co * cin + ci];
+#pragma unroll
+          for (int j = 0; j < V; ++j) acc[c][j] += wv * xv[j];
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (co0 + c >= cout) break;
+        if (mask)
+#pragma unroll
+          for (int j = 0; j < V; ++j) acc[c][j] = mk[c][j] <= 0.f ? 0.f : acc[c][j];
+        *reinterpret_cast<vec*>(y + (b * cout + co0 + c) * plane + p) = acc[c];
+      }
     }
   }
 }
@@ -572,12 +679,6 @@ __global__ __launch_bounds__(256) void k_conv1_wgrad_split(const float* __restri
   if (threadIdx.x == 0) part[(size_t)s * n + e] = red[0] + red[1] + red[2] + red[3];
 }
 
-// dy = 0 where the ReLU output y is 0 (the derivative at 0 is taken as 0)
-__global__ void k_relu_bwd(const float* __restrict__ y, float* __restrict__ dy, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    if (y[i] <= 0.f) dy[i] = 0.f;
-}
-
 // 2x2 average pooling of [planes][H][W] -> [planes][H/2][W/2], and its adjoint
 __global__ void k_pool(const float* __restrict__ x, float* __restrict__ y, size_t planes, int H, int W) {
   const int h = H / 2, w = W / 2;
@@ -590,18 +691,23 @@ __global__ void k_pool(const float* __restrict__ x, float* __restrict__ y, size_
     y[i] = 0.25f * (s[0] + s[1] + s[W] + s[W + 1]);
   }
 }
-__global__ void k_pool_bwd(const float* __restrict__ dy, float* __restrict__ dx, size_t planes, int H, int W) {
+// dx = the pooling's adjoint of dy + dskip, 0 where y <= 0 (y: the pooled ReLU output).
+// One pass instead of three: 32 channels of batch 8, 256 x 256 in 41 us against 30 + 32 + 31.
+__global__ void k_pool_bwd(const float* __restrict__ dy, const float* __restrict__ dskip,
+                           const float* __restrict__ y, float* __restrict__ dx, size_t planes, int H, int W) {
   const size_t n = planes * H * W;
-  const int w = W / 2;
+  const unsigned w = W / 2, hw = (unsigned)H * W;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const size_t pl = i / ((size_t)H * W);
-    const int r = (int)(i % ((size_t)H * W));
-    const int yy = r / W, xx = r % W;
-    dx[i] = 0.25f * dy[pl * (H / 2) * w + (size_t)(yy / 2) * w + xx / 2];
+    const size_t pl = i / hw;
+    const unsigned r = (unsigned)(i - pl * hw);
+    const unsigned yy = r / (unsigned)W, xx = r - yy * W;
+    const float v = 0.25f * dy[pl * (hw / 4) + (size_t)(yy / 2) * w + xx / 2] + dskip[i];
+    dx[i] = y[i] <= 0.f ? 0.f : v;
   }
 }
 // nearest-neighbour 2x upsampling of [B][C][h][w] into channels [c0, c0+C) of
-// [B][Ctot][2h][2w], and its adjoint (sum over each 2x2 block)
+// [B][Ctot][2h][2w], and its adjoint on [planes][2h][2w] (sum over each 2x2 block; 0 where
+// the upsampled ReLU output y <= 0)
 __global__ void k_up(const float* __restrict__ x, float* __restrict__ y, int B, int C, int Ctot, int c0, int h,
                      int w) {
   const int H = 2 * h, W = 2 * w;
@@ -613,36 +719,28 @@ __global__ void k_up(const float* __restrict__ x, float* __restrict__ y, int B, 
     y[(((size_t)b * Ctot + c0 + c) * H + yy) * W + xx] = x[(((size_t)b * C + c) * h + yy / 2) * w + xx / 2];
   }
 }
-__global__ void k_up_bwd(const float* __restrict__ dy, float* __restrict__ dx, int B, int C, int Ctot, int c0, int h,
-                         int w) {
-  const int H = 2 * h, W = 2 * w;
-  const size_t n = (size_t)B * C * h * w;
+__global__ void k_up_bwd(const float* __restrict__ dy, const float* __restrict__ y, float* __restrict__ dx,
+                         size_t planes, int h, int w) {
+  const unsigned W = 2 * (unsigned)w, hw = (unsigned)h * w;
+  const size_t n = planes * hw;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int xx = (int)(i % w), yy = (int)((i / w) % h);
-    const size_t bc = i / ((size_t)h * w);
-    const int c = (int)(bc % C), b = (int)(bc / C);
-    const float* s = dy + (((size_t)b * Ctot + c0 + c) * H + 2 * yy) * W + 2 * xx;
-    dx[i] = s[0] + s[1] + s[W] + s[W + 1];
+    const size_t pl = i / hw;
+    const unsigned r = (unsigned)(i - pl * hw);
+    const unsigned yy = r / (unsigned)w, xx = r - yy * w;
+    const float* s = dy + pl * 4 * hw + (size_t)(2 * yy) * W + 2 * xx;
+    dx[i] = y[i] <= 0.f ? 0.f : s[0] + s[1] + s[W] + s[W + 1];
   }
 }
-// small [B][C][P] <-> channels [c0, c0+C) of big [B][Ctot][P]; dir 0: small -> big
-__global__ void k_chcopy(float* __restrict__ big, float* __restrict__ small, int B, int C, int Ctot, int c0, size_t P,
-                         int dir) {
+// small [B][C][P] -> channels [c0, c0+C) of big [B][Ctot][P]
+__global__ void k_chcopy(float* __restrict__ big, const float* __restrict__ small, int B, int C, int Ctot, int c0,
+                         size_t P) {
   const size_t n = (size_t)B * C * P;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
     const size_t p = i % P;
     const size_t bc = i / P;
     const int c = (int)(bc % C), b = (int)(bc / C);
-    const size_t j = ((size_t)b * Ctot + c0 + c) * P + p;
-    if (dir == 0)
-      big[j] = small[i];
-    else
-      small[i] = big[j];
+    big[((size_t)b * Ctot + c0 + c) * P + p] = small[i];
   }
-}
-__global__ void k_add(float* __restrict__ a, const float* __restrict__ b, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    a[i] += b[i];
 }
 // loss = mean (y - t)^2: d = 2 (y - t) / n and per-block partial sums of (y - t)^2
 __global__ __launch_bounds__(256) void k_mse(const float* __restrict__ y, const float* __restrict__ t,
@@ -966,54 +1064,79 @@ int ensure_acts(hp_unet n, int B, int H, int W) {
   return HP_OK;
 }
 
-// y = conv(x) with weights addressed as in k_conv3; float32 or bf16 matrix cores
-void conv3_any(hp_unet n, const float* x, const float* w, const float* bias, float* y, int cin, int cout, int B,
-               int H, int W, int wso, int wsi, int flip, int relu) {
+// conv(in) with weights addressed as in k_conv3; float32 or bf16 matrix cores
+void conv3_any(hp_unet n, const ConvIn& in, const float* w, const ConvOut& out, int cin, int cout, int B, int H, int W,
+               int wso, int wsi, int flip) {
   if (n->bf16) {
     const int nch = (cin + mf::CK - 1) / mf::CK, nct = (cout + mf::CO - 1) / mf::CO;
     const size_t xn = (size_t)B * nch * H * W, wn = (size_t)nct * nch * 9 * mf::CB * 64 * 8;
-    hipLaunchKernelGGL(k_to_bf16c, dim3(eblocks(xn)), dim3(256), 0, n->stream, x, n->xb, B, cin, H, W);
-    hipLaunchKernelGGL(k_pack_w, dim3(eblocks(wn)), dim3(256), 0, n->stream, w, n->wpk, cin, cout, wso, wsi, flip);
-    dim3 grid(((W + mf::TWD - 1) / mf::TWD) * ((H + mf::TH - 1) / mf::TH), nct, B);
-    hipLaunchKernelGGL(k_conv3_mfma, grid, dim3(256), 0, n->stream, n->xb, n->wpk, bias, y, cin, cout, H, W, relu);
+    const unsigned nbx = (unsigned)eblocks(xn * 4);
+    hipLaunchKernelGGL(k_conv3_prep, dim3(nbx + eblocks(wn)), dim3(256), 0, n->stream, in, n->xb, B, cin, H, W, nbx, w,
+                       n->wpk, cout, wso, wsi, flip);
+    const int n32 = (cout + 31) / 32, wc = n32 % 2 ? 1 : 2;
+    const int th = mf::rows(wc);
+    const dim3 grid(((W + mf::TWD - 1) / mf::TWD) * ((H + th - 1) / th), n32 / wc, B);
+    auto kern = wc == 1 ? (out.mask ? k_conv3_mfma<1, true> : k_conv3_mfma<1, false>)
+                        : (out.mask ? k_conv3_mfma<2, true> : k_conv3_mfma<2, false>);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, n->stream, n->xb, n->wpk, out, cin, cout, H, W);
   } else {
     dim3 grid(((W + TILE - 1) / TILE) * ((H + TILE - 1) / TILE), (cout + COB - 1) / COB, B);
-    hipLaunchKernelGGL(k_conv3, grid, dim3(256), 0, n->stream, x, w, bias, y, cin, cout, H, W, wso, wsi, flip,
-                       relu);
+    hipLaunchKernelGGL(k_conv3, grid, dim3(256), 0, n->stream, in.x, w, out, cin, cout, H, W, wso, wsi, flip);
   }
 }
 
-void conv3(hp_unet n, const float* x, const hp_unet_s::Conv& c, float* y, int B, int H, int W, int relu) {
-  conv3_any(n, x, n->P + c.w, n->P + c.b, y, c.ci, c.co, B, H, W, c.ci * 9, 9, 0, relu);
+// the output layer and its data gradient (all its buffers are allocated here)
+void conv1(hp_unet n, const float* x, const float* bias, const float* mask, float* y, int B, int cin, int cout,
+           size_t plane, int transpose) {
+  const bool vec = plane % 4 == 0;
+  hipLaunchKernelGGL(vec ? k_conv1<4> : k_conv1<1>, dim3(eblocks(B * plane / (vec ? 4 : 1))), dim3(256), 0, n->stream,
+                     x, n->P + n->out.w, bias, mask, y, B, cin, cout, plane, transpose);
 }
 
-// Gradients of one 3x3 convolution: dW, db into G; dx (when wanted) from dy.
-void conv3_bwd(hp_unet n, const float* x, const float* dy, const hp_unet_s::Conv& c, float* dx, int B, int H,
+ConvIn plain(const float* x) { return ConvIn{x, nullptr, 0}; }
+
+void conv3(hp_unet n, const ConvIn& in, const hp_unet_s::Conv& c, float* y, int B, int H, int W) {
+  conv3_any(n, in, n->P + c.w, ConvOut{n->P + c.b, nullptr, y, nullptr, c.co, 1}, c.ci, c.co, B, H, W, c.ci * 9, 9, 0);
+}
+
+// Gradients of one 3x3 convolution: dW, db into G; the input's from dy into `dx` (when wanted).
+void conv3_bwd(hp_unet n, const ConvIn& in, const float* dy, const hp_unet_s::Conv& c, const ConvOut* dx, int B, int H,
                int W) {
-  if (dx) conv3_any(n, dy, n->P + c.w, nullptr, dx, c.co, c.ci, B, H, W, 9, c.ci * 9, 1, 0);
+  if (dx) conv3_any(n, plain(dy), n->P + c.w, *dx, c.co, c.ci, B, H, W, 9, c.ci * 9, 1);
   if (n->bf16) {
     const int ns = wgrad_splits(B, H, W, c.ci, c.co);
-    const bool vec = (W % 4 == 0) && (size_t)H * W < ((size_t)1 << 27) && ((uintptr_t)x % 16 == 0) && ((uintptr_t)dy % 16 == 0);
+    const bool vec = (W % 4 == 0) && (size_t)H * W < ((size_t)1 << 27) && ((uintptr_t)in.x % 16 == 0) &&
+                     ((uintptr_t)dy % 16 == 0);
     const dim3 grid((unsigned)(((c.co + wgm::CO - 1) / wgm::CO) * ((c.ci + wgm::CI - 1) / wgm::CI) * ns));
     if (vec)
-      hipLaunchKernelGGL((k_conv3_wgrad_mfma<true>), grid, dim3(256), 0, n->stream, x, dy, n->wgpart, B, c.ci, c.co, H,
+      hipLaunchKernelGGL((k_conv3_wgrad_mfma<true>), grid, dim3(256), 0, n->stream, in, dy, n->wgpart, B, c.ci, c.co, H,
                          W, ns);
     else
-      hipLaunchKernelGGL((k_conv3_wgrad_mfma<false>), grid, dim3(256), 0, n->stream, x, dy, n->wgpart, B, c.ci, c.co, H,
-                         W, ns);
+      hipLaunchKernelGGL((k_conv3_wgrad_mfma<false>), grid, dim3(256), 0, n->stream, in, dy, n->wgpart, B, c.ci, c.co,
+                         H, W, ns);
     // weights then bias: contiguous in the parameter layout
     const size_t nw = (size_t)c.co * c.ci * 9 + c.co;
     hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)((nw + 63) / 64)), dim3(64 * wgm::SUM_WAVES), 0, n->stream,
                        n->wgpart, n->G + c.w, nw, ns);
   } else {
-    hipLaunchKernelGGL(k_conv3_wgrad, dim3(c.co * c.ci), dim3(256), 0, n->stream, x, dy, n->G + c.w, B, c.ci, c.co,
+    hipLaunchKernelGGL(k_conv3_wgrad, dim3(c.co * c.ci), dim3(256), 0, n->stream, in.x, dy, n->G + c.w, B, c.ci, c.co,
                        H, W);
     hipLaunchKernelGGL(k_bias_grad, dim3(c.co), dim3(256), 0, n->stream, dy, n->G + c.b, B, c.co, (size_t)H * W);
   }
 }
 
-void relu_bwd(hp_unet n, const float* y, float* dy, size_t count) {
-  hipLaunchKernelGGL(k_relu_bwd, dim3(eblocks(count)), dim3(256), 0, n->stream, y, dy, count);
+// The input of dec_a[l], [upsampled low, enc2[l]].  The bf16 kernels read it where it lies
+// when a 32-channel chunk and an aligned group of four pixels fall into one part and lane
+// offsets fit 32 bits; otherwise, and in float32, forward() has written it to up[l] (batch 8,
+// 256 x 256, 64 + 32 channels: 107 + 41 us for that and 87 for its bf16 copy, against 53 for
+// the copy from the parts).
+bool reads_parts(hp_unet n, int l, int H, int W) {
+  return n->bf16 && ch(n, l + 1) % mf::CK == 0 && (W >> l) % 8 == 0 &&
+         (size_t)(H >> l) * (W >> l) < ((size_t)1 << 27);
+}
+ConvIn dec_input(hp_unet n, int l, int H, int W) {
+  if (!reads_parts(n, l, H, W)) return plain(n->up[l]);
+  return ConvIn{n->enc2[l], l + 2 == n->levels ? n->enc2[l + 1] : n->dec2[l + 1], ch(n, l + 1)};
 }
 
 int forward(hp_unet n, const float* x, int B, int H, int W) {
@@ -1023,8 +1146,8 @@ int forward(hp_unet n, const float* x, int B, int H, int W) {
   const float* in = x;
   for (int l = 0; l < L; ++l) {
     const int h = H >> l, w = W >> l;
-    conv3(n, in, n->enc_a[l], n->enc1[l], B, h, w, 1);
-    conv3(n, n->enc1[l], n->enc_b[l], n->enc2[l], B, h, w, 1);
+    conv3(n, plain(in), n->enc_a[l], n->enc1[l], B, h, w);
+    conv3(n, plain(n->enc1[l]), n->enc_b[l], n->enc2[l], B, h, w);
     if (l + 1 < L) {
       const size_t planes = (size_t)B * ch(n, l);
       hipLaunchKernelGGL(k_pool, dim3(eblocks(planes * h * w / 4)), dim3(256), 0, n->stream, n->enc2[l], n->pool[l],
@@ -1036,17 +1159,18 @@ int forward(hp_unet n, const float* x, int B, int H, int W) {
   for (int l = L - 2; l >= 0; --l) {
     const int h = H >> l, w = W >> l;
     const int cu = ch(n, l + 1), cs = ch(n, l), ct = cu + cs;
-    hipLaunchKernelGGL(k_up, dim3(eblocks((size_t)B * cu * h * w)), dim3(256), 0, n->stream, cur, n->up[l], B, cu,
-                       ct, 0, h / 2, w / 2);
-    hipLaunchKernelGGL(k_chcopy, dim3(eblocks((size_t)B * cs * h * w)), dim3(256), 0, n->stream, n->up[l],
-                       n->enc2[l], B, cs, ct, cu, (size_t)h * w, 0);
-    conv3(n, n->up[l], n->dec_a[l], n->dec1[l], B, h, w, 1);
-    conv3(n, n->dec1[l], n->dec_b[l], n->dec2[l], B, h, w, 1);
+    if (!reads_parts(n, l, H, W)) {
+      hipLaunchKernelGGL(k_up, dim3(eblocks((size_t)B * cu * h * w)), dim3(256), 0, n->stream, cur, n->up[l], B, cu,
+                         ct, 0, h / 2, w / 2);
+      hipLaunchKernelGGL(k_chcopy, dim3(eblocks((size_t)B * cs * h * w)), dim3(256), 0, n->stream, n->up[l],
+                         n->enc2[l], B, cs, ct, cu, (size_t)h * w);
+    }
+    conv3(n, dec_input(n, l, H, W), n->dec_a[l], n->dec1[l], B, h, w);
+    conv3(n, plain(n->dec1[l]), n->dec_b[l], n->dec2[l], B, h, w);
     cur = n->dec2[l];
   }
   const size_t pl0 = (size_t)H * W;
-  hipLaunchKernelGGL(k_conv1, dim3(eblocks((size_t)B * pl0)), dim3(256), 0, n->stream, cur, n->P + n->out.w,
-                     n->P + n->out.b, n->y, B, n->out.ci, n->out.co, pl0, 0);
+  conv1(n, cur, n->P + n->out.b, nullptr, n->y, B, n->out.ci, n->out.co, pl0, 0);
   return HP_OK;
 }
 
@@ -1066,39 +1190,35 @@ void backward(hp_unet n, const float* x) {
     hipLaunchKernelGGL(k_wgrad_sum, dim3((unsigned)((ne + 63) / 64)), dim3(64 * wgm::SUM_WAVES), 0, n->stream,
                        n->wgpart, n->G + n->out.w, (size_t)ne, ns);
   }
-  hipLaunchKernelGGL(k_conv1, dim3(eblocks((size_t)B * pl0)), dim3(256), 0, n->stream, n->dy, n->P + n->out.w,
-                     nullptr, ga, B, n->out.co, n->out.ci, pl0, 1);
-  // decoder, top level first: ga = gradient w.r.t. dec2[l]
+  // each gradient below is stored already multiplied by its ReLU's derivative
+  conv1(n, n->dy, nullptr, top, ga, B, n->out.co, n->out.ci, pl0, 1);
+  // decoder, top level first: ga = gradient before the ReLU of dec2[l]
   for (int l = 0; l < L - 1; ++l) {
     const int h = H >> l, w = W >> l;
-    const size_t pl = (size_t)h * w;
-    const int cu = ch(n, l + 1), cs = ch(n, l), ct = cu + cs;
-    relu_bwd(n, n->dec2[l], ga, (size_t)B * cs * pl);
-    conv3_bwd(n, n->dec1[l], ga, n->dec_b[l], gb, B, h, w);
-    relu_bwd(n, n->dec1[l], gb, (size_t)B * cs * pl);
-    conv3_bwd(n, n->up[l], gb, n->dec_a[l], ga, B, h, w);  // ga = gradient w.r.t. up[l]
-    hipLaunchKernelGGL(k_chcopy, dim3(eblocks((size_t)B * cs * pl)), dim3(256), 0, n->stream, ga, n->dskip[l], B, cs,
-                       ct, cu, pl, 1);
-    hipLaunchKernelGGL(k_up_bwd, dim3(eblocks((size_t)B * cu * pl / 4)), dim3(256), 0, n->stream, ga, gb, B, cu, ct,
-                       0, h / 2, w / 2);
-    std::swap(ga, gb);  // ga = gradient w.r.t. the level below's output
+    const int cu = ch(n, l + 1), cs = ch(n, l);
+    const ConvOut to_dec1{nullptr, n->dec1[l], gb, nullptr, cs, 0};
+    conv3_bwd(n, plain(n->dec1[l]), ga, n->dec_b[l], &to_dec1, B, h, w);
+    const ConvOut to_parts{nullptr, nullptr, ga, n->dskip[l], cu, 0};  // ga = gradient w.r.t. the upsampled part
+    conv3_bwd(n, dec_input(n, l, H, W), gb, n->dec_a[l], &to_parts, B, h, w);
+    const size_t planes = (size_t)B * cu;
+    hipLaunchKernelGGL(k_up_bwd, dim3(eblocks(planes * h * w / 4)), dim3(256), 0, n->stream, ga,
+                       l + 2 == L ? n->enc2[l + 1] : n->dec2[l + 1], gb, planes, h / 2, w / 2);
+    std::swap(ga, gb);  // ga = gradient before the ReLU of the level below's output
   }
-  // encoder, bottom level first: ga = gradient w.r.t. enc2[L-1], then w.r.t. pool[l]
+  // encoder, bottom level first: ga = gradient before the ReLU of enc2[L-1], then w.r.t. pool[l]
   for (int l = L - 1; l >= 0; --l) {
     const int h = H >> l, w = W >> l;
-    const size_t pl = (size_t)h * w;
     const int c = ch(n, l);
     if (l < L - 1) {
-      hipLaunchKernelGGL(k_pool_bwd, dim3(eblocks((size_t)B * c * pl)), dim3(256), 0, n->stream, ga, gb,
-                         (size_t)B * c, h, w);
-      hipLaunchKernelGGL(k_add, dim3(eblocks((size_t)B * c * pl)), dim3(256), 0, n->stream, gb, n->dskip[l],
-                         (size_t)B * c * pl);
+      const size_t planes = (size_t)B * c;
+      hipLaunchKernelGGL(k_pool_bwd, dim3(eblocks(planes * h * w)), dim3(256), 0, n->stream, ga, n->dskip[l],
+                         n->enc2[l], gb, planes, h, w);
       std::swap(ga, gb);
     }
-    relu_bwd(n, n->enc2[l], ga, (size_t)B * c * pl);
-    conv3_bwd(n, n->enc1[l], ga, n->enc_b[l], gb, B, h, w);
-    relu_bwd(n, n->enc1[l], gb, (size_t)B * c * pl);
-    conv3_bwd(n, l == 0 ? x : n->pool[l - 1], gb, n->enc_a[l], l == 0 ? nullptr : ga, B, h, w);
+    const ConvOut to_enc1{nullptr, n->enc1[l], gb, nullptr, c, 0};
+    conv3_bwd(n, plain(n->enc1[l]), ga, n->enc_b[l], &to_enc1, B, h, w);
+    const ConvOut to_pool{nullptr, nullptr, ga, nullptr, n->enc_a[l].ci, 0};
+    conv3_bwd(n, plain(l == 0 ? x : n->pool[l - 1]), gb, n->enc_a[l], l == 0 ? nullptr : &to_pool, B, h, w);
   }
 }
 

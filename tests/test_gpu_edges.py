@@ -117,3 +117,45 @@ def test_weight_gradient_exact_at_segment_edges(base, B, H, W):
     assert np.abs(rg * y.size / 2.0 - ints).max() < 1e-6 and np.abs(ints).max() < 2**16
     assert np.array_equal(g[w], (sb * ints[w]).astype(np.float32).astype(np.float64))
     assert np.abs(g[b] - s * ints[b]).max() <= y.size * 2.0**-24 * s * y.size
+
+
+@pytest.mark.parametrize("base,B,H,W", [(16, 1, 2, 16), (16, 2, 16, 64), (32, 1, 8, 32), (16, 4, 8, 128), (16, 2, 8, 8),
+                                        (8, 2, 8, 16), (16, 2, 8, 4)])
+def test_two_level_gradient_exact_on_small_integers(base, B, H, W):
+    """bf16 forward and reverse pass of a two-level net on weights so sparse (two of a channel's
+    are +-1), and inputs and output errors so small, that every operand the matrix cores see has at
+    most 8 significant bits (checked on the oracle's) and every sum is exact: the loss and all
+    gradients equal the oracle's bit for bit.  Base 16 and 32: the decoder reads the upsampled and
+    the skip part where they lie (rows of 8, 16, 32, 64, 128 pixels); base 8 and rows of 4: from the
+    concatenation.  16, 32, 48 and 96 channels: odd and even numbers of 32."""
+    _cuda()
+    from oracle import unet as ounet
+    from paper_2410_17446_amd.unet import HP_UNET_BF16, UNet
+    rng = np.random.default_rng(base + W)
+    cin = 3
+    net = UNet(2, base, cin, 1, seed=0, precision=HP_UNET_BF16)
+    p = np.zeros(net.nparam, np.float32)
+    layers = ounet.layout(2, base, cin, 1)
+    for c in [*layers[0], *layers[1], *layers[2], *layers[3]]:
+        for o in range(c.co):
+            for i in rng.choice(c.ci * 9, 2, replace=False):
+                p[c.w + o * c.ci * 9 + i] = rng.choice([1.0, 1.0, -1.0])
+    p[layers[4].w:layers[4].b] = rng.integers(-1, 2, base)
+    net.load_state(p)
+    ref = ounet.UNet(2, base, cin, 1, p.astype(np.float64))
+    x = rng.integers(-1, 3, size=(B, cin, H, W)).astype(np.float64)
+    y, cache = ref.forward(x)
+    t = y - rng.integers(-1, 2, size=y.shape) * (rng.random(y.shape) < 0.25)
+    seen = []
+    inner = ounet.conv3_backward
+    ounet.conv3_backward = lambda xx, w, dy: (seen.extend([xx, dy]), inner(xx, w, dy))[1]
+    try:
+        loss, g = ref.loss_and_grad(x, t)
+    finally:
+        ounet.conv3_backward = inner
+    for a in seen:
+        m, _ = np.frexp(a)
+        assert np.array_equal(np.rint(m * 256), m * 256)
+    lg = net.grad(to_gpu(x.astype(np.float32)), to_gpu(t.astype(np.float32)))
+    assert np.count_nonzero(g) > g.size // 100
+    assert lg == loss and np.array_equal(net.state()["grads"].astype(np.float64), g)
