@@ -67,7 +67,8 @@ struct RowCfg {
 // LDS budget of a column workgroup's transform buffers, which sets how many
 // columns it transforms at once.  Three budgets are built; the plan uses the
 // middle one (two complex128 columns of 1024 per workgroup, four workgroups per
-// CU) unless hp_autotune measured another to be faster for its shape.
+// CU; the largest for long complex128 vector columns, see launch_col) unless
+// hp_autotune measured another to be faster for its shape.
 constexpr int kColLds[3] = {20480, 40960, 81920};
 
 template <typename T, typename C, int N, int LB = 40960>
@@ -1562,7 +1563,7 @@ void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi,
     if (g.ncomp == 1)                                                                                          \
       hipLaunchKernelGGL((k_col<T, C, NN, 1, LB, MODE>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, IN, OUT,  \
                          OSP, OSI, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
-    else                                                                                                       \
+    else if constexpr (LB != kColLds[1] || !WIDE_(NN, 2))                                                      \
       hipLaunchKernelGGL((k_col<T, C, NN, 2, LB, MODE>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, IN, OUT,  \
                          OSP, OSI, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
   }
@@ -1586,11 +1587,18 @@ void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi,
     }                                                                                                          \
     COLM_(NN, LB, COL_WHOLE, list.n, basis, zbase, zsp, zsi)                                                   \
   }
+  // Complex128 vector fields with columns of 1024 and more take the largest budget in the
+  // middle variant too: their pass writes twice what it reads, and one or two columns at a
+  // time are a small part of each line (a step, 40 and 80 KB: 2048^2 with 8 poles, 13.90 and
+  // 12.93 ms; with 12, 1024 x 2048, 9.23 and 8.48; 1536^2, 12.41 and 11.93; 512 x 1024, 2.14 and
+  // 2.13; columns of 768 and 384, 1.63 and 1.72, 0.80 and 0.84; scalar fields at 1024^2, 1.53 and
+  // 1.55; complex64 storage, 2-6 % more).
+#define WIDE_(NN, NCOMP) ((NCOMP) == 2 && sizeof(T) == sizeof(double) && (NN) >= 1024)
 #define L_(NN)                                                                                                 \
   {                                                                                                            \
     if (g.col_variant == 0)                                                                                    \
       COLV_(NN, kColLds[0])                                                                                    \
-    else if (g.col_variant == 2)                                                                               \
+    else if (g.col_variant == 2 || WIDE_(NN, g.ncomp))                                                         \
       COLV_(NN, kColLds[2])                                                                                    \
     else                                                                                                       \
       COLV_(NN, kColLds[1])                                                                                    \
@@ -1599,6 +1607,7 @@ void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi,
 #undef L_
 #undef COLV_
 #undef COLM_
+#undef WIDE_
 }
 
 static int apply_groups(const Geo& g) {
