@@ -159,3 +159,63 @@ def test_two_level_gradient_exact_on_small_integers(base, B, H, W):
     lg = net.grad(to_gpu(x.astype(np.float32)), to_gpu(t.astype(np.float32)))
     assert np.count_nonzero(g) > g.size // 100
     assert lg == loss and np.array_equal(net.state()["grads"].astype(np.float64), g)
+
+
+@pytest.mark.parametrize("sample", [0, 1, 255, 256, 16383, 16384, 50000, 99999, 100000])
+def test_stability_check_sees_every_sample(sample):
+    """One pole 1e-3 beside one sample of the free-space spectrum's interval: |r| there is the
+    residue over 1e-3 and smaller at all others, so a residue 1e-9 above or below the limit
+    1 + 1e-6 decides the status (the quotient is rounded at 1e-16).  First and last sample, the
+    edges of workgroups and of the grid's stride of 64 x 256."""
+    _cuda()
+    from paper_2410_17446_amd import hp
+    wl = workload(N=64, W=8)
+    g = oracle_grid(wl)
+    mu = precond.mu(g.N, g.dx, g.c, g.s)
+    lo, hi = 2 * mu.min(), 2 * mu.max()
+    z = lo + (hi - lo) * sample / 100000.0
+    poles = wl["fit"]["poles"].copy()
+    poles[0] = z - 1e-3j
+    for amp, status in ((1 + 1e-6 + 1e-9, hp.HP_WARN_UNSTABLE), (1 + 1e-6 - 1e-9, hp.HP_OK)):
+        res = np.zeros_like(poles)
+        res[0] = 1e-3 * amp
+        plan = gpu_plan(dict(wl, fit=dict(poles=poles, residues=res, r_inf=0.0)))
+        assert plan.create_status == status
+        plan.close()
+
+
+@pytest.mark.parametrize("ncomp,nx,ny,precision", [(1, 64, 64, 0), (2, 64, 128, 0), (1, 128, 64, 1), (2, 64, 64, 2)])
+def test_workspace_contents_do_not_matter(ncomp, nx, ny, precision):
+    """A plan in a caller's workspace full of NaN steps bit for bit like one in its own."""
+    torch = _cuda()
+    from paper_2410_17446_amd import hp
+    wl = workload(N=nx, ny=ny, ncomp=ncomp, W=8, medium=("sine", 0.02, 1.0), w0=2.0, tol=1e-8)
+    f, outs, ws = wl["fit"], [], None
+    for garbage in (False, True):
+        plan = hp.Plan(nx=nx, ny=ny, dx=0.25, dy=0.25, k0=inputs.K0, n0=1.0, dz=1.0, ncomp=ncomp, poles=f["poles"],
+                       residues=f["residues"], r_inf=f["r_inf"], d2=wl["c"], d1=wl["d"], edge_width=8, edge_eta=0.25,
+                       tol=1e-8, precision=precision, workspace=ws)
+        outs.append(plan.step(to_gpu(wl["w"]), to_gpu(wl["n2"])).cpu().numpy())
+        if not garbage:
+            ws = torch.full((plan.workspace_bytes(),), 255, dtype=torch.uint8, device="cuda")
+        plan.close()
+    assert np.isfinite(outs[0]).all() and np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("ncomp,nx,ny,npoles", [(2, 128, 1024, 8), (1, 512, 512, 8), (1, 256, 1024, 16), (2, 64, 2048, 8)])
+def test_shared_first_column_transform(ncomp, nx, ny, npoles):
+    """Rounds of 2^21 elements and more over the poles that start from the shared first vector
+    transform it once; a pole solved alone transforms it by itself.  Two Arnoldi steps of each,
+    in which only that differs: equal to 64 eps log2(ny) over the residual polynomial's
+    condition, here below 10."""
+    _cuda()
+    wl = workload(N=nx, ny=ny, ncomp=ncomp, W=8, npoles=npoles, medium=("sine", 0.02, 1.0), w0=2.0, tol=1e-8)
+    plan = gpu_plan(wl)
+    plan.set_fixed_iters([2] * npoles)
+    w, n2 = to_gpu(wl["w"]), to_gpu(wl["n2"])
+    plan.step(w, n2)
+    got = [plan.solution(k).cpu().numpy() for k in range(npoles)]
+    for k in (0, npoles // 2, npoles - 1):
+        alone = plan.solve(k, w).cpu().numpy()
+        assert rel_l2(got[k], alone) <= 10 * 64 * np.finfo(float).eps * np.log2(ny), k
+    plan.close()
