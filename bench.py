@@ -46,7 +46,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 SQRT_TERMS, SQRT_ALPHA, SQRT_SUBSTEPS = 25, 1.0, 8
-KERNEL_SOURCES = ("kernels.hip", "fft.hpp", "cplx.hpp", "state.hpp", "kernels.hpp")
+KERNEL_SOURCES = ("kernels.hip", "fft.hpp", "wave.hpp", "cplx.hpp", "state.hpp", "kernels.hpp")
 COUNTERS = os.path.join(ROOT, "profiles", "row_apply_scalar1024_fp64_hbm_counters.md")
 
 
