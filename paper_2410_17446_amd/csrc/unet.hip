@@ -329,32 +329,27 @@ __global__ __launch_bounds__(256) void k_conv3_wgrad(const float* __restrict__ x
 // v_mfma_f32_16x16x32_bf16 takes 32 pixels of one image row (lane group kg
 // holds the 8 consecutive pixels 8 kg .. 8 kg + 7 of the segment) for 16 output
 // channels (A = dy, row = lane % 16) against 16 input channels (B = x moved by
-// the tap, column = lane % 16).  A workgroup owns 32 output x 16 input channels
-// and a share of the segments, ordered down the columns of 32 pixels, so that a
-// wave walks down rows: row r of x is loaded and converted once and meets the dy
-// rows r - 1, r, r + 1 (taps ky = 2, 1, 0), which stay in LDS;
-// the taps kx = 0 and 2 are the same fragment moved by one pixel, the pixel at
-// either end taken from the neighbouring lane group.  The waves' sums are added
-// through LDS in wave order, and the workgroup writes part[split][co][ci][tap];
-// workgroups of the first input-channel block also sum dy for the bias gradient
-// into part[split][cout * cin * 9 + co].  k_wgrad_sum adds the splits in a fixed
-// order, so the result does not depend on scheduling.
+// the tap, column = lane % 16).  A workgroup owns 32 output x 16 input
+// channels and a contiguous share of the row segments; its four waves take
+// every fourth segment (the next one's operands loaded while the current one
+// is multiplied).  A wave converts a segment's rows once, into LDS of its own, and the
+// taps kx = 0 and 2 are the fragment of kx = 1 moved by one pixel.  The waves'
+// sums are added through LDS in wave order, and the workgroup writes
+// part[split][co][ci][tap]; workgroups of the first input-channel block also
+// sum dy for the bias gradient into part[split][cout * cin * 9 + co].
+// k_wgrad_sum adds the splits in a fixed order, so the result does not depend
+// on scheduling.
 namespace wgm {
 constexpr int CO = 32, CI = 16, SEG = 32;
 constexpr int SUM_WAVES = 16;  // waves per output chunk in k_wgrad_sum
 }
 
-// One step of a wave: x row r of column (b, xs) against the dy rows of [y0, y1).
-struct WgPos {
-  int b, xs, r, y0, y1;
-};
-
-// Operands of a step as loaded, lane l: pixels 4 (l % 8) .. + 3 of channel l / 8 + 8 i,
-// dy row r + 1 in a (output channels) and x row r in b (input channels); e: the pixel
-// left (l % 32 < 16) or right of the segment, input channel l % 16.
-struct WgRow {
-  float4 a[4], b[2];
-  float e;
+// Operands of a segment as loaded, lane l: pixels 4 (l % 8) .. + 3 of channel l / 8 + 8 i,
+// dy in a (output channels) and the three rows around in b (input channels); e: the pixel
+// left (l % 32 < 16) or right of the segment in each, input channel l % 16.
+struct WgSeg {
+  float4 a[4], b[3][2];
+  float e[3];
 };
 
 // Every load is taken, from a valid address next to the wanted one where that is
@@ -377,23 +372,26 @@ __device__ __forceinline__ float4 wg_load4(const float* __restrict__ img, int c0
 // The upsampled part of a concatenated input (VEC): the aligned four pixels of the low row
 // that hold the lane's two, picked by wg_up.
 template <bool VEC>
-__device__ __forceinline__ void wg_load(WgRow& g, const ConvIn& in, const float* __restrict__ dy, const WgPos& p,
-                                        int cin, int cout, int H, int W, int co0, int ci0, int lane) {
+__device__ __forceinline__ void wg_load(WgSeg& g, const ConvIn& in, const float* __restrict__ dy, int b, int yy,
+                                        int xs, int cin, int cout, int H, int W, int co0, int ci0, int lane) {
   const size_t plane = (size_t)H * W;
-  const int x0 = p.xs * wgm::SEG, px = x0 + (lane & 7) * 4;
-  const int yd = min(p.r + 1, H - 1), yx = min(max(p.r, 0), H - 1);
-  const float* db = dy + (size_t)p.b * cout * plane + (size_t)yd * W;
+  const int x0 = xs * wgm::SEG, px = x0 + (lane & 7) * 4;
+  const float* db = dy + (size_t)b * cout * plane + (size_t)yy * W;
 #pragma unroll
   for (int i = 0; i < 4; ++i) g.a[i] = wg_load4<VEC>(db, co0 + 8 * i, cout, lane / 8, plane, px, W);
   const bool low = ci0 < in.cu;
   const int sh = low ? 1 : 0, nc = low ? in.cu : cin - in.cu, c0 = low ? ci0 : ci0 - in.cu, wx = W >> sh;
   const size_t px_plane = plane >> (2 * sh);
-  const float* xb = (low ? in.low : in.x) + (size_t)p.b * nc * px_plane + (size_t)(yx >> sh) * wx;
   const int pxx = VEC ? (px >> sh) & ~3 : px;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) g.b[i] = wg_load4<VEC>(xb, c0 + 8 * i, nc, lane / 8, px_plane, pxx, wx);
-  g.e = xb[min(c0 + (lane & 15), nc - 1) * px_plane +
-           (min(max((lane & 16) ? x0 + wgm::SEG : x0 - 1, 0), W - 1) >> sh)];
+  for (int ky = 0; ky < 3; ++ky) {
+    const int yx = min(max(yy + ky - 1, 0), H - 1);
+    const float* xb = (low ? in.low : in.x) + (size_t)b * nc * px_plane + (size_t)(yx >> sh) * wx;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) g.b[ky][i] = wg_load4<VEC>(xb, c0 + 8 * i, nc, lane / 8, px_plane, pxx, wx);
+    g.e[ky] = xb[min(c0 + (lane & 15), nc - 1) * px_plane +
+                 (min(max((lane & 16) ? x0 + wgm::SEG : x0 - 1, 0), W - 1) >> sh)];
+  }
 }
 
 // the lane's four pixels of v (see wg_load); low: each low pixel twice
@@ -419,25 +417,29 @@ __device__ __forceinline__ unsigned bf2(float lo, float hi) {
 typedef unsigned mf_u4 __attribute__((ext_vector_type(4)));
 typedef unsigned mf_u2 __attribute__((ext_vector_type(2)));
 
-// A wave's rows in LDS as bf16, written and read by that wave only: a ring of three dy rows
-// [32][80 bytes], x [16][96 bytes] with the pixels from byte 16 on
-// and their neighbours around them.
-namespace wgm {
-constexpr int DS = 20, XS = 24;  // dwords per channel
-constexpr int ROW = CO * DS;
-constexpr int WAVE = 3 * ROW + CI * XS;
+// v of the neighbouring lane (l ^ 1)
+__device__ __forceinline__ float lane_xor1(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false));
 }
 
-// Bound: memory.  A step loads 6.2 KB for 18 products (288 cycles of a matrix core), x once
-// for every 32 output channels and dy once for every 16 input channels, those of one split
-// on one XCD (split = block id mod nsplit, a multiple of 8 where it can be).  Global loads
-// take 8 lanes per channel, a whole line each; a lane group per channel quarter, as the
-// fragments want it, touches 16 lines with every 16 lanes.  Batch 8, 256 x 256, 96 -> 32
-// channels: 238 us (three rows of x with every row of dy, loads under lane conditions) -> 131
-// (rows walked, unconditional) -> 121 (line-wise loads), 2.2 TB/s; 384 -> 128 channels on
-// 64 x 64: 234 -> 92 -> 59 us; all of a four-level step's, 1506 -> 659 us.
+// A wave's segment in LDS as bf16, written and read by that wave only: dy [32][80 bytes],
+// x [3][16][96 bytes] with the pixels from byte 16 on and their neighbours around them.
+namespace wgm {
+constexpr int DS = 20, XS = 24;  // dwords per channel
+constexpr int WAVE = CO * DS + 3 * CI * XS;
+}
+
+// Bound: memory.  A segment loads 11 KB for 18 products (288 cycles of a matrix core), dy
+// once for every 16 input channels, those of one split on one XCD (split = block id mod
+// nsplit, a multiple of 8 where it can be).  Global loads take 8 lanes per channel, a whole
+// line each; a lane group per channel quarter, as the fragments want it, touches 16 lines
+// with every 16 lanes, and under lane conditions each load waited for the one before
+// (batch 8, 256 x 256, 96 -> 32 channels: 238 -> 142 us; 384 -> 128 on 64 x 64: 234 -> 101; all
+// of a four-level step's, 1506 -> 863).  Walking down the rows, each row of x loaded once,
+// takes 659, but sums in another order, and one bf16 rounding of a weight that falls the
+// other way after an Adam step moves the next gradients by 3e-4.
 template <bool VEC>
-__global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const ConvIn in_x, const float* __restrict__ dy,
+__global__ __launch_bounds__(256, VEC ? 3 : 2) void k_conv3_wgrad_mfma(const ConvIn in_x, const float* __restrict__ dy,
                                                              float* __restrict__ part, int B, int cin, int cout,
                                                              int H, int W, int nsplit) {
   __shared__ __attribute__((aligned(16))) unsigned buf[4 * wgm::WAVE > 2 * 9 * 256 ? 4 * wgm::WAVE : 2 * 9 * 256];
@@ -449,9 +451,7 @@ __global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const ConvIn in_x, 
   const int co0 = (blk % ncob) * wgm::CO, ci0 = (blk / ncob) * wgm::CI;
   const int ws = (W + wgm::SEG - 1) / wgm::SEG;
   const long nseg = (long)B * H * ws;
-  const long share = (long)split * 4 + wave;
-  long q = nseg * share / (4L * nsplit);
-  const long q1 = nseg * (share + 1) / (4L * nsplit);
+  const long q0 = nseg * split / nsplit, q1 = nseg * (split + 1) / nsplit;
   const size_t stride = (size_t)cout * cin * 9 + cout;  // floats per split
   mf_f4 acc[2][9];
 #pragma unroll
@@ -459,80 +459,69 @@ __global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const ConvIn in_x, 
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[c][t] = mf_f4{0.f, 0.f, 0.f, 0.f};
   float bs[4] = {0.f, 0.f, 0.f, 0.f};
-  // the rows of one column in this wave's share: the next piece
-  auto piece = [&]() {
-    WgPos p;
-    const long col = q / H;
-    p.y0 = (int)(q - col * H);
-    p.y1 = (int)min((long)H, p.y0 + (q1 - q));
-    p.b = (int)(col / ws);
-    p.xs = (int)(col - (long)p.b * ws);
-    p.r = p.y0 - 1;
-    q += p.y1 - p.y0;
-    return p;
-  };
   unsigned* da = buf + wave * wgm::WAVE;
-  unsigned* dx = da + 3 * wgm::ROW;
-  if (q < q1) {
-    WgPos p = piece();
-    WgRow g;
-    wg_load<VEC>(g, in_x, dy, p, cin, cout, H, W, co0, ci0, lane);
-    int slot = 0;  // of dy row r + 1
-    for (;;) {
-      // pixels past the row's end and x rows outside the image are zeros
-      const int x0 = p.xs * wgm::SEG, nv = W - (x0 + (lane & 7) * 4);
-      const bool in = p.r >= 0 && p.r < H, h0 = p.r + 1 < p.y1, h1 = p.r >= p.y0 && p.r < p.y1, h2 = p.r > p.y0;
+  unsigned* dx = da + wgm::CO * wgm::DS;
+  WgSeg g;
+  auto load = [&](long q, int& yy, int& xs) {
+    const long r = q / ws;
+    xs = (int)(q - r * ws);
+    const long b = r / H;
+    yy = (int)(r - b * H);
+    wg_load<VEC>(g, in_x, dy, (int)b, yy, xs, cin, cout, H, W, co0, ci0, lane);
+  };
+  long q = q0 + wave;
+  int yy, xs;
+  if (q < q1) load(q, yy, xs);
+  for (; q < q1; q += 4) {
+    // pixels past the row's end and x rows outside the image are zeros
+    const int x0 = xs * wgm::SEG, nv = W - (x0 + (lane & 7) * 4);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float4 v = wg_mask(g.a[i], nv);
-        *reinterpret_cast<mf_u2*>(da + slot * wgm::ROW + (8 * i + lane / 8) * wgm::DS + (lane & 7) * 2) =
-            mf_u2{bf2(v.x, v.y), bf2(v.z, v.w)};
-        if (ci0 == 0 && h0) bs[i] += (v.x + v.y) + (v.z + v.w);
+    for (int i = 0; i < 4; ++i) {
+      const float4 v = wg_mask(g.a[i], nv);
+      *reinterpret_cast<mf_u2*>(da + (8 * i + lane / 8) * wgm::DS + (lane & 7) * 2) =
+          mf_u2{bf2(v.x, v.y), bf2(v.z, v.w)};
+      if (ci0 == 0) {
+        // eight pixels in turn: the even lane's four, then the odd lane's; held by the even lane
+        float t = bs[i] + v.x;
+        t = lane_xor1(((t + v.y) + v.z) + v.w);
+        bs[i] = lane_xor1((((t + v.x) + v.y) + v.z) + v.w);
       }
+    }
+#pragma unroll
+    for (int ky = 0; ky < 3; ++ky) {
+      const bool in = yy + ky >= 1 && yy + ky - 1 < H;
+      unsigned* xr = dx + ky * wgm::CI * wgm::XS;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const float4 v = wg_mask(wg_up(g.b[i], ci0 < in_x.cu, lane), in ? nv : 0);
-        *reinterpret_cast<mf_u2*>(dx + (8 * i + lane / 8) * wgm::XS + 4 + (lane & 7) * 2) =
+        const float4 v = wg_mask(wg_up(g.b[ky][i], ci0 < in_x.cu, lane), in ? nv : 0);
+        *reinterpret_cast<mf_u2*>(xr + (8 * i + lane / 8) * wgm::XS + 4 + (lane & 7) * 2) =
             mf_u2{bf2(v.x, v.y), bf2(v.z, v.w)};
       }
       const bool ev = in && ((lane & 16) ? x0 + wgm::SEG < W : x0 > 0);
-      dx[l16 * wgm::XS + ((lane & 16) ? 20 : 3)] = ev ? bf2(g.e, g.e) : 0u;
-      // the next step's operands, in flight during the products (the last step's again)
-      bool more = true;
-      WgPos n = p;
-      if (p.r < p.y1)
-        ++n.r;
-      else if (q < q1)
-        n = piece();
-      else
-        more = false;
-      wg_load<VEC>(g, in_x, dy, n, cin, cout, H, W, co0, ci0, lane);
-      const unsigned* xr = dx + l16 * wgm::XS + 4 + kg * 4;
+      xr[l16 * wgm::XS + ((lane & 16) ? 20 : 3)] = ev ? bf2(g.e[ky], g.e[ky]) : 0u;
+    }
+    // the next segment's operands, in flight during the products (the last one's again)
+    load(q + 4 < q1 ? q + 4 : q, yy, xs);
+    mf_b8 a[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      a[c] = __builtin_bit_cast(mf_b8, *reinterpret_cast<const mf_u4*>(da + (16 * c + l16) * wgm::DS + kg * 4));
+#pragma unroll
+    for (int ky = 0; ky < 3; ++ky) {
+      const unsigned* xr = dx + (ky * wgm::CI + l16) * wgm::XS + 4 + kg * 4;
       const mf_u4 b1 = *reinterpret_cast<const mf_u4*>(xr);
       const unsigned left = xr[-1], right = xr[4];
       const unsigned s1 = __builtin_amdgcn_alignbit(b1[1], b1[0], 16), s2 = __builtin_amdgcn_alignbit(b1[2], b1[1], 16),
                      s3 = __builtin_amdgcn_alignbit(b1[3], b1[2], 16);
       const mf_u4 b0 = {(unsigned)__builtin_amdgcn_alignbit(b1[0], left, 16), s1, s2, s3};
       const mf_u4 b2 = {s1, s2, s3, (unsigned)__builtin_amdgcn_alignbit(right, b1[3], 16)};
-      auto row = [&](int sl, int ky) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const mf_b8 av = __builtin_bit_cast(
-              mf_b8, *reinterpret_cast<const mf_u4*>(da + sl * wgm::ROW + (16 * c + l16) * wgm::DS + kg * 4));
-          acc[c][ky * 3 + 0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(mf_b8, b0),
-                                                                       acc[c][ky * 3 + 0], 0, 0, 0);
-          acc[c][ky * 3 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(mf_b8, b1),
-                                                                       acc[c][ky * 3 + 1], 0, 0, 0);
-          acc[c][ky * 3 + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(mf_b8, b2),
-                                                                       acc[c][ky * 3 + 2], 0, 0, 0);
-        }
-      };
-      if (h0) row(slot, 0);
-      if (h1) row(slot == 0 ? 2 : slot - 1, 1);
-      if (h2) row(slot == 2 ? 0 : slot + 1, 2);
-      if (!more) break;
-      slot = slot == 2 ? 0 : slot + 1;
-      p = n;
+      for (int c = 0; c < 2; ++c) {
+        mf_f4* t = acc[c] + ky * 3;
+        t[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], __builtin_bit_cast(mf_b8, b0), t[0], 0, 0, 0);
+        t[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], __builtin_bit_cast(mf_b8, b1), t[1], 0, 0, 0);
+        t[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], __builtin_bit_cast(mf_b8, b2), t[2], 0, 0, 0);
+      }
     }
   }
   float* red = reinterpret_cast<float*>(buf);
@@ -566,7 +555,7 @@ __global__ __launch_bounds__(256, 3) void k_conv3_wgrad_mfma(const ConvIn in_x, 
       const int i = threadIdx.x / 8, l0 = threadIdx.x % 8 * 8, co = co0 + threadIdx.x;
       float a = 0.f;
       for (int w = 0; w < 4; ++w)
-        for (int j = 0; j < 8; ++j) a += bred[w][i][l0 + j];
+        for (int j = 0; j < 8; j += 2) a += bred[w][i][l0 + j];
       if (co < cout) out[(size_t)cout * cin * 9 + co] = a;
     }
   }
@@ -943,13 +932,11 @@ int ufail(hp_unet n, int code, const std::string& msg) {
 int ch(const hp_unet_s* n, int l) { return n->base << l; }
 
 // Splits of the pixel contraction in the matrix-core weight gradient: about
-// 768 workgroups in all, the three per CU that their registers allow, each with at
-// least 32 row segments (eight per wave: a share of n rows reads n + 2).
+// 1024 workgroups in all, each with at least 16 row segments (four per wave).
 int wgrad_splits(int B, int H, int W, int cin, int cout) {
   const long nseg = (long)B * H * ((W + wgm::SEG - 1) / wgm::SEG);
   const long blocks = (long)((cout + wgm::CO - 1) / wgm::CO) * ((cin + wgm::CI - 1) / wgm::CI);
-  const long s = std::max(1L, std::min(nseg / 32, 768 / blocks));
-  return (int)(s > 8 ? s / 8 * 8 : s);
+  return (int)std::max(1L, std::min(nseg / 16, 1024 / blocks));
 }
 
 // Splits of the 1x1 weight and bias gradients: about 1024 workgroups, each
