@@ -279,8 +279,8 @@ int hp_fit_exp_sqrt(double K, int degree, int lawson_steps, void* stream, hp_c12
  *
  * Q, Qinv: host complex128 [N-1][N-1] row-major, lam: host complex128 [N-1],
  * N = nx = ny, for the unknowns 1..N-1 of one axis (computed by the caller,
- * e.g. by a dense eigensolver); the library copies them (2 N^2 complex128 on
- * the device) and checks on the host that Q diag(lam) Qinv reproduces its own
+ * e.g. by a dense eigensolver); the library copies them (3 N^2 complex128 on
+ * the device, with their parity halves) and checks on the host that Q diag(lam) Qinv reproduces its own
  * s D~ on two pseudo-random vectors to 1e-3 (HP_EINVAL otherwise; the dense
  * stages only precondition, since every Arnoldi step applies the explicit
  * stretched operator to the stored z, but wide layers with a weak sigma_max
