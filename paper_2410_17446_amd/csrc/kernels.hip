@@ -1424,23 +1424,43 @@ __global__ __launch_bounds__(256) void k_clear_rows(char* __restrict__ base, siz
     reinterpret_cast<double2*>(base + i / words * tile_bytes)[i % words] = make_double2(0.0, 0.0);
 }
 
+// a / b with b scaled by a power of two, so that |b|^2 neither overflows nor underflows; infinite
+// for b = 0 and a neither 0 nor a NaN, 0 for b infinite and a finite (cdiv gives NaN there).
+__device__ __forceinline__ c128 cdiv_scaled(c128 a, c128 b) {
+  const double big = fmax(fabs(b.re), fabs(b.im));
+  if (big == 0.0 && (fabs(a.re) > 0.0 || fabs(a.im) > 0.0)) return mk((double)INFINITY, 0.0);
+  if (isinf(big) && isfinite(a.re) && isfinite(a.im)) return mk(0.0, 0.0);
+  if (big == 0.0 || !isfinite(big)) return cdiv(a, b);
+  const int e = -ilogb(big);
+  return cdiv(mk(ldexp(a.re, e), ldexp(a.im, e)), mk(ldexp(b.re, e), ldexp(b.im, e)));
+}
+
+// Maxima of |f| over the samples.  A NaN counts for nothing where r itself is one, and as an
+// infinity where r is not (infinite terms of both signs met, or a finite r overflowed in the polynomial).
 __global__ __launch_bounds__(256) void k_spectrum_max(const SpectrumCheck c, double* __restrict__ out) {
   __shared__ double red[4];
   double best = 0.0;
   for (int i = blockIdx.x * 256 + threadIdx.x; i <= 100000; i += kSpectrumBlocks * 256) {
     const double z = c.lo + (c.hi - c.lo) * i / 100000.0;
     c128 r = c.r_inf;
-    for (int k = 0; k < c.npoles; ++k) r = r + cdiv(c.a[k], mk(z - c.b[k].re, -c.b[k].im));
-    if (c.hk != 0.0) {
+    bool over = false;  // a term or the sum so far infinite
+    for (int k = 0; k < c.npoles; ++k) {
+      const c128 t = cdiv_scaled(c.a[k], mk(z - c.b[k].re, -c.b[k].im));
+      r = r + t;
+      over = over || isinf(t.re) || isinf(t.im) || isinf(r.re) || isinf(r.im);
+    }
+    if (c.hk != 0.0 && !over) {
+      const bool number = r.re == r.re && r.im == r.im;
       const c128 x = mk(-c.hk * r.im, c.hk * (r.re - 1.0));  // i hk (r - 1)
       const c128 one = mk(1.0, 0.0);
       c128 q = mk(1.0 / 6.0, 0.0) + (1.0 / 24.0) * x;
       q = mk(0.5, 0.0) + x * q;
       q = one + x * q;
       r = one + x * q;
+      over = number && !(isfinite(r.re) && isfinite(r.im));
     }
-    const double v = sqrt(abs2(r));
-    if (v > best) best = v;  // a NaN counts for nothing
+    const double v = over ? INFINITY : sqrt(abs2(r));
+    if (v > best) best = v;
   }
   for (int off = 32; off > 0; off >>= 1) best = fmax(best, __shfl_down(best, off, 64));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = best;

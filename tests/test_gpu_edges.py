@@ -184,6 +184,50 @@ def test_stability_check_sees_every_sample(sample):
         plan.close()
 
 
+@pytest.mark.parametrize("sample", [1, 4095, 50001, 99999])
+def test_stability_check_counts_a_pole_on_a_sample(sample):
+    """A real pole exactly on a sample makes |r| infinite there, whatever its residue; one rounding of
+    the sample (1e-16) away a residue of 1e-300 is nothing.  The library's sample is within 16
+    roundings of the test's."""
+    _cuda()
+    from paper_2410_17446_amd import hp
+    wl = workload(N=64, W=8)
+    g = oracle_grid(wl)
+    mu = precond.mu(g.N, g.dx, g.c, g.s)
+    lo, hi = 2 * mu.min(), 2 * mu.max()
+    z = lo + (hi - lo) * sample / 100000.0
+    assert np.abs(mu[1:, None] + mu[None, 1:] - z).min() > 1e-12  # no eigenvalue: the table is accepted
+    hits = []
+    for ulp in range(-16, 17):
+        poles = wl["fit"]["poles"].copy()
+        poles[0] = z + ulp * np.spacing(abs(z))
+        res = np.zeros_like(poles)
+        res[0] = 1e-300
+        plan = gpu_plan(dict(wl, fit=dict(poles=poles, residues=res, r_inf=0.0)))
+        hits.append((plan.create_status, plan.set_form(hp.HP_FORM_SQRT, 4)))
+        plan.close()
+    # sqrt form: i h k0 n0 (0 - 1) on the RK4 circle is stable but for the sample hit
+    assert hits.count((hp.HP_WARN_UNSTABLE, hp.HP_WARN_UNSTABLE)) == 1
+    assert hits.count((hp.HP_OK, hp.HP_OK)) == len(hits) - 1
+
+
+@pytest.mark.parametrize("poles,residues,r_inf,create,form", [
+    ([1j], [1e100], 0.0, 2, 2),            # finite r whose fourth power is not
+    ([1j, 1j], [1e308, 1e308], 0.0, 2, 2),  # infinite sum of finite terms
+    ([np.inf, 1j], [1.0, 0.0], 0.5, 0, 0),  # a pole at infinity contributes nothing
+    ([np.inf, 1j], [1.0, 0.0], 2.0, 2, 0),
+    ([1j], [np.nan], 0.0, 0, 0)])          # NaN: nothing to say
+def test_stability_check_beyond_the_range_of_doubles(poles, residues, r_inf, create, form):
+    """Statuses where terms, sums or powers leave the range of doubles (status 2: unstable)."""
+    _cuda()
+    from paper_2410_17446_amd import hp
+    wl = workload(N=64, W=8)
+    plan = gpu_plan(dict(wl, fit=dict(poles=np.array(poles, complex), residues=np.array(residues, complex), r_inf=r_inf)))
+    assert plan.create_status == create
+    assert plan.set_form(hp.HP_FORM_SQRT, 8) == form
+    plan.close()
+
+
 @pytest.mark.parametrize("ncomp,nx,ny,precision", [(1, 64, 64, 0), (2, 64, 128, 0), (1, 128, 64, 1), (2, 64, 64, 2)])
 def test_workspace_contents_do_not_matter(ncomp, nx, ny, precision):
     """A plan in a caller's workspace full of NaN steps bit for bit like one in its own."""
