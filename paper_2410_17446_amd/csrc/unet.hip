@@ -422,6 +422,15 @@ __device__ __forceinline__ float lane_xor1(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, false));
 }
 
+// Orders a wave's LDS accesses before and after it for the lanes of that wave (its LDS
+// instructions run in order, so it costs nothing; without it the compiler may move one
+// lane's read above another lane's write).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // A wave's segment in LDS as bf16, written and read by that wave only: dy [32][80 bytes],
 // x [3][16][96 bytes] with the pixels from byte 16 on and their neighbours around them.
 namespace wgm {
@@ -500,6 +509,7 @@ __global__ __launch_bounds__(256, VEC ? 3 : 2) void k_conv3_wgrad_mfma(const Con
       const bool ev = in && ((lane & 16) ? x0 + wgm::SEG < W : x0 > 0);
       xr[l16 * wgm::XS + ((lane & 16) ? 20 : 3)] = ev ? bf2(g.e[ky], g.e[ky]) : 0u;
     }
+    wave_lds_order();
     // the next segment's operands, in flight during the products (the last one's again)
     load(q + 4 < q1 ? q + 4 : q, yy, xs);
     mf_b8 a[2];
@@ -523,6 +533,7 @@ __global__ __launch_bounds__(256, VEC ? 3 : 2) void k_conv3_wgrad_mfma(const Con
         t[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], __builtin_bit_cast(mf_b8, b2), t[2], 0, 0, 0);
       }
     }
+    wave_lds_order();  // the next segment overwrites this one
   }
   float* red = reinterpret_cast<float*>(buf);
   __syncthreads();
