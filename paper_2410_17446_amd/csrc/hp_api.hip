@@ -10,13 +10,13 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
 #include "../../include/hp.h"
 #include "../../include/hp_unet.h"
 #include "kernels.hpp"
+#include "parity.hpp"
 #include "pml.hpp"
 
 // the rational fit on the device (fit.hip)
@@ -1473,178 +1473,6 @@ int hp_set_form(hp_plan p, int form, int substeps) {
   return gmax > 1.0 + 1e-6 ? HP_WARN_UNSTABLE : HP_OK;
 }
 
-// ---- the eigen tables by parity
-
-// Q, Q^-1 and lam of the even and the odd subspace of the reflection j -> N - j (even block first),
-// in the coordinates of the folded fields: node j = 1..N/2 at entry j - 1, the odd block's last
-// entry padding (zero).  Empty when the given tables do not split.
-struct ParityTables {
-  std::vector<std::complex<double>> q, qi, lam;
-};
-
-// In place inverse of the n x n matrix a (row stride ld): LU with row pivots, then the columns of
-// the identity solved together (Gauss-Jordan, cheaper, loses four digits on these eigenvectors);
-// false if it meets a zero or non-finite pivot.
-static bool invert(std::complex<double>* a, int n, int ld) {
-  struct Rows {  // rows of real and imaginary parts, so that the row operations vectorise
-    int n;
-    std::vector<double> re, im;
-    explicit Rows(int n_) : n(n_), re((size_t)n_ * n_), im((size_t)n_ * n_) {}
-    // row r -= f * row k, from column c0 on
-    void axpy(int r, int k, double fr, double fi, int c0) {
-      double *__restrict__ ar = &re[(size_t)r * n], *__restrict__ ai = &im[(size_t)r * n];
-      const double *__restrict__ pr = &re[(size_t)k * n], *__restrict__ pi = &im[(size_t)k * n];
-      for (int c = c0; c < n; ++c) {
-        ar[c] -= fr * pr[c] - fi * pi[c];
-        ai[c] -= fr * pi[c] + fi * pr[c];
-      }
-    }
-    void swap(int r, int k) {
-      std::swap_ranges(&re[(size_t)r * n], &re[(size_t)r * n] + n, &re[(size_t)k * n]);
-      std::swap_ranges(&im[(size_t)r * n], &im[(size_t)r * n] + n, &im[(size_t)k * n]);
-    }
-  };
-  Rows m(n), x(n);
-  for (int r = 0; r < n; ++r) {
-    for (int c = 0; c < n; ++c) {
-      m.re[(size_t)r * n + c] = a[(size_t)r * ld + c].real();
-      m.im[(size_t)r * n + c] = a[(size_t)r * ld + c].imag();
-    }
-    x.re[(size_t)r * n + r] = 1.0;
-  }
-  for (int k = 0; k < n; ++k) {
-    int best = k;
-    double mag = -1.0;
-    for (int r = k; r < n; ++r) {
-      const double u = m.re[(size_t)r * n + k], v = m.im[(size_t)r * n + k], w = u * u + v * v;
-      if (w > mag) mag = w, best = r;
-    }
-    if (!(mag > 0.0) || !std::isfinite(mag)) return false;
-    if (best != k) m.swap(best, k), x.swap(best, k);
-    const double dr = m.re[(size_t)k * n + k] / mag, di = -m.im[(size_t)k * n + k] / mag;
-    for (int r = k + 1; r < n; ++r) {
-      const double u = m.re[(size_t)r * n + k], v = m.im[(size_t)r * n + k];
-      const double fr = u * dr - v * di, fi = u * di + v * dr;
-      m.axpy(r, k, fr, fi, k);
-      x.axpy(r, k, fr, fi, 0);
-    }
-  }
-  for (int k = n - 1; k >= 0; --k) {
-    const double u = m.re[(size_t)k * n + k], v = m.im[(size_t)k * n + k], w = u * u + v * v;
-    double *xr = &x.re[(size_t)k * n], *xi = &x.im[(size_t)k * n];
-    for (int c = 0; c < n; ++c) {
-      const double p = (xr[c] * u + xi[c] * v) / w, q = (xi[c] * u - xr[c] * v) / w;
-      xr[c] = p;
-      xi[c] = q;
-    }
-    for (int r = 0; r < k; ++r) x.axpy(r, k, m.re[(size_t)r * n + k], m.im[(size_t)r * n + k], 0);
-  }
-  for (int r = 0; r < n; ++r)
-    for (int c = 0; c < n; ++c) {
-      a[(size_t)r * ld + c] = {x.re[(size_t)r * n + c], x.im[(size_t)r * n + c]};
-      if (!std::isfinite(x.re[(size_t)r * n + c]) || !std::isfinite(x.im[(size_t)r * n + c])) return false;
-    }
-  return true;
-}
-
-// The operator commutes with the reflection, so each eigenvector is even or odd, except that an
-// eigensolver returns arbitrary mixtures where an even and an odd eigenvalue agree to rounding (modes
-// confined to the two layers).  Both columns of such a pair hold the same even and the same odd
-// vector, so one of them supplies each.  The halves' inverses are computed afresh: Q is so
-// ill-conditioned that folding the given inverse would not invert the folded vectors.
-static ParityTables parity_tables(const std::complex<double>* q, const std::complex<double>* l, int N) {
-  using cd = std::complex<double>;
-  const int n = N - 1, h = N / 2;
-  std::vector<double> ev(n, 0.0), od(n, 0.0);  // squared norms of each column's even and odd part
-  for (int j = 0; j < h; ++j)
-    for (int c = 0; c < n; ++c) {
-      const cd a = q[(size_t)j * n + c], b = q[(size_t)(n - 1 - j) * n + c];
-      const double w = j == h - 1 ? 0.25 : 0.5;  // the middle node is its own mirror image
-      ev[c] += w * std::norm(a + b);
-      od[c] += w * std::norm(a - b);
-    }
-  std::vector<int> role(n, -1), mixed;
-  int ne = 0, no = 0;
-  for (int c = 0; c < n; ++c) {
-    const double s = ev[c] + od[c];
-    if (!(s > 0.0) || !std::isfinite(s)) return {};
-    if (std::min(ev[c], od[c]) > 1e-6 * s)
-      mixed.push_back(c);
-    else if (ev[c] > od[c])
-      role[c] = 0, ++ne;
-    else
-      role[c] = 1, ++no;
-  }
-  for (int a : mixed) {
-    if (role[a] >= 0) continue;
-    int b = -1;
-    double gap = 1e300;
-    for (int c : mixed)
-      if (c != a && role[c] < 0 && std::norm(l[c] - l[a]) < gap) gap = std::norm(l[c] - l[a]), b = c;
-    if (b < 0) return {};
-    const bool first = ev[a] / (ev[a] + od[a]) >= ev[b] / (ev[b] + od[b]);
-    role[first ? a : b] = 0;
-    role[first ? b : a] = 1;
-    ++ne, ++no;
-  }
-  if (ne != h || no != h - 1) return {};
-  ParityTables t;
-  t.q.assign(2 * (size_t)h * h, cd(0.0));
-  t.lam.assign(2 * (size_t)h, cd(0.0));
-  int at[2] = {0, 0};
-  for (int c = 0; c < n; ++c) {
-    const int r = role[c], k = at[r]++;
-    for (int j = 0; j < h - r; ++j) {
-      const cd a = q[(size_t)j * n + c], b = q[(size_t)(n - 1 - j) * n + c];
-      t.q[((size_t)r * h + j) * h + k] = 0.5 * (r ? a - b : a + b);
-    }
-    t.lam[(size_t)r * h + k] = l[c];
-  }
-  t.qi = t.q;
-  bool ok[2] = {false, false};
-  auto odd = [&]() { ok[1] = invert(t.qi.data() + (size_t)h * h, h - 1, h); };
-  std::thread side;
-  try {
-    side = std::thread(odd);
-  } catch (const std::system_error&) {  // no thread to be had
-    odd();
-  }
-  ok[0] = invert(t.qi.data(), h, h);
-  if (side.joinable()) side.join();
-  return ok[0] && ok[1] ? t : ParityTables();
-}
-
-// Relative error of the split tables' operator on x against y = s D~ x.
-static double parity_error(const ParityTables& t, int N, const std::vector<std::complex<double>>& x,
-                           const std::vector<std::complex<double>>& y) {
-  using cd = std::complex<double>;
-  const int n = N - 1, h = N / 2;
-  std::vector<cd> out[2];
-  for (int r = 0; r < 2; ++r) {
-    const cd *q = t.q.data() + (size_t)r * h * h, *qi = t.qi.data() + (size_t)r * h * h;
-    std::vector<cd> f(h), m(h);
-    out[r].assign(h, cd(0.0));
-    for (int j = 0; j < h; ++j) f[j] = 0.5 * (r ? x[j] - x[n - 1 - j] : x[j] + x[n - 1 - j]);
-    for (int k = 0; k < h; ++k) {
-      cd s = 0.0;
-      for (int j = 0; j < h; ++j) s += qi[(size_t)k * h + j] * f[j];
-      m[k] = t.lam[(size_t)r * h + k] * s;
-    }
-    for (int j = 0; j < h; ++j)
-      for (int k = 0; k < h; ++k) out[r][j] += q[(size_t)j * h + k] * m[k];
-  }
-  double num = 0.0, den = 0.0;
-  for (int j = 0; j < h; ++j) {
-    num += std::norm(out[0][j] + out[1][j] - y[j]);
-    den += std::norm(y[j]);
-    if (j == h - 1) continue;
-    num += std::norm(out[0][j] - out[1][j] - y[n - 1 - j]);
-    den += std::norm(y[n - 1 - j]);
-  }
-  const double e = std::sqrt(num / den);
-  return std::isfinite(e) ? e : 1e300;
-}
-
 static void free_pml(hp_plan p) {
   if (p->pml_mem) (void)hipFree(p->pml_mem);
   p->pml_mem = nullptr;
@@ -1697,18 +1525,21 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
     a2[j] = mk(a2c[j].real(), a2c[j].imag());
     a1[j] = mk(a1c[j].real(), a1c[j].imag());
   }
-  ParityTables split = parity_tables(q, l, N);
   // the tables must decompose this library's stretched operator: compare
   // Q (lam .* (Q^-1 x)) with s D~ x for two pseudo-random x
+  std::vector<cd> px[2], py[2];
+  double whole = 0.0;  // largest relative error
   {
     uint64_t rs = 0x9E3779B97F4A7C15ull;
     auto rnd = [&]() {
       rs = rs * 6364136223846793005ull + 1442695040888963407ull;
       return (double)(rs >> 11) / 9007199254740992.0 - 0.5;
     };
-    double whole = 0.0, halves = 0.0;  // largest relative errors of the given and the split tables
     for (int probe = 0; probe < 2; ++probe) {
-      std::vector<cd> x(n), t(n), ye(n, 0.0), yd(n);
+      std::vector<cd>&x = px[probe], &yd = py[probe];
+      x.resize(n);
+      yd.resize(n);
+      std::vector<cd> t(n), ye(n, 0.0);
       for (int j = 0; j < n; ++j) x[j] = cd(rnd(), rnd());
       for (int r = 0; r < n; ++r) {
         cd acc = 0.0;
@@ -1750,10 +1581,7 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
                     "Q diag(lam) Q^-1 does not reproduce the stretched operator s D~ of this plan (relative error " +
                         std::to_string(std::sqrt(num / den)) + ")");
       whole = std::max(whole, std::sqrt(num / den));
-      if (!split.lam.empty()) halves = std::max(halves, parity_error(split, N, x, yd));
     }
-    // the split tables serve only where they decompose the operator as well as the given ones
-    if (!(halves <= 4.0 * whole + 1e-12)) split = ParityTables();
   }
   for (int k = 0; k < d.npoles; ++k) {
     const cd b(p->poles[k].re, p->poles[k].im);
@@ -1768,6 +1596,17 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
     }
     if (!(std::sqrt(mn) > 1e-12 * (1.0 + std::abs(b))))
       return fail(p, HP_EINVAL, "pole " + std::to_string(k) + " lies on the stretched free-space spectrum");
+  }
+  // the tables are accepted; their parity halves serve only where they decompose the operator as well
+  ParityTables split;
+  try {
+    split = parity_tables(q, l, N);
+    double halves = 0.0;
+    for (int probe = 0; probe < 2 && !split.lam.empty(); ++probe)
+      halves = std::max(halves, parity_error(split, N, px[probe], py[probe]));
+    if (!(halves <= 4.0 * whole + 1e-12)) split = ParityTables();
+  } catch (const std::bad_alloc&) {  // whole planes
+    split = ParityTables();
   }
   const size_t NN = (size_t)N * N, fn = p->fieldn, K = (size_t)d.npoles;
   const size_t nparts = (size_t)pml_apply_parts(N);

@@ -261,6 +261,29 @@ def test_eigenvectors_in_any_order_and_scale():
         plan.set_pml(g.sigma_max, bad, np.linalg.inv(bad), lam)
 
 
+def test_refused_tables_cost_no_inversion():
+    """Tables of another operator are refused after the O(N^2) probe: at 2047 unknowns the split's
+    two dense inversions would take seconds of the host."""
+    _cuda()
+    import time
+    from paper_2410_17446_amd import hp
+    wl = workload(N=64, W=12, npoles=1)
+    f, N = wl["fit"], 2048
+    plan = hp.Plan(nx=N, ny=N, dx=0.25, dy=0.25, k0=K0, n0=1.0, dz=1.0, ncomp=1, poles=f["poles"],
+                   residues=f["residues"], r_inf=f["r_inf"], d2=wl["c"], d1=wl["d"], edge_width=12, edge_eta=0.25,
+                   tol=1e-8, restart=1, max_cycles=1, precision=0)
+    Q = np.eye(N - 1, dtype=complex) + 0.01
+    lam = -np.linspace(0.1, 1.0, N - 1) + 0.1j
+    best = 1e9
+    for _ in range(3):
+        t = time.perf_counter()
+        with pytest.raises(hp.HPError):
+            plan.set_pml(1.0, Q, Q, lam)
+        best = min(best, time.perf_counter() - t)
+    plan.close()
+    assert best < 0.4
+
+
 def test_removed_layers_leave_no_trace():
     """A step after the layers are removed equals a fresh plan's bit for bit (the layers' fields are
     physical, the plain path's transformed, in the same memory)."""
