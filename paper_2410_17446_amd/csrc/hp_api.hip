@@ -1604,7 +1604,7 @@ int hp_set_pml(hp_plan p, double sigma_max, const void* Q, const void* Qinv, con
     double halves = 0.0;
     for (int probe = 0; probe < 2 && !split.lam.empty(); ++probe)
       halves = std::max(halves, parity_error(split, N, px[probe], py[probe]));
-    if (!(halves <= 4.0 * whole + 1e-12)) split = ParityTables();
+    if (!parity_as_good(halves, whole)) split = ParityTables();
   } catch (const std::bad_alloc&) {  // whole planes
     split = ParityTables();
   }

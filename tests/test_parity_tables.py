@@ -26,7 +26,7 @@ void* operator new(std::size_t n) {
 void operator delete(void* p) noexcept { std::free(p); }
 void operator delete(void* p, std::size_t) noexcept { std::free(p); }
 extern "C" int t_invert(cd* a, int n, int ld, int threads) { return parity::invert(a, n, ld, threads); }
-extern "C" long t_left() { return allowed; }
+extern "C" int t_as_good(double halves, double whole) { return parity_as_good(halves, whole); }
 // 1: split, 0: does not split, -1: bad_alloc
 extern "C" int t_tables(const cd* q, const cd* l, int N, cd* hq, cd* hqi, cd* hl, long limit) {
   allowed = limit;
@@ -126,3 +126,56 @@ def test_an_allocation_that_fails_is_reported(lib):
         rc = _split(lib, Q, lam, 64, limit)[0]
         assert rc == -1 or rc > 0, limit
     assert _split(lib, Q, lam, 64, 4)[0] == -1
+
+
+def test_halves_serve_within_the_scatter_of_rounding_only(lib):
+    lib.t_as_good.argtypes = [ctypes.c_double, ctypes.c_double]
+    for whole in (1e-13, 1e-9, 1e-4):
+        assert lib.t_as_good(2.4 * whole, whole) and not lib.t_as_good(2.6 * whole + 1e-13, whole)
+    assert lib.t_as_good(1e-14, 0.0) and not lib.t_as_good(2e-14, 0.0) and not lib.t_as_good(np.nan, 1e-9)
+
+
+def _fold(x):
+    h = (x.shape[0] + 1) // 2
+    return 0.5 * (x + x[::-1])[:h], 0.5 * (x - x[::-1])[:h]
+
+
+def _unfold(e, o):
+    h = e.shape[0]
+    out = np.empty((2 * h - 1,) + e.shape[1:], complex)
+    out[:h] = e + o
+    out[::-1][:h - 1] = (e - o)[:h - 1]
+    return out
+
+
+@pytest.mark.parametrize("N,W,sigma", [(64, 8, 1.0), (64, 8, 10.0), (128, 16, 10.0), (128, 16, 3.0), (192, 24, 10.0)])
+def test_solves_by_halves_are_as_good_as_whole(lib, N, W, sigma):
+    """(A Z + Z A^T - b Z = x) by the halves and by the whole planes against Bartels-Stewart, refined:
+    over four right-hand sides and poles the halves' errors are no larger in the geometric mean and
+    none is over twice the other's (both are rounding times the same condition)."""
+    from oracle import fit
+    from scipy.linalg import solve_sylvester
+    A, Q, Qi, lam = _layer(N, W, sigma)
+    rc, q, qi, l = _split(lib, Q, lam, N)
+    assert rc > 0
+    poles = fit.fit_exp_sqrt(inputs.K0, 8)["poles"]
+    n, rng, ratios = N - 1, np.random.default_rng(N), []
+    X = (np.arange(1, N) - N / 2) / 32.0
+    beam = np.exp(-X[:, None] ** 2 - X[None] ** 2).astype(complex)
+    for b in (poles[np.argmin(abs(poles.imag))], poles[3]):
+        for x in (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n)), beam):
+            S = A - b * np.eye(n)
+            z = solve_sylvester(S, A.T, x)
+            for _ in range(2):
+                z = z + solve_sylvester(S, A.T, x - (S @ z + z @ A.T))
+            whole = Q @ ((Qi @ x @ Qi.T) / (lam[:, None] + lam[None] - b)) @ Q.T
+            rows = []
+            for i, xi in enumerate(_fold(x)):
+                cols = []
+                for j, xij in enumerate(_fold(xi.T)):
+                    den = l[i][:, None] + l[j][None] - b
+                    cols.append((q[i] @ ((qi[i] @ xij.T @ qi[j].T) / np.where(den == 0, 1, den)) @ q[j].T).T)
+                rows.append(_unfold(*cols).T)
+            halves = _unfold(*rows)
+            ratios.append(np.linalg.norm(halves - z) / np.linalg.norm(whole - z))
+    assert np.exp(np.mean(np.log(ratios))) <= 1.0 and max(ratios) <= 2.0, ratios
