@@ -66,3 +66,29 @@ def to_gpu(a):
 
 def rel_l2(a, b):
     return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def unsplit_tables(A, Q, Qinv, lam):
+    """Eigen tables of A that hp_set_pml accepts and whose columns don't split by parity: one column
+    takes 1 % of a vector of the other parity and another eigenvalue, the pair chosen for the
+    smallest operator error."""
+    n = len(lam)
+    ev, od = np.linalg.norm(Q + Q[::-1], axis=0), np.linalg.norm(Q - Q[::-1], axis=0)
+    pure = np.minimum(ev, od) < 1e-6 * np.maximum(ev, od)
+    x = np.random.default_rng(0).standard_normal(n) + 1j * np.random.default_rng(1).standard_normal(n)
+    y, best = A @ x, None
+    for i in range(n):
+        for j in range(n):
+            if not (pure[i] and pure[j] and (ev[i] > od[i]) != (ev[j] > od[j]) and abs(lam[i] - lam[j]) > 1e-3):
+                continue
+            err = abs((lam[j] - lam[i]) * (Qinv[j] @ x)) * np.linalg.norm(Q[:, j])
+            if best is None or err < best[0]:
+                best = (err, i, j)
+    _, i, j = best
+    E = np.eye(n, dtype=complex)
+    E[i, j] = 0.01 * np.linalg.norm(Q[:, j]) / np.linalg.norm(Q[:, i])
+    Q2 = Q @ E
+    E[i, j] = -E[i, j]
+    Q2i = E @ Qinv
+    assert np.linalg.norm(Q2 @ (lam * (Q2i @ x)) - y) < 1e-4 * np.linalg.norm(y)
+    return np.ascontiguousarray(Q2), Q2i, lam

@@ -19,7 +19,7 @@ import pytest
 from oracle import pml
 from paper_2410_17446_amd import tables
 
-from helpers import K0, rel_l2, to_gpu, workload
+from helpers import K0, rel_l2, to_gpu, unsplit_tables, workload
 
 pytestmark = pytest.mark.gpu
 
@@ -236,6 +236,62 @@ def test_parity_halves_equal_whole_planes(N, ncomp):
     for y in ys[1:]:
         assert rel_l2(y, ys[0]) < bound
         assert not y[:, 0, :].any() and not y[:, :, 0].any()
+
+
+@pytest.mark.parametrize("N,W,ncomp", [(64, 8, 1), (128, 16, 2), (192, 24, 1), (512, 64, 1)])
+def test_parity_halves_are_taken(N, W, ncomp):
+    """The dense stages' operation count says which path ran: two Arnoldi steps of K poles on whole
+    planes are 8 K products (variant 0); the matrix-core variants make the first round's first two
+    products once for all poles, 6 K + 2, at half the operations each."""
+    torch = _cuda()
+    from paper_2410_17446_amd import hp
+    K, sig = 4, 10.0
+    wl = workload(N=N, W=W, npoles=K)
+    f = wl["fit"]
+    plan = hp.Plan(nx=N, ny=N, dx=0.25, dy=0.25, k0=K0, n0=1.0, dz=1.0, ncomp=ncomp, poles=f["poles"],
+                   residues=f["residues"], r_inf=f["r_inf"], d2=wl["c"], d1=wl["d"], edge_width=W, edge_eta=0.25,
+                   tol=1e-10, restart=2, max_cycles=1, precision=0)
+    plan.set_pml(sig, *tables.pml_eigen(N, 0.25, K0, 1.0, W, sig, wl["c"], wl["d"]))
+    plan.set_fixed_iters([2] * K)
+    w = to_gpu(np.broadcast_to(wl["w"].reshape(-1, N, N)[:1], (ncomp, N, N)).copy())
+    n2, product = to_gpu(wl["n2"]), 8.0 * (N - 1.0) ** 3 * ncomp
+    for variant, count in ((0, 8 * K), (1, 3 * K + 1), (2, 3 * K + 1), (3, 3 * K + 1)):
+        plan.set_launch(variant)
+        plan.profile(True, ["pml_gemm"])
+        plan.step(w, n2)
+        assert plan.profile_totals()["pml_gemm"][1] == pytest.approx(count * product, rel=1e-12), variant
+    plan.close()
+
+
+def test_tables_that_do_not_split_run_whole_planes():
+    """Accepted tables with a column of mixed parity: whole planes in every variant (6 K + 2 products
+    of full cost), which agree with each other to rounding, and the step still solves."""
+    torch = _cuda()
+    from paper_2410_17446_amd import hp
+    wl, g = _setup()
+    plan, _ = _plan(wl, g)
+    K = plan.npoles
+    A = tables.pml_stretched_d2(64, g.h, g.k0, g.n0, g.W, g.sigma_max, wl["c"], wl["d"])
+    Q, Qi, lam = unsplit_tables(A, *tables.pml_eigen(64, g.h, g.k0, g.n0, g.W, g.sigma_max, wl["c"], wl["d"]))
+    plan.set_pml(g.sigma_max, Q, Qi, lam)
+    rng = np.random.default_rng(8)
+    x = to_gpu(rng.standard_normal((1, 64, 64)) + 1j * rng.standard_normal((1, 64, 64)))
+    ys = []
+    for variant in (0, 1, 2, 3):
+        plan.set_launch(variant)
+        y = torch.zeros_like(x)
+        plan.apply_preconditioner(3, x, y)
+        ys.append(y.cpu().numpy())
+    bound = 40 * 2.2e-16 * 64 * np.linalg.cond(Q) ** 2
+    assert all(rel_l2(y, ys[0]) < bound for y in ys[1:])
+    plan.set_launch(1)
+    w, n2 = to_gpu(wl["w"]), to_gpu(wl["n2"])
+    plan.step(w, n2)
+    assert max(plan.stats()[1]) <= wl["cfg"]["tol"]
+    plan.set_fixed_iters([2] * K)
+    plan.profile(True, ["pml_gemm"])
+    plan.step(w, n2)
+    assert plan.profile_totals()["pml_gemm"][1] == pytest.approx((6 * K + 2) * 8.0 * 63.0 ** 3, rel=1e-12)
 
 
 def test_eigenvectors_in_any_order_and_scale():

@@ -11,6 +11,8 @@ import pytest
 from oracle import stencil
 from paper_2410_17446_amd import build, inputs, tables
 
+from helpers import unsplit_tables
+
 HARNESS = r"""
 #include "parity.hpp"
 #include <atomic>
@@ -114,6 +116,12 @@ def test_halves_invert_and_hold_every_eigenvalue(lib, N, W, sigma):
     assert not q[1, -1].any() and not q[1, :, -1].any() and not qi[1, -1].any() and not qi[1, :, -1].any()
     both = np.concatenate([l[0], l[1, :-1]])
     assert np.array_equal(np.sort_complex(both), np.sort_complex(lam))
+
+
+def test_columns_of_mixed_parity_do_not_split(lib):
+    A, Q, Qi, lam = _layer(64, 12, 1.0)
+    Q, Qi, lam = unsplit_tables(A, Q, Qi, lam)
+    assert _split(lib, Q, lam, 64)[0] == 0
 
 
 def test_an_allocation_that_fails_is_reported(lib):
