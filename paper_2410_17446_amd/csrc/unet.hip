@@ -12,12 +12,12 @@
 
 #include <algorithm>
 #include <new>
-#include <random>
 #include <string>
 #include <vector>
 
 #include "../../include/hp_unet.h"
 #include "cplx.hpp"
+#include "normal.hpp"
 
 namespace {
 
@@ -1265,11 +1265,10 @@ int hp_unet_create(int levels, int base, int cin, int cout, unsigned long long s
   unet_layout(n);
   // He-normal weights (std sqrt(2 / fan_in)), zero biases; the output layer scaled by 0.1
   std::vector<float> h(n->nparam, 0.f);
-  std::mt19937_64 rng(seed);
-  std::normal_distribution<double> nd(0.0, 1.0);
+  NormalStream normal(seed);
   auto init = [&](const hp_unet_s::Conv& c, double gain) {
     const double sd = gain * std::sqrt(2.0 / (double)(c.ci * c.k * c.k));
-    for (size_t i = 0; i < (size_t)c.ci * c.co * c.k * c.k; ++i) h[c.w + i] = (float)(sd * nd(rng));
+    for (size_t i = 0; i < (size_t)c.ci * c.co * c.k * c.k; ++i) h[c.w + i] = (float)(sd * normal());
   };
   for (int l = 0; l < levels; ++l) {
     init(n->enc_a[l], 1.0);

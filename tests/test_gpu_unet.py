@@ -215,3 +215,59 @@ def test_learned_guess_end_to_end():
         tot_p += sum(it_p)
     print(f"total iterations: learned {tot_l}, plain {tot_p}")
     assert tot_l < tot_p, (tot_l, tot_p)
+
+
+def test_initial_weights_of_a_seed():
+    """He-normal weights by Marsaglia's polar method on the 64-bit Mersenne twister, written out here:
+    layer by layer, rounded to float32, biases 0, the output layer 0.1 times.  And creating the
+    training net takes no longer than 2.5 times as many normals of NumPy's, and 10 ms."""
+    import math
+    import time
+    _cuda()
+    from paper_2410_17446_amd.unet import UNet
+    M = (1 << 64) - 1
+
+    def twister(seed):  # Matsumoto and Nishimura's mt19937_64
+        mt = [seed & M]
+        for i in range(1, 312):
+            mt.append((6364136223846793005 * (mt[-1] ^ (mt[-1] >> 62)) + i) & M)
+        while True:
+            for i in range(312):
+                x = (mt[i] & 0xFFFFFFFF80000000) | (mt[(i + 1) % 312] & 0x7FFFFFFF)
+                mt[i] = mt[(i + 156) % 312] ^ (x >> 1) ^ (0xB5026F5AA96619E9 if x & 1 else 0)
+            for x in list(mt):
+                x ^= (x >> 29) & 0x5555555555555555
+                x ^= (x << 17) & 0x71D67FFFEDA60000
+                x ^= (x << 37) & 0xFFF7EEE000000000
+                yield (x ^ (x >> 43)) & M
+
+    def normals(seed):
+        g = twister(seed)
+        while True:
+            x, y = 2.0 * (float(next(g)) * 2.0**-64) - 1.0, 2.0 * (float(next(g)) * 2.0**-64) - 1.0
+            r2 = x * x + y * y
+            if 0.0 < r2 <= 1.0:
+                m = math.sqrt(-2.0 * math.log(r2) / r2)
+                yield y * m
+                yield x * m
+
+    levels, base, cin, cout, seed = 2, 3, 3, 2, 11
+    net = UNet(levels, base, cin, cout, seed=seed)
+    got = net.state()["params"]
+    enc_a, enc_b, dec_a, dec_b, out, size = ounet.layout(levels, base, cin, cout)
+    z, want = normals(seed), np.zeros(size, np.float32)
+    for c, gain in [(c, 1.0) for a, b in ((enc_a, enc_b), (dec_a, dec_b)) for p in zip(a, b) for c in p] + [(out, 0.1)]:
+        sd = gain * math.sqrt(2.0 / (c.ci * c.k * c.k))
+        want[c.w:c.b] = [np.float32(sd * next(z)) for _ in range(c.b - c.w)]
+    assert np.allclose(got, want, rtol=2.0**-22, atol=0)  # the two libraries' log may round differently
+
+    def best(f):
+        ts = []
+        for _ in range(5):
+            t = time.perf_counter()
+            f()
+            ts.append(time.perf_counter() - t)
+        return min(ts)
+
+    n = UNet(4, 32, 7, 2).nparam
+    assert best(lambda: UNet(4, 32, 7, 2)) < 2.5 * best(lambda: np.random.default_rng(0).standard_normal(n)) + 0.01
