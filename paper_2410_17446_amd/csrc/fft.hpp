@@ -81,19 +81,18 @@ __device__ __forceinline__ void dft(cx<T>* v) {
     v[0] = v[0] + t1;
     v[1] = t2 + t3;
     v[2] = t2 - t3;
-  } else if constexpr (R == 6 || R == 12) {
-    // prime factors A x 3 (A = R/3), no twiddles: with n = 3 n1 + A n2 (mod R), F_k is
-    // the A x 3 transform at (k mod A, k mod 3)
-    constexpr int A = R / 3;
-    cx<T> a[3][A];
+  } else if constexpr (R == 12) {
+    // prime factors 4 x 3, no twiddles: with n = 3 n1 + 4 n2 (mod 12), F_k is the 4 x 3
+    // transform at (k mod 4, k mod 3)
+    cx<T> a[3][4];
 #pragma unroll
     for (int n2 = 0; n2 < 3; ++n2) {
 #pragma unroll
-      for (int n1 = 0; n1 < A; ++n1) a[n2][n1] = v[(3 * n1 + A * n2) % R];
-      dft<T, A>(a[n2]);
+      for (int n1 = 0; n1 < 4; ++n1) a[n2][n1] = v[(3 * n1 + 4 * n2) % 12];
+      dft4(a[n2][0], a[n2][1], a[n2][2], a[n2][3]);
     }
 #pragma unroll
-    for (int k1 = 0; k1 < A; ++k1) {
+    for (int k1 = 0; k1 < 4; ++k1) {
       cx<T> b[3] = {a[0][k1], a[1][k1], a[2][k1]};
       dft<T, 3>(b);
       a[0][k1] = b[0];
@@ -101,7 +100,7 @@ __device__ __forceinline__ void dft(cx<T>* v) {
       a[2][k1] = b[2];
     }
 #pragma unroll
-    for (int k = 0; k < R; ++k) v[k] = a[k % 3][k % A];
+    for (int k = 0; k < 12; ++k) v[k] = a[k % 3][k % 4];
   } else if constexpr (R == 2) {
     cx<T> t = v[0];
     v[0] = t + v[1];
