@@ -1435,6 +1435,21 @@ __device__ __forceinline__ c128 cdiv_scaled(c128 a, c128 b) {
   return cdiv(mk(ldexp(a.re, e), ldexp(a.im, e)), mk(ldexp(b.re, e), ldexp(b.im, e)));
 }
 
+__device__ __forceinline__ bool finite2(c128 a) { return isfinite(a.re) && isfinite(a.im); }
+
+// r(z) where a denominator or the sum leaves the range of cdiv; over: a term or the sum became
+// infinite, whatever it met after.
+__device__ __forceinline__ c128 rat_scaled(const SpectrumCheck& c, double z, bool& over) {
+  c128 r = c.r_inf;
+  over = false;
+  for (int k = 0; k < c.npoles; ++k) {
+    const c128 t = cdiv_scaled(c.a[k], mk(z - c.b[k].re, -c.b[k].im));
+    r = r + t;
+    over = over || isinf(t.re) || isinf(t.im) || isinf(r.re) || isinf(r.im);
+  }
+  return r;
+}
+
 // Maxima of |f| over the samples.  A NaN counts for nothing where r itself is one, and as an
 // infinity where r is not (infinite terms of both signs met, or a finite r overflowed in the polynomial).
 __global__ __launch_bounds__(256) void k_spectrum_max(const SpectrumCheck c, double* __restrict__ out) {
@@ -1443,21 +1458,23 @@ __global__ __launch_bounds__(256) void k_spectrum_max(const SpectrumCheck c, dou
   for (int i = blockIdx.x * 256 + threadIdx.x; i <= 100000; i += kSpectrumBlocks * 256) {
     const double z = c.lo + (c.hi - c.lo) * i / 100000.0;
     c128 r = c.r_inf;
-    bool over = false;  // a term or the sum so far infinite
+    bool plain = true, over = false;
     for (int k = 0; k < c.npoles; ++k) {
-      const c128 t = cdiv_scaled(c.a[k], mk(z - c.b[k].re, -c.b[k].im));
-      r = r + t;
-      over = over || isinf(t.re) || isinf(t.im) || isinf(r.re) || isinf(r.im);
+      const c128 q = mk(z - c.b[k].re, -c.b[k].im);
+      const double d = abs2(q);
+      plain = plain && d > 1e-280 && d < 1e280;
+      r = r + cdiv(c.a[k], q);
     }
+    if (!(plain && finite2(r))) r = rat_scaled(c, z, over);
     if (c.hk != 0.0 && !over) {
-      const bool number = r.re == r.re && r.im == r.im;
+      const bool number = finite2(r);
       const c128 x = mk(-c.hk * r.im, c.hk * (r.re - 1.0));  // i hk (r - 1)
       const c128 one = mk(1.0, 0.0);
       c128 q = mk(1.0 / 6.0, 0.0) + (1.0 / 24.0) * x;
       q = mk(0.5, 0.0) + x * q;
       q = one + x * q;
       r = one + x * q;
-      over = number && !(isfinite(r.re) && isfinite(r.im));
+      over = number && !finite2(r);
     }
     const double v = over ? INFINITY : sqrt(abs2(r));
     if (v > best) best = v;
