@@ -60,7 +60,9 @@ long hp_unet_num_params(hp_unet net);
  * and float32 accumulation (the weight gradient contracts over pixels in
  * fixed splits summed in a fixed order, so repeated calls give identical
  * results).  Parameters, the 1x1 output layer, bias gradients and Adam stay
- * float32 in both. */
+ * float32 in both.  Once a shape is in use, a change may allocate what only the
+ * other arithmetic needs (HP_ENOMEM when there is no room; the old one then
+ * stays). */
 enum { HP_UNET_F32 = 0, HP_UNET_BF16 = 1 };
 int hp_unet_set_precision(hp_unet net, int precision);
 

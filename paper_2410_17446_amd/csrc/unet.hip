@@ -999,6 +999,26 @@ float* dalloc(hp_unet n, size_t count, bool* ok) {
   return p;
 }
 
+// The input of dec_a[l], [upsampled low, enc2[l]].  The bf16 kernels read it where it lies
+// when a 32-channel chunk and an aligned group of four pixels fall into one part and lane
+// offsets fit 32 bits; otherwise, and in float32, forward() has written it to up[l] (batch 8,
+// 256 x 256, 64 + 32 channels: 107 + 41 us for that and 87 for its bf16 copy, against 53 for
+// the copy from the parts).
+bool reads_parts(hp_unet n, int l, int H, int W) {
+  return n->bf16 && ch(n, l + 1) % mf::CK == 0 && (W >> l) % 8 == 0 &&
+         (size_t)(H >> l) * (W >> l) < ((size_t)1 << 27);
+}
+
+// up[l] where forward() writes it and there is none yet (352 MB at batch 8, 256 x 256, four
+// levels from 32 channels, that the bf16 kernels do without).
+bool ensure_up(hp_unet n, int B, int H, int W) {
+  bool ok = true;
+  for (int l = 0; l + 1 < n->levels; ++l)
+    if (!n->up[l] && !reads_parts(n, l, H, W))
+      n->up[l] = dalloc(n, (size_t)B * (ch(n, l + 1) + ch(n, l)) * (H >> l) * (W >> l), &ok);
+  return ok;
+}
+
 // Activation buffers for (B, H, W); reallocated only when the shape changes.
 int ensure_acts(hp_unet n, int B, int H, int W) {
   if (n->B == B && n->H == H && n->W == W) return HP_OK;
@@ -1013,7 +1033,7 @@ int ensure_acts(hp_unet n, int B, int H, int W) {
     n->enc1.push_back(dalloc(n, c, &ok));
     n->enc2.push_back(dalloc(n, c, &ok));
     n->pool.push_back(last ? nullptr : dalloc(n, c / 4, &ok));
-    n->up.push_back(last ? nullptr : dalloc(n, (size_t)B * (ch(n, l + 1) + ch(n, l)) * pl, &ok));
+    n->up.push_back(nullptr);
     n->dec1.push_back(last ? nullptr : dalloc(n, c, &ok));
     n->dec2.push_back(last ? nullptr : dalloc(n, c, &ok));
     n->dskip.push_back(last ? nullptr : dalloc(n, c, &ok));
@@ -1052,6 +1072,7 @@ int ensure_acts(hp_unet n, int B, int H, int W) {
     pmax = std::max(pmax, (size_t)conv1_splits(B, H, W, n->out.ci, n->out.co) * n->out.co * (n->out.ci + 1));
     n->wgpart = dalloc(n, pmax, &ok);
   }
+  ok = ensure_up(n, B, H, W) && ok;
   if (!ok) {
     free_acts(n);
     return ufail(n, HP_ENOMEM, "activation allocation failed");
@@ -1123,15 +1144,6 @@ void conv3_bwd(hp_unet n, const ConvIn& in, const float* dy, const hp_unet_s::Co
   }
 }
 
-// The input of dec_a[l], [upsampled low, enc2[l]].  The bf16 kernels read it where it lies
-// when a 32-channel chunk and an aligned group of four pixels fall into one part and lane
-// offsets fit 32 bits; otherwise, and in float32, forward() has written it to up[l] (batch 8,
-// 256 x 256, 64 + 32 channels: 107 + 41 us for that and 87 for its bf16 copy, against 53 for
-// the copy from the parts).
-bool reads_parts(hp_unet n, int l, int H, int W) {
-  return n->bf16 && ch(n, l + 1) % mf::CK == 0 && (W >> l) % 8 == 0 &&
-         (size_t)(H >> l) * (W >> l) < ((size_t)1 << 27);
-}
 ConvIn dec_input(hp_unet n, int l, int H, int W) {
   if (!reads_parts(n, l, H, W)) return plain(n->up[l]);
   return ConvIn{n->enc2[l], l + 2 == n->levels ? n->enc2[l + 1] : n->dec2[l + 1], ch(n, l + 1)};
@@ -1304,7 +1316,13 @@ long hp_unet_num_params(hp_unet n) { return n ? (long)n->nparam : 0; }
 int hp_unet_set_precision(hp_unet n, int precision) {
   if (!n) return ufail(nullptr, HP_EINVAL, "net is NULL");
   if (precision != HP_UNET_F32 && precision != HP_UNET_BF16) return ufail(n, HP_EINVAL, "unknown precision");
+  const bool was = n->bf16;
   n->bf16 = precision == HP_UNET_BF16;
+  // buffers of a shape already in use that only the new precision needs
+  if (n->B && !ensure_up(n, n->B, n->H, n->W)) {
+    n->bf16 = was;
+    return ufail(n, HP_ENOMEM, "activation allocation failed");
+  }
   return HP_OK;
 }
 

@@ -217,6 +217,33 @@ def test_learned_guess_end_to_end():
     assert tot_l < tot_p, (tot_l, tot_p)
 
 
+def test_concatenations_are_held_where_they_are_written():
+    """bf16 reads the decoders' two inputs where they lie: no buffers for their concatenations, which
+    float32 keeps; changing the arithmetic of a net in use gives what a new net gives, both ways."""
+    torch = _cuda()
+    from paper_2410_17446_amd.unet import HP_UNET_BF16, HP_UNET_F32, UNet
+    levels, base, B, H = 3, 32, 4, 128
+    concat = 4 * sum(B * (base << l) * 3 * (H >> l) ** 2 for l in range(levels - 1))
+    x, t = _data(B=B, H=H, W=H)
+    x, t = to_gpu(x), to_gpu(t)
+    held, grads, nets = [], [], []
+    for precision in (HP_UNET_F32, HP_UNET_BF16):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        net = UNet(levels, base, 7, 2, seed=3, precision=precision)
+        net.grad(x, t)
+        torch.cuda.synchronize()
+        held.append(free - torch.cuda.mem_get_info()[0])
+        grads.append(net.state()["grads"])
+        nets.append(net)
+    assert held[0] - held[1] >= 0.9 * concat, held
+    for net, first in zip(nets, (0, 1)):
+        for k in (1 - first, first, 1 - first):
+            net.set_precision((HP_UNET_F32, HP_UNET_BF16)[k])
+            net.grad(x, t)
+            assert np.array_equal(net.state()["grads"], grads[k])
+
+
 def test_initial_weights_of_a_seed():
     """He-normal weights by Marsaglia's polar method on the 64-bit Mersenne twister, written out here:
     layer by layer, rounded to float32, biases 0, the output layer 0.1 times.  And creating the
