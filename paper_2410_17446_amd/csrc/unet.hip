@@ -439,8 +439,7 @@ constexpr int WAVE = CO * DS + 3 * CI * XS;
 }
 
 // Bound: memory.  A segment loads 11 KB for 18 products (288 cycles of a matrix core), dy
-// once for every 16 input channels, those of one split on one XCD (split = block id mod
-// nsplit, a multiple of 8 where it can be).  Global loads take 8 lanes per channel, a whole
+// once for every 16 input channels.  Global loads take 8 lanes per channel, a whole
 // line each; a lane group per channel quarter, as the fragments want it, touches 16 lines
 // with every 16 lanes, and under lane conditions each load waited for the one before
 // (batch 8, 256 x 256, 96 -> 32 channels: 238 -> 142 us; 384 -> 128 on 64 x 64: 234 -> 101; all
