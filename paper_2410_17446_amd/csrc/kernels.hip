@@ -1609,11 +1609,20 @@ void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi,
                          OSP, OSI, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
   }
   // The poles of a round that all start from the shared first basis vector share its
-  // forward transform (scratch: one R-domain field) where that is worth a launch of
-  // its own (a launch costs about as much as half the column work of 2^20 elements), from
-  // 2^21 elements over all poles on, and the storage keeps the transform's precision.
-  // 2048^2 vector, 8 poles: 13.54 -> 13.27 ms a step of three rounds.
-  bool shared = scratch && sizeof(T) == sizeof(C) && list.n > 1 &&
+  // forward transform (scratch: one R-domain field) where the storage keeps the transform's
+  // precision and n poles save more than the launch and the field written and read again
+  // cost.  First rounds, us, each pole its own transform -> shared:
+  //   complex128, 2 to 5 poles: 1024^2 17.3 -> 20.3, 22.5 -> 24.6, 26.9 -> 27.0, 31.5 -> 30.7; 512^2
+  //     vector with 5, 21.3 -> 22.3; 2048^2 vector with 3, 4, 5: 213 -> 228, 291 -> 292, 373 -> 348
+  //   from 6 on: 768^2 24.6 -> 22.2, 1024^2 36.0 -> 33.8, 512^2 vector 24.0 -> 23.5, 1024^2 vector with
+  //     8, 111 -> 92; scalar columns of 1536 and more from 12 on: 2048^2 with 8, 12, 16 177 -> 183,
+  //     262 -> 253, 346 -> 340; 1536^2 with 8, 16 106 -> 109, 201 -> 198
+  //   complex64: 2048^2 with 2, 3 53.6 -> 55.6, 76.5 -> 69.3; 1024^2 with 3, 22.8 -> 19.5
+  //   below 2^21 elements over all poles: 256^2 with 16, 14.0 -> 14.8; 512^2 with 6, 13.8 -> 14.2 (with
+  //     8, 15.7 -> 15.6; with 10, 18.6 -> 17.4)
+  //   fewer than 256 columns: 64 x 2048 vector, complex64, 8 poles, 26.4 -> 28.8 (256 x 1024 scalar 18.2 -> 17.0)
+  const int least = sizeof(C) == sizeof(float) ? 3 : (g.ncomp == 1 && g.ny >= 1536 ? 12 : 6);
+  bool shared = scratch && sizeof(T) == sizeof(C) && list.n >= least && g.nx * g.ncomp >= 256 &&
                 (size_t)list.n * g.ncomp * g.fsz >= (size_t)1 << 21;
   for (int a = 0; a < list.n && shared; ++a) shared = round_shared(list.e[a]) && round_m(list.e[a]) == 0;
   const Basis<cx<T>> once{scratch, nullptr, 0, 0};
@@ -1683,10 +1692,13 @@ void launch_row_apply(const cx<T>* zbase, size_t zsp, size_t zsi, const cx<T>* d
 #undef L_
 }
 
-// Elements per thread of the update: one for fields of up to 384^2 elements, whose
-// workgroups of four elements a thread would leave CUs without work (64 of them at
-// 256^2, 144 at 384^2: 12.0 us against 10.5), else four.  The rule looks at the field alone, so a pole's sums are
-// the same whatever the other poles do.
+// Elements per thread of the update: one for fields of up to 384^2 elements, whose workgroups
+// of four elements a thread leave CUs without work when one pole is left (64 of them at 256^2,
+// 144 at 384^2), else four.  us, four -> one element, one pole and 16 (12 at 256^2): 256^2 5.8 -> 5.3
+// and 11.9 -> 12.6, 384^2 6.1 -> 5.5 and 30.9 -> 30.5, 512 x 384 6.4 -> 6.0 and 41.4 -> 41.5, 512^2
+// 7.1 -> 6.8 and 57.5 -> 58.7, 768 x 512 8.8 -> 8.4 and 90.2 -> 91.3: above 384^2 many poles lose more
+// than one gains.  The rule looks at the field alone, so a pole's sums are the same whatever the
+// other poles do.
 static int update_elems(size_t total) { return total <= 384 * 384 ? 1 : 4; }
 
 template <typename T>

@@ -263,3 +263,24 @@ def test_shared_first_column_transform(ncomp, nx, ny, npoles):
         alone = plan.solve(k, w).cpu().numpy()
         assert rel_l2(got[k], alone) <= 10 * 64 * np.finfo(float).eps * np.log2(ny), k
     plan.close()
+
+
+@pytest.mark.parametrize("ncomp,nx,ny,npoles,precision", [
+    (1, 1024, 512, 5, 0), (1, 1024, 512, 6, 0), (1, 1024, 256, 8, 0), (1, 256, 2048, 11, 0), (1, 256, 2048, 12, 0),
+    (1, 1024, 1024, 2, 1), (1, 1024, 1024, 3, 1), (2, 64, 2048, 16, 1), (2, 128, 1024, 16, 1)])
+def test_shared_first_column_transform_at_the_lines_of_its_rule(ncomp, nx, ny, npoles, precision):
+    """Just below and on the numbers of poles, of columns and of elements from which a first round
+    shares its forward transform: each pole's solution is what it is alone, as above (complex64
+    vectors: their eps)."""
+    _cuda()
+    wl = workload(N=nx, ny=ny, ncomp=ncomp, W=8, npoles=npoles, medium=("sine", 0.02, 1.0), w0=2.0, tol=1e-8)
+    plan = gpu_plan(wl, precision=precision, restart=4)
+    plan.set_fixed_iters([2] * npoles)
+    w, n2 = to_gpu(wl["w"]), to_gpu(wl["n2"])
+    plan.step(w, n2)
+    got = [plan.solution(k).cpu().numpy() for k in range(npoles)]
+    eps = np.finfo(np.float32 if precision else float).eps
+    for k in (0, npoles - 1):
+        alone = plan.solve(k, w).cpu().numpy()
+        assert rel_l2(got[k], alone) <= 10 * 64 * eps * np.log2(ny), k
+    plan.close()
