@@ -417,21 +417,25 @@ struct ApplyCfg {
   static_assert(NT >= 8, "the stencil's interior points assume at least 8 threads per row");
 };
 
-// Waves per SIMD the register allocation must allow: two up to 256 (a field has no
-// more of them to offer, and the basis vectors' loads want the registers); above,
+// Lengths whose row pass is also built with a basis vector's loads in flight ahead (AHEAD), for
+// rounds whose workgroups leave the SIMDs a wave each at most.
+constexpr bool apply_ahead(int n) { return n <= 384; }
+
+// Waves per SIMD the register allocation must allow: two where a round has no more of them to
+// offer and the basis vectors' loads want the registers (AHEAD); else
 // scalar fields four (128 VGPRs) for 2^k up to 1024, else three (complex128
 // at 2048: two); vector fields four, which lets two 512-thread workgroups share
 // a CU at 2048 (their LDS, one buffer per component, fits twice).
-template <typename C, int N, int NC>
+template <typename C, int N, int NC, bool AHEAD>
 struct ApplyWaves {
   static constexpr bool POW2 = (N & (N - 1)) == 0;
-  static constexpr int V = N <= 384 ? 2
+  static constexpr int V = AHEAD     ? 2
                            : NC == 2 ? 4
                                      : ((N <= 1024 && POW2) ? 4 : (sizeof(C) == 4 || N < 2048 ? 3 : 2));
 };
 
-template <typename T, typename C, int N, int NC>
-__global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) void k_row_apply(
+template <typename T, typename C, int N, int NC, bool AHEAD>
+__global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC, AHEAD>::V)) void k_row_apply(
     const cx<T>* __restrict__ zbase, size_t zsp, size_t zsi, const cx<T>* __restrict__ dzbase, size_t dzsp,
     cx<T>* __restrict__ pbase, size_t psp, const Basis<cx<T>> basis, const C* __restrict__ coef,
     const PoleState* __restrict__ st, const RoundList list, int nrb, double2* __restrict__ part,
@@ -592,12 +596,10 @@ __global__ __launch_bounds__((ApplyCfg<N, NC>::WG), (ApplyWaves<C, N, NC>::V)) v
   // without, 1024^2 scalar 6.03 -> 5.90 ms a step, 512 x 768 vector 2.13 -> 2.05).  The
   // loads are unconditional (a row beyond the field reads row 0, and its p and u_m are
   // zero; a vector beyond u_m reads u_m), so nothing waits for them
-  // before their products; up to 384, where a pole alone leaves the SIMDs one wave
-  // each, the next vector's are in flight during the current one's (one 384^2 pole,
-  // average over the cycle: 26.6 -> 18.7 us with the smaller workgroups).  The waves' sums
+  // before their products; with AHEAD the next vector's are in flight during the current one's (one
+  // 384^2 pole, average over the cycle: 26.6 -> 18.7 us with the smaller workgroups).  The waves' sums
   // meet in LDS once per DOT_B vectors, so a workgroup leaves one partial sum per
   // product.
-  constexpr bool AHEAD = N <= 384;
   auto load_u = [&](int i, cx<T>* v) {
     const cx<T>* __restrict__ u = basis.at(e, min(i, m));
 #pragma unroll
@@ -1681,14 +1683,27 @@ void launch_row_apply(const cx<T>* zbase, size_t zsp, size_t zsi, const cx<T>* d
   const int nblk = row_apply_blocks<T>(g);
   // one workgroup per (row block, pole), row blocks padded to a multiple of 8
   dim3 grid((unsigned)((nblk + 7) / 8 * 8) * (unsigned)list.n);
+  // The next vector's loads ahead up to 1024 workgroups, one for each SIMD; beyond, other waves hide
+  // the latency and the registers are better spent on more of those.  The form changes no
+  // sum.  us per launch over a cycle, ahead and not: one pole 256^2 17.3 and 19.6, 384^2 17.4 and 20.1;
+  // 16 poles 64^2 (128 workgroups) 15.8 and 18.0, 256^2 (2048) 59.0 and 58.3, 384^2 152 and 147, vector
+  // 256^2 125 and 112, 384^2 303 and 283, 256 x 1024 352 and 317, 384 x 768 429 and 381.
+  const bool ahead = (size_t)nblk * list.n < 1024;
+#define R_(NN, NC, AH)                                                                                          \
+  hipLaunchKernelGGL((k_row_apply<T, C, NN, NC, AH>), grid, dim3(ApplyCfg<NN, NC>::WG), 0, s, zbase, zsp, zsi,  \
+                     dzbase, dzsp, pbase, psp, basis, coef, st, list, nblk, part, tw, g.ny, g.fsz, sc)
 #define L_(NN)                                                                                                  \
-  if (g.ncomp == 1)                                                                                             \
-    hipLaunchKernelGGL((k_row_apply<T, C, NN, 1>), grid, dim3(ApplyCfg<NN, 1>::WG), 0, s, zbase, zsp, zsi, dzbase,  \
-                       dzsp, pbase, psp, basis, coef, st, list, nblk, part, tw, g.ny, g.fsz, sc);               \
+  if (apply_ahead(NN) && ahead) {                                                                               \
+    if (g.ncomp == 1)                                                                                           \
+      R_(NN, 1, apply_ahead(NN));                                                                               \
+    else                                                                                                        \
+      R_(NN, 2, apply_ahead(NN));                                                                               \
+  } else if (g.ncomp == 1)                                                                                      \
+    R_(NN, 1, false);                                                                                           \
   else                                                                                                          \
-    hipLaunchKernelGGL((k_row_apply<T, C, NN, 2>), grid, dim3(ApplyCfg<NN, 2>::WG), 0, s, zbase, zsp, zsi, dzbase,  \
-                       dzsp, pbase, psp, basis, coef, st, list, nblk, part, tw, g.ny, g.fsz, sc);
+    R_(NN, 2, false);
   HP_DISPATCH_N(g.nx, L_)
+#undef R_
 #undef L_
 }
 

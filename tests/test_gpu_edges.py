@@ -284,3 +284,23 @@ def test_shared_first_column_transform_at_the_lines_of_its_rule(ncomp, nx, ny, n
         alone = plan.solve(k, w).cpu().numpy()
         assert rel_l2(got[k], alone) <= 10 * 64 * eps * np.log2(ny), k
     plan.close()
+
+
+@pytest.mark.parametrize("ncomp,nx,ny,npoles,precision", [
+    (1, 64, 2048, 4, 0), (2, 64, 1024, 5, 0), (1, 128, 1024, 5, 0), (2, 128, 512, 5, 0), (1, 192, 512, 5, 0),
+    (2, 192, 256, 5, 0), (1, 256, 512, 5, 0), (2, 256, 256, 5, 0), (1, 384, 256, 5, 0), (2, 384, 256, 5, 0),
+    (2, 64, 1024, 5, 1), (1, 192, 512, 5, 2), (2, 384, 256, 5, 1)])
+def test_row_pass_of_many_workgroups_sums_alike(ncomp, nx, ny, npoles, precision):
+    """Rounds of 1024 row workgroups and more run the form without loads ahead, a pole alone the one
+    with them: the same sums, so after five Arnoldi steps a pole's solution in the step is bit for
+    bit the one it has alone (the sizes stay below the shared column transform's)."""
+    _cuda()
+    wl = workload(N=nx, ny=ny, ncomp=ncomp, W=8, npoles=npoles, medium=("sine", 0.02, 1.0), w0=2.0, tol=1e-8)
+    plan = gpu_plan(wl, precision=precision, restart=6)
+    plan.set_fixed_iters([5] * npoles)
+    w, n2 = to_gpu(wl["w"]), to_gpu(wl["n2"])
+    plan.step(w, n2)
+    got = [plan.solution(k).cpu().numpy() for k in range(npoles)]
+    for k in range(npoles):
+        assert np.array_equal(got[k], plan.solve(k, w).cpu().numpy()), k
+    plan.close()
