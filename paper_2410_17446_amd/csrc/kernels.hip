@@ -1136,7 +1136,9 @@ __global__ __launch_bounds__(64) void k_cycle_init(PoleState* __restrict__ st, c
 // index) in turn and meet in LDS in a fixed order, then the first group runs the
 // transform.  (With a row per group 256^2 had 32 workgroups and every thread a
 // chain of all terms: 37 us, latency-bound; large fields run at the copy rate.)
-template <typename T, int N>
+// A term's loads are all in flight before its first product; FULL: one at a time, where the
+// workgroups fill the chip evenly (see launch_final).
+template <typename T, int N, bool FULL>
 __global__ __launch_bounds__(RowCfg<N>::WG) void k_final(const c128* __restrict__ w, c128* __restrict__ out,
                                                          const cx<T>* __restrict__ zbase, size_t zsp, size_t zsi,
                                                          const c128* __restrict__ xacc, size_t xsp,
@@ -1175,13 +1177,22 @@ __global__ __launch_bounds__(RowCfg<N>::WG) void k_final(const c128* __restrict_
         next += RPW;
       }
     }
-#pragma unroll 2
+#pragma unroll 1
     for (; next < nt; next += RPW) {
       const int i = next - hx;
-      const c128 cf = ak * st[k].y[i];
+      const c128 y = st[k].y[i];
       const cx<T>* zi = zk + i * zsi;
+      constexpr int LOADS = FULL ? 1 : PT;
 #pragma unroll
-      for (int s = 0; s < PT; ++s) acc[s] = cfma(cf, cvt<double>(zi[toff.at(s)]), acc[s]);
+      for (int h = 0; h < PT; h += LOADS) {
+        cx<T> a[LOADS];
+#pragma unroll
+        for (int s = 0; s < LOADS; ++s) a[s] = zi[toff.at(h + s)];
+        if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < LOADS; ++s) acc[h + s] = cfma(ak * y, cvt<double>(a[s]), acc[h + s]);
+        if constexpr (FULL) __builtin_amdgcn_sched_barrier(0);
+      }
     }
     next -= nt;
   }
@@ -1733,10 +1744,23 @@ void launch_final(const c128* w, c128* out, const cx<T>* zbase, size_t zsp, size
                   const PoleState* st, int npoles, c128 phase, c128 rinf_phase, double loss_coef, double eta, int W,
                   const c128* tw64, const Geo& g, hipStream_t s) {
   dim3 grid(g.ny, g.ncomp);
-#define L_(NN)                                                                                                     \
-  hipLaunchKernelGGL((k_final<T, NN>), grid, dim3(RowCfg<NN>::WG), 0, s, w, out, zbase, zsp, zsi, xacc, xsp, st, \
-                     npoles, phase, rinf_phase, loss_coef, eta, W, tw64, g.nx, g.ny, g.fsz)
+  // Complex128 rows of 512 and more whose workgroups come in multiples of 1024, four for each CU: then
+  // enough waves wait for memory with one load a thread, and more of them only spread the
+  // requests (all of a term's -> one at a time, us: 1024^2 with 16 poles 254 -> 203, 2048^2 with 8 504 -> 426,
+  // 512^2 vector 136 -> 116).  With fewer or a part of 1024 left over the chain counts: 2048 x 64
+  // 165 -> 620, 1536^2 287 -> 340, 768^2 152 -> 164, 512^2 122 -> 155; complex64 1024^2 122 -> 165; shorter rows
+  // 384 x 1024 vector 108 -> 115, 64 x 2048 vector 89 -> 116.  (Both forms sum in the same order.)
+  const bool full = sizeof(T) == sizeof(double) && (g.ny * g.ncomp) % 1024 == 0;
+#define F_(NN, FULL)                                                                                              \
+  hipLaunchKernelGGL((k_final<T, NN, FULL>), grid, dim3(RowCfg<NN>::WG), 0, s, w, out, zbase, zsp, zsi, xacc, xsp, \
+                     st, npoles, phase, rinf_phase, loss_coef, eta, W, tw64, g.nx, g.ny, g.fsz)
+#define L_(NN)                                                 \
+  if (full && NN >= 512)                                       \
+    F_(NN, (NN >= 512 && sizeof(T) == sizeof(double)));        \
+  else                                                         \
+    F_(NN, false);
   HP_DISPATCH_N(g.nx, L_)
+#undef F_
 #undef L_
 }
 

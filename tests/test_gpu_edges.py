@@ -304,3 +304,27 @@ def test_row_pass_of_many_workgroups_sums_alike(ncomp, nx, ny, npoles, precision
     for k in range(npoles):
         assert np.array_equal(got[k], plan.solve(k, w).cpu().numpy()), k
     plan.close()
+
+
+@pytest.mark.parametrize("ncomp,nx,ny,npoles,precision,restart", [
+    (1, 64, 64, 8, 0, 30), (2, 192, 64, 3, 0, 3), (1, 384, 128, 5, 0, 4), (2, 512, 512, 3, 0, 4), (1, 512, 512, 3, 0, 4),
+    (1, 768, 1024, 3, 0, 3), (1, 1024, 1024, 2, 0, 5), (1, 1024, 64, 5, 0, 30), (2, 1536, 512, 2, 0, 3),
+    (1, 1536, 64, 3, 0, 4), (1, 2048, 1024, 2, 0, 3), (2, 2048, 64, 3, 0, 4), (1, 256, 64, 4, 1, 5),
+    (2, 512, 512, 2, 1, 4), (1, 2048, 1024, 2, 1, 3)])
+def test_weighted_sum_of_the_solutions(ncomp, nx, ny, npoles, precision, restart):
+    """The step's field without edge loss is e^{-iK} (r_inf w + sum a_k x_k) of its own solutions: few
+    and many rows of every length, odd and even numbers of terms, with and without solutions
+    accumulated over restarts.  Each side rounds every term, and the sum's inverse transform
+    log2 nx stages: 16 eps (terms + log2 nx) over the terms' norms."""
+    _cuda()
+    wl = workload(N=nx, ny=ny, ncomp=ncomp, W=8, eta=0.0, npoles=npoles, medium=("sine", 0.02, 1.0), w0=2.0, tol=1e-9)
+    plan = gpu_plan(wl, precision=precision, restart=restart)
+    f, w = wl["fit"], wl["w"]
+    out = plan.step(to_gpu(w), to_gpu(wl["n2"])).cpu().numpy()
+    iters = plan.stats()[0]
+    xs = [plan.solution(k).cpu().numpy() for k in range(npoles)]
+    ph = np.exp(-1j * inputs.K0 * wl["cfg"]["dz"])
+    ref = ph * (f["r_inf"] * w + sum(a * x for a, x in zip(f["residues"], xs)))
+    size = abs(f["r_inf"]) * np.linalg.norm(w) + sum(abs(a) * np.linalg.norm(x) for a, x in zip(f["residues"], xs))
+    plan.close()
+    assert np.linalg.norm(out - ref) <= 16 * 2.2e-16 * (sum(iters) + np.log2(nx)) * size
