@@ -59,7 +59,9 @@ __device__ __forceinline__ float wsumf(float v) {
 // d_k = (k / 3 - 1, k % 3 - 1).  The weight of (co, ci, k) is read at
 // co * wso + ci * wsi + (flip ? 8 - k : k): the forward pass uses wso = Cin*9,
 // wsi = 9; the data gradient runs the same loop with the channel roles swapped
-// and the taps flipped.
+// and the taps flipped.  GRAD: any ConvOut; else bias and ReLU into y alone (the forward pass, which
+// the other cases' address arithmetic cost 0.5 to 1 us a launch).
+template <bool GRAD>
 __global__ __launch_bounds__(256) void k_conv3(const float* __restrict__ x, const float* __restrict__ w,
                                                const ConvOut out, int cin, int cout, int H, int W, int wso, int wsi,
                                                int flip) {
@@ -100,7 +102,11 @@ __global__ __launch_bounds__(256) void k_conv3(const float* __restrict__ x, cons
   for (int c = 0; c < COB; ++c) {
     const int co = co0 + c;
     if (co >= cout) break;
-    conv_store(out, acc[c], b, co, cout, plane, (size_t)oy * W + ox);
+    const size_t p = (size_t)oy * W + ox;
+    if (GRAD)
+      conv_store(out, acc[c], b, co, cout, plane, p);
+    else
+      out.y[((size_t)b * cout + co) * plane + p] = fmaxf(acc[c] + out.bias[co], 0.f);
   }
 }
 
@@ -1099,7 +1105,9 @@ void conv3_any(hp_unet n, const ConvIn& in, const float* w, const ConvOut& out, 
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, n->stream, n->xb, n->wpk, out, cin, cout, H, W);
   } else {
     dim3 grid(((W + TILE - 1) / TILE) * ((H + TILE - 1) / TILE), (cout + COB - 1) / COB, B);
-    hipLaunchKernelGGL(k_conv3, grid, dim3(256), 0, n->stream, in.x, w, out, cin, cout, H, W, wso, wsi, flip);
+    const bool fwd = out.bias && out.relu && !out.mask && out.csplit == cout;
+    hipLaunchKernelGGL(fwd ? k_conv3<false> : k_conv3<true>, grid, dim3(256), 0, n->stream, in.x, w, out, cin, cout, H,
+                       W, wso, wsi, flip);
   }
 }
 
