@@ -183,9 +183,9 @@ int hp_set_guess(hp_plan plan, int mode);
  * no arithmetic, only how the shifted solves are launched).  The column
  * pass of the preconditioner is built for three LDS budgets per workgroup (20,
  * 40 and 80 KB: one to four complex128 columns of 1024 at once, more for
- * complex64 or shorter columns; complex128 vector columns of 1024 and more take
- * 80 KB in the middle variant too); which is fastest depends on the grid, the precision and the
- * number of poles.  hp_autotune takes one step E_in -> E_out
+ * complex64 or shorter columns; the middle variant takes 80 KB for complex128
+ * vector columns of 1024 and more where a launch has enough of them); which is
+ * fastest depends on the grid, the precision and the number of poles.  hp_autotune takes one step E_in -> E_out
  * with each variant untimed, then `reps` (1..100) timed steps each from the
  * same E_in, keeps the fastest variant in the plan for every later call, and
  * ends with one step by it, so E_out and hp_get_stats are that variant's.

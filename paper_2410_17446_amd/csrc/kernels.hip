@@ -1617,7 +1617,7 @@ void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi,
     if (g.ncomp == 1)                                                                                          \
       hipLaunchKernelGGL((k_col<T, C, NN, 1, LB, MODE>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, IN, OUT,  \
                          OSP, OSI, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
-    else if constexpr (LB != kColLds[1] || !WIDE_(NN, 2))                                                      \
+    else                                                                                                       \
       hipLaunchKernelGGL((k_col<T, C, NN, 2, LB, MODE>), grid, dim3(ColCfg<T, C, NN, LB>::WG), 0, s, IN, OUT,  \
                          OSP, OSI, dzbase, dzsp, st, list, mu_x, mu_y, tw, g.fsz, sc);                         \
   }
@@ -1652,16 +1652,23 @@ void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi,
   }
   // Complex128 vector fields with columns of 1024 and more take the largest budget in the
   // middle variant too: their pass writes twice what it reads, and one or two columns at a
-  // time are a small part of each line (a step, 40 and 80 KB: 2048^2 with 8 poles, 13.90 and
-  // 12.93 ms; with 12, 1024 x 2048, 9.23 and 8.48; 1536^2, 12.41 and 11.93; 512 x 1024, 2.14 and
-  // 2.13; columns of 768 and 384, 1.63 and 1.72, 0.80 and 0.84; scalar fields at 1024^2, 1.53 and
-  // 1.55; complex64 storage, 2-6 % more).
-#define WIDE_(NN, NCOMP) ((NCOMP) == 2 && sizeof(T) == sizeof(double) && (NN) >= 1024)
+  // time are a small part of each line.  It has to leave every CU a workgroup, though, and columns
+  // of 1536, two at a time instead of one, lose from about 1024 workgroups on.  us a launch, 40 and
+  // 80 KB: 2048^2 with 1, 4 poles 140 and 127, 613 and 526; 1024^2 with 4, 8 116 and 112, 221 and 214; 64 x 1024
+  // with 2, 4, 8 (64, 128, 256 workgroups) 17.8 and 20.9, 18.6 and 21.7, 23.2 and 22.9; 128 x 2048 with 1 (128)
+  // 20.2 and 23.1, 256 x 2048 (256) 26.6 and 24.3; columns of 1536, 64, 384 and 512 with 4, 2, 1 (256, 768, 512)
+  // 23.4 and 22.1, 49.7 and 47.8, 35.3 and 32.3, 1536^2 with 1, 4 89.8 and 98.7, 321 and 350.  Shorter columns and
+  // scalar fields: a step of 768 and 384 1.63 and 1.72 ms, 0.80 and 0.84, 1024^2 1.53 and 1.55;
+  // complex64 storage 2-6 % more.
+  auto wide = [&](int nn, int gc) {
+    const size_t wgs = (size_t)(g.nx / gc) * g.ncomp * list.n;
+    return g.ncomp == 2 && sizeof(T) == sizeof(double) && nn >= 1024 && wgs >= 256 && (nn != 1536 || wgs < 1024);
+  };
 #define L_(NN)                                                                                                 \
   {                                                                                                            \
     if (g.col_variant == 0)                                                                                    \
       COLV_(NN, kColLds[0])                                                                                    \
-    else if (g.col_variant == 2 || WIDE_(NN, g.ncomp))                                                         \
+    else if (g.col_variant == 2 || wide(NN, ColCfg<T, C, NN, kColLds[2]>::GC))                                 \
       COLV_(NN, kColLds[2])                                                                                    \
     else                                                                                                       \
       COLV_(NN, kColLds[1])                                                                                    \
@@ -1670,7 +1677,6 @@ void launch_col(const Basis<cx<T>>& basis, cx<T>* zbase, size_t zsp, size_t zsi,
 #undef L_
 #undef COLV_
 #undef COLM_
-#undef WIDE_
 }
 
 static int apply_groups(const Geo& g) {

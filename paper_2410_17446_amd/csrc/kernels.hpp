@@ -16,7 +16,7 @@ struct StencilCoef {
 struct Geo {
   int nx, ny, ncomp;
   size_t fsz;           // nx * ny
-  int col_variant = 1;  // column-pass LDS budget: 0, 1, 2 = 20, 40 (long vector columns: 80), 80 KB
+  int col_variant = 1;  // column-pass LDS budget: 0, 1, 2 = 20, 40 (many long vector columns: 80), 80 KB
 };
 
 // Row DST-I of the unknowns of a complex128 field (physical, row-major): out

@@ -328,3 +328,27 @@ def test_weighted_sum_of_the_solutions(ncomp, nx, ny, npoles, precision, restart
     size = abs(f["r_inf"]) * np.linalg.norm(w) + sum(abs(a) * np.linalg.norm(x) for a, x in zip(f["residues"], xs))
     plan.close()
     assert np.linalg.norm(out - ref) <= 16 * 2.2e-16 * (sum(iters) + np.log2(nx)) * size
+
+
+@pytest.mark.parametrize("nx,ny,npoles", [(64, 1024, 7), (64, 1024, 8), (128, 1024, 4), (64, 1536, 3), (64, 1536, 4),
+                                          (192, 1536, 6), (64, 2048, 3), (64, 2048, 4)])
+def test_column_budgets_change_no_bit(nx, ny, npoles):
+    """Long complex128 vector columns take 40 or 80 KB of LDS by the number of workgroups in the round (a
+    pole alone: 40; from 256 on 80, of 1536 up to 1024), and the outer variants 20 and 80: the same
+    solutions."""
+    _cuda()
+    wl = workload(N=nx, ny=ny, ncomp=2, W=8, npoles=npoles, medium=("sine", 0.02, 1.0), w0=2.0, tol=1e-8)
+    plan = gpu_plan(wl, restart=4)
+    plan.set_fixed_iters([3] * npoles)
+    w, n2 = to_gpu(wl["w"]), to_gpu(wl["n2"])
+    got = []
+    for variant in (1, 0, 2):
+        plan.set_launch(variant)
+        plan.step(w, n2)
+        got.append([plan.solution(k).cpu().numpy() for k in range(npoles)])
+    plan.set_launch(1)
+    got.append([plan.solve(k, w).cpu().numpy() for k in range(npoles)])
+    plan.close()
+    for other in got[1:]:
+        for k in range(npoles):
+            assert np.array_equal(got[0][k], other[k]), k
