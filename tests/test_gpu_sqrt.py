@@ -194,3 +194,37 @@ def test_sqrt_form_mixed_precision_and_previous_guesses():
     it_prev, rr = prev.stats()
     assert rel_l2(out, ref) < 1e-8 and max(rr) <= 1e-10
     assert sum(it_prev) <= sum(it_ref), (it_prev, it_ref)
+
+
+@pytest.mark.parametrize("dx,status", [(0.25, 2), (1.0, 0)])  # as in the stability check above
+def test_form_switch_while_its_stream_is_captured(dx, status):
+    """hp_set_form of a plan that has its stage fields touches no stream (as before the check ran on
+    the device), so it may be called while its stream is captured, with the same status; the graph
+    around it replays as the eager calls go, between eager work."""
+    import ctypes as C
+    torch = _cuda()
+    from paper_2410_17446_amd import hp
+    wl = workload(N=64, W=8, dx=dx)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        plan, _ = _plan(wl, sf.cauchy_sqrt_pf(25, 1.0), 1e-10, 4)
+        assert plan.set_form(hp.HP_FORM_SQRT, 8) == status
+        x = to_gpu(inputs.random_field(64, 1, seed=2))
+        y = torch.zeros_like(x)
+        L = hp.lib()
+        solve = lambda: L.hp_apply_preconditioner_noalloc(plan.handle, 3, C.c_void_p(x.data_ptr()), C.c_void_p(y.data_ptr()))
+        assert solve() == 0
+        s.synchronize()
+        ref = y.clone()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            got = plan.set_form(hp.HP_FORM_SQRT, 8)
+            assert solve() == 0
+        assert got == status
+        for _ in range(3):
+            y.zero_()
+            g.replay()
+            s.synchronize()
+            assert torch.equal(y, ref)
+            assert plan.set_form(hp.HP_FORM_SQRT, 8) == status
+    plan.close()
