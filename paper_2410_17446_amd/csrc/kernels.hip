@@ -1700,12 +1700,13 @@ void launch_row_apply(const cx<T>* zbase, size_t zsp, size_t zsi, const cx<T>* d
   const int nblk = row_apply_blocks<T>(g);
   // one workgroup per (row block, pole), row blocks padded to a multiple of 8
   dim3 grid((unsigned)((nblk + 7) / 8 * 8) * (unsigned)list.n);
-  // The next vector's loads ahead up to 1024 workgroups, one for each SIMD; beyond, other waves hide
-  // the latency and the registers are better spent on more of those.  The form changes no
-  // sum.  us per launch over a cycle, ahead and not: one pole 256^2 17.3 and 19.6, 384^2 17.4 and 20.1;
+  // The next vector's loads ahead up to 1024 workgroups, one for each SIMD (2048 with complex64
+  // storage, half the bytes in flight); beyond, other waves hide the latency and the registers are
+  // better spent on more of those.  The form changes no sum.  us per launch over a cycle, ahead and not: one pole 256^2 17.3 and 19.6, 384^2 17.4 and 20.1;
   // 16 poles 64^2 (128 workgroups) 15.8 and 18.0, 256^2 (2048) 59.0 and 58.3, 384^2 152 and 147, vector
-  // 256^2 125 and 112, 384^2 303 and 283, 256 x 1024 352 and 317, 384 x 768 429 and 381.
-  const bool ahead = (size_t)nblk * list.n < 1024;
+  // 256^2 125 and 112, 384^2 303 and 283, 256 x 1024 352 and 317, 384 x 768 429 and 381; complex64, a
+  // step of 256 x 128 (1024) 477 and 485, launches of 256^2 (2048) 25.4 and 25.1.
+  const bool ahead = (size_t)nblk * list.n < (sizeof(T) == sizeof(float) ? 2048 : 1024);
 #define R_(NN, NC, AH)                                                                                          \
   hipLaunchKernelGGL((k_row_apply<T, C, NN, NC, AH>), grid, dim3(ApplyCfg<NN, NC>::WG), 0, s, zbase, zsp, zsi,  \
                      dzbase, dzsp, pbase, psp, basis, coef, st, list, nblk, part, tw, g.ny, g.fsz, sc)

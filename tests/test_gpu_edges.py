@@ -289,9 +289,10 @@ def test_shared_first_column_transform_at_the_lines_of_its_rule(ncomp, nx, ny, n
 @pytest.mark.parametrize("ncomp,nx,ny,npoles,precision", [
     (1, 64, 2048, 4, 0), (2, 64, 1024, 5, 0), (1, 128, 1024, 5, 0), (2, 128, 512, 5, 0), (1, 192, 512, 5, 0),
     (2, 192, 256, 5, 0), (1, 256, 512, 5, 0), (2, 256, 256, 5, 0), (1, 384, 256, 5, 0), (2, 384, 256, 5, 0),
-    (2, 64, 1024, 5, 1), (1, 192, 512, 5, 2), (2, 384, 256, 5, 1)])
+    (2, 64, 1024, 5, 1), (1, 192, 512, 5, 2), (2, 384, 256, 5, 1), (2, 64, 1024, 9, 1), (1, 192, 512, 9, 2),
+    (2, 384, 256, 9, 1)])
 def test_row_pass_of_many_workgroups_sums_alike(ncomp, nx, ny, npoles, precision):
-    """Rounds of 1024 row workgroups and more run the form without loads ahead, a pole alone the one
+    """Rounds of 1024 row workgroups and more (complex64 storage: 2048) run the form without loads ahead, a pole alone the one
     with them: the same sums, so after five Arnoldi steps a pole's solution in the step is bit for
     bit the one it has alone (the sizes stay below the shared column transform's)."""
     _cuda()
